@@ -140,6 +140,30 @@ def test_canvas_ranges_and_misaligned_output(torch):
     assert buf[0].item() == SENTINEL  # nothing written before the view
 
 
+@pytest.mark.parametrize("cw,ch", [(3, 2), (67, 1), (64, 96), (6145, 1), (2047, 3), (111, 111)])
+def test_any_plane_size_and_output_offset(torch, cw, ch):
+    """Outputs whose planes start at every offset from a 16-byte boundary and at several from
+    a 128-byte line; planes of one short run, of exactly one run, and one and a few pixels
+    past it. Nothing outside the output is written."""
+    rng = np.random.default_rng(cw)
+    rois = W.random_rois(rng, 40, 2, 700, 120, 1, min(cw, 300), min(ch, 100))
+    frames = W.random_frames_np(2, 120, 700, 9)
+    frames_d = torch.from_numpy(frames).cuda()
+    plan = tg.plan_pack(rois, cw, ch, 700, 120, 2, 0)
+    n = min(plan.n_canvases, 3)
+    want = oracle.stitch(frames, rois, oracle_plan(plan), 0, n, cw, ch, W.MEAN, W.STD, W.PAD)
+    dplan = tg.DevicePlan(rois, plan)
+    for off in (0, 1, 2, 3, 4, 5, 6, 7, 13, 40, 63):
+        say("offset", off, cw, ch)
+        buf = torch.full((n * 3 * cw * ch + 128,), SENTINEL, dtype=torch.int16, device="cuda")
+        out = buf[off:off + n * 3 * cw * ch].view(n, 3, ch, cw)
+        tg.stitch(frames_d, dplan, 0, n, cw, ch, W.MEAN, W.STD, W.PAD, out)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(out.cpu().numpy().view(np.uint16), want)
+        rest = torch.cat([buf[:off], buf[off + n * 3 * cw * ch:]])
+        assert bool((rest == SENTINEL).all())
+
+
 def test_corrupt_plan_entries_are_skipped(torch):
     """Out-of-range ids, wrong canvas, rects leaving canvas or frame: read as pad."""
     rng = np.random.default_rng(6)
