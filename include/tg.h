@@ -347,8 +347,8 @@ typedef struct {
 
 /*
  * Device scratch tg_unstitch needs for n_boxes boxes over a plan of n_rois RoIs (0 when
- * n_boxes <= 0): the compaction's look-back words (8 bytes per 1024 boxes and one more,
- * rounded up to 16) and 24 bytes of patch record per RoI.
+ * n_boxes <= 0): counts of kept boxes (8 bytes per 1024 boxes and 8 more, rounded up to
+ * 16) and 24 bytes per RoI for the plan laid out by canvas.
  */
 size_t tg_unstitch_workspace_bytes(int32_t n_boxes, int32_t n_rois);
 
@@ -373,14 +373,13 @@ size_t tg_unstitch_workspace_bytes(int32_t n_boxes, int32_t n_rois);
  * Returns TG_E_INVAL on null pointers (unless n_boxes == 0, which only writes
  * *n_out = 0) or n_boxes < 0, TG_E_WORKSPACE when the workspace is too small or not
  * 16-byte aligned, TG_E_HIP on launch failure, TG_E_INVAL for a rule other than 0 or 1.
- * *n_out = TG_E_INTERNAL reports a device-side failure of the compaction.
  */
 int tg_unstitch(const tg_unstitch_args *args, void *stream);
 
 /* Largest n_boxes tg_unstitch_noalloc accepts. */
 #define TG_UNSTITCH_NOALLOC_MAX_BOXES (1 << 24)
-/* Largest plan (n_rois) for which tg_unstitch_noalloc keeps patch records in its
- * scratch array; larger plans are read without them, with the same results. */
+/* Largest plan (n_rois) that tg_unstitch_noalloc lays out by canvas in its scratch array;
+ * larger plans are read as they are, with the same results. */
 #define TG_UNSTITCH_NOALLOC_MAX_ROIS (1 << 17)
 
 /*

@@ -208,3 +208,85 @@ def test_patch_records_with_small_canvases(torch, rule):
     for clip in (0, 1):
         say("records, small canvases", per_canvas, "rule", rule, "clip", clip)
         check(torch, boxes, canv, rois, plan, clip, rule=rule)
+
+
+def _grid_plan(sizes, cell, cw):
+    """A plan of one canvas per entry of `sizes`, that many cell x cell patches in rows."""
+    per = cw // cell
+    place, rois, begin = [], [], [0]
+    for c, n in enumerate(sizes):
+        for j in range(n):
+            place.append((c, cell * (j % per), cell * (j // per)))
+            rois.append((0, (7 * len(rois)) % 300, (3 * len(rois)) % 200, cell, cell))
+        begin.append(len(rois))
+    order = np.arange(len(rois), dtype=np.int32)
+    return (np.array(rois, np.int32),
+            tg.Plan(np.array(place, np.int32), order, np.array(begin, np.int32), len(sizes)))
+
+
+@pytest.mark.parametrize("sizes", [[16, 17, 32, 33, 64, 65, 0, 1], [300, 257, 256, 129],
+                                   [1000, 5, 96, 97], [15, 16, 17, 18]])
+@pytest.mark.parametrize("rule", [0, 1])
+def test_band_layout_sizes(torch, sizes, rule):
+    """Canvases around the smallest count with band words and around whole 32-patch words,
+    in calls of every lanes-per-box width and of the gathered path; boxes on patch edges,
+    with NaN and infinite corners and inverted, whole-canvas boxes, bad canvases."""
+    rois, plan = _grid_plan(sizes, 9, 300)
+    rng = np.random.default_rng(len(rois))
+    most = -(-(1 << 21) * len(sizes) // len(rois)) + 7  # enough boxes for the laid out path
+    for n in (min(most, 140000), 16384, 16385):
+        c, s = rng.uniform(-5, 305, (n, 2)), rng.uniform(0, 30, (n, 2))
+        boxes = np.concatenate([c - s / 2, c + s / 2], 1).astype(np.float32)
+        boxes[:4000] = np.round(boxes[:4000])
+        boxes[4000:4050, 0] = np.nan
+        boxes[4050:4100, 2] = np.inf
+        boxes[4100:4150, 1] = -np.inf
+        boxes[4150:4200] = boxes[4150:4200][:, [2, 3, 0, 1]]
+        boxes[4200:4250] = [-10, -10, 400, 400]
+        canv = rng.integers(-1, plan.n_canvases + 1, n).astype(np.int32)
+        say("bands", sizes, rule, n)
+        check(torch, boxes, canv, rois, plan, 1, rule=rule)
+
+
+def test_laid_out_path_with_corrupt_plans(torch):
+    """Positions holding no RoI, RoIs placed on another canvas, and canvas_begin that does not
+    cut the plan into consecutive segments: the same boxes in calls that lay the plan out
+    and in calls that gather it."""
+    rois, plan = _grid_plan([100, 200, 300, 40], 9, 300)
+    rng = np.random.default_rng(3)
+    n = 20000
+    c = rng.uniform(-5, 305, (n, 2))
+    boxes = np.concatenate([c - 6, c + 6], 1).astype(np.float32)
+    canv = rng.integers(0, 4, n).astype(np.int32)
+    for what in ("ids", "begin"):
+        place, order, begin = plan.place.copy(), plan.order.copy(), plan.canvas_begin.copy()
+        if what == "ids":
+            order[::7], order[3::31] = 100000, -4
+            place[5::11, 0] = 3
+        else:
+            begin[:] = [50, 310, 250, 700, 600]  # overlapping, empty, past the end
+        dplan = tg.DevicePlan(rois, tg.Plan(place, order, begin, 4))
+        for rule in (0, 1):
+            say("corrupt", what, rule)
+            whole = run_unstitch(torch, boxes, canv, rois, plan, 1, dplan, rule)
+            parts = [run_unstitch(torch, boxes[k:k + 5000], canv[k:k + 5000], rois, plan, 1, dplan,
+                                  rule)[0] for k in range(0, n, 5000)]
+            assert (whole[0] >= 0).any()
+            np.testing.assert_array_equal(whole[0], np.concatenate(parts))
+            assert whole[2] == (whole[0] >= 0).sum()
+            np.testing.assert_array_equal(whole[1]["box"], np.flatnonzero(whole[0] >= 0))
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 255, 256, 257])
+def test_few_boxes(torch, n):
+    """The one-workgroup path and the first size past it, by boxes and by RoIs."""
+    rng = np.random.default_rng(n)
+    for n_rois in (1, 128, 129):
+        rois = W.random_rois(rng, n_rois, 2, 400, 300, 4, 60, 60)
+        plan = tg.plan_pack(rois, 160, 160, 400, 300, 2, 0)
+        c, s = rng.uniform(0, 160, (n, 2)), rng.uniform(0, 40, (n, 2))
+        boxes = np.concatenate([c - s / 2, c + s / 2], 1).astype(np.float32)
+        canv = rng.integers(-1, plan.n_canvases + 1, n).astype(np.int32)
+        for rule in (0, 1):
+            say("few", n, n_rois, rule)
+            check(torch, boxes, canv, rois, plan, 1, rule=rule)
