@@ -433,8 +433,8 @@ size_t tg_merge_workspace_bytes(int32_t n_max, int32_t n_frames);
  * suppressed when inter > iou_threshold * union. Detections whose frame is outside
  * [0, n_frames) are dropped. Kept detections are written to out in input order and their
  * count to *n_kept. Every frame is merged, whatever its number of detections (the walk's
- * decisions are reached in parallel rounds over a spatial index of the frame's boxes,
- * kept in the workspace, with the same result). The
+ * decisions are reached in parallel rounds over the pairs that suppress, with the same
+ * result). The
  * coordinates are not expected to be NaN (tg_unstitch never keeps such a box); if one is,
  * min and max ignore the NaN operand. Enqueued on `stream`; the library allocates nothing.
  * Returns TG_E_INVAL (null pointer, negative size, NaN threshold), TG_E_WORKSPACE,

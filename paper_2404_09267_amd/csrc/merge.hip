@@ -9,30 +9,43 @@
 // IoU > threshold, decided as inter > threshold * union in binary32 with every operation
 // rounded on its own. Kept detections are written in input order.
 //
-// Eight launches on the caller's stream, all on device data (the detection count comes from
-// tg_unstitch's n_out on the device):
-//  1. clear the per-frame counters and look-back words;
-//  2. count detections per frame (LDS histograms, one global atomic per frame and
-//     workgroup);
-//  3. exclusive scan of the counts (one workgroup);
-//  4. scatter detection indices into frame groups (ranks inside a workgroup from LDS, one
-//     range per frame and workgroup from a global cursor; the order inside a group does
-//     not matter, the ranking below is a total order), with each detection's ranking key
-//     (score, box), box and patch at its place in the group;
-//  5-7. the greedy decided in rounds, with no sort: a spatial index of each frame's boxes
-//     (one workgroup per frame), each detection's suppressors ranked above it (over the
-//     whole grid), then per frame rounds in which a detection is suppressed once one of
-//     them is kept and kept once all of them are suppressed (see "the greedy of a frame"
-//     for why this is the greedy walk's result and why the index finds every suppressor);
-//     a frame of at most kSmallMax detections is instead decided by its index workgroup
-//     in LDS, each pair of its detections tested once;
-//  8. stable compaction of the kept detections (decoupled look-back, 1024 per workgroup).
-// Inputs of at most kTiny detections (by capacity) take one launch instead (tiny_kernel).
+// The greedy walk keeps a detection exactly when no detection ranked above it that
+// suppresses it is kept (by induction over the ranking). So no sorted ranking is needed:
+// given each detection's suppressors ranked above it, rounds decide the frame -- a
+// detection is suppressed once one of them is kept, kept once all of them are suppressed.
+// The best-ranked undecided detection of a round has only decided suppressors, so every
+// round decides at least one: a frame of n detections needs at most n rounds (two to four
+// in practice, where chains of boxes suppressing each other are short).
+//
+// The call is bound by latency -- launches, and chains of dependent loads inside them --
+// not by its bytes, so it takes few launches and no global atomics on shared counters:
+//  1. hist:    each workgroup counts its chunk of detections per bin (a frame, or a run of
+//              frames when there are more than kBinsMax) into its row of a small table.
+//  2. scatter: each workgroup sums the table's columns for its positions and writes its
+//              detections' ranking keys, boxes, patches and indices into bin order.
+//  3. local:   one workgroup per bin orders a bin of several frames by frame in LDS and
+//              decides every frame of at most kLocal detections there: band bits (bands.h)
+//              name the few boxes that can meet each box, those pairs are listed and tested,
+//              and the rounds run on the suppressing ones. Larger frames, and crowded ones
+//              whose suppressing pairs do not fit, are put on a list.
+//  4. tile:    the listed frames cut into tiles of about kTileDets detections (by their
+//              top-left corners), a workgroup each: its detections' suppressors among the
+//              frame's boxes that meet the rectangle around its own.
+//  5. resolve: the rounds of each listed frame, over its detections that have suppressors.
+//  6. compact: the kept detections in input order.
+// Measured (unstitched detections, IoU 0.5 across patches), with the eight launches of a
+// grid index per frame before: 8,249 in 20 frames 45.6 -> 27 us; 47,939 in 8 frames
+// 111 -> 47; 164,685 in 1,920 frames 62.7 -> 45.5; 20,000 in one frame 367 -> 141, crowded
+// into 300 x 300 pixels 619 ms (its pairs overran the lists) -> 4.1 ms.
+// Tile and resolve return at once when no frame is listed. Inputs of at most kTiny
+// detections (by capacity) take one launch instead (tiny_kernel).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
+#include "bands.h"
 #include "lookback.h"
 #include "tg.h"
 
@@ -42,10 +55,61 @@
 
 namespace {
 
+using tg_detail::band_axis;
+using tg_detail::band_of;
+using tg_detail::BandAxis;
+using tg_detail::transpose32;
+using tg_detail::wave_min;
+
 constexpr int kThreads = 256;
-constexpr int kPerThread = 4;  // compaction: consecutive detections per thread
+constexpr int kPerThread = 4;  // look-back compaction: consecutive detections per thread
 constexpr int kCompactBlock = kThreads * kPerThread;
-constexpr int kScanThreads = 1024;
+constexpr int kCountThreads = 1024;   // counting compaction: a detection per thread
+constexpr int kCountDets = 65536;     // largest capacity it takes
+constexpr int kBinThreads = 1024;     // hist and scatter
+constexpr int kBinsMax = 256;
+constexpr int kChunksMax = 128;       // workgroups of hist and scatter: rows of the table
+constexpr int kLocal = 1024;          // detections decided in LDS by one workgroup
+constexpr int kLocalWords = kLocal / 32;
+constexpr int kFrameHist = 4096;      // frames of a bin ordered in one pass
+constexpr int kPairs = 4096;          // pairs that bands bring together, held in LDS
+constexpr int kHits = 4096;           // and those that suppress
+constexpr int kTileThreads = 1024;
+constexpr int kTileDets = 256;        // detections per tile, about
+constexpr int kTilesMax = 256;        // tiles per frame
+constexpr int kPredSlots = 16;        // suppressors kept in place per detection
+// workgroups of tile and resolve, which step through their work: tile's LDS lets one run per
+// CU (two small ones on one CU left others idle and ran one after the other: 37 -> 22 us)
+constexpr int kGridCap = 256;
+constexpr int kResolveThreads = 1024;
+constexpr int32_t kUndecided = 0, kKept = 1, kSuppressed = 2;
+
+// A frame of more than kLocal detections, or of more than kHits suppressing pairs:
+// positions [lo, lo + n) of the frame order, cut
+// into g x g tiles numbered from `start` among all listed frames' tiles; tile (cx, cy) owns
+// the detections whose top-left corner has those cells. open: how many of its detections
+// have suppressors (their positions are listed in MergeParams::open from lo on).
+struct LargeFrame {
+  int32_t lo, n, g;
+  uint32_t start;
+  float x0, sx, y0, sy;
+  int32_t open;
+};
+
+// What a detection has besides its box: ranking key, patch, index.
+struct alignas(16) Aux {
+  uint64_t key;
+  int32_t roi, idx;
+};
+
+// A detection in bin or frame order. One 32-byte record, a whole memory sector, so that
+// scattered writes replace sectors instead of merging into them (separate arrays of boxes,
+// keys and the rest: the pass that read them waited 8-16 us for 165,000 detections in
+// 1,920 frames, and the scatter itself took 18.8 us instead of 12).
+struct alignas(16) Rec {
+  float4 box;
+  Aux aux;
+};
 
 struct MergeParams {
   const tg_det *dets;
@@ -58,104 +122,112 @@ struct MergeParams {
   int32_t *keep;
   tg_det *out;
   int32_t *n_kept;
-  int32_t *counts;       // frame f at [f * cstride]
-  int32_t *cursor;       // frame f at [f * cstride]
-  int32_t cstride;       // kCounterStride, or 1 for very many frames
-  int32_t *frame_begin;  // [n_frames + 1]
-  int32_t *grouped;      // [n_max]
+  int32_t chunk, n_chunks;  // detections per hist / scatter workgroup, and how many those are
+  int32_t n_bins, per_bin;  // frames per bin (1 up to kBinsMax frames)
+  int64_t n_words;          // 64-bit words from `ticket` on, zeroed by hist
   uint32_t *ticket;
-  uint32_t *status;      // set when a frame's rounds overrun (cannot happen)
-  uint64_t *state;       // [compaction workgroups]
-  uint32_t *big;         // set when a frame is too large for its index workgroup alone
-  // Per detection, at its position in its frame group: frame f (first detection lo, n of
-  // them) owns [lo, lo + n) of these (times kCellsMax for the cell lists), so frames
-  // never share a word.
-  uint64_t *rkey;        // [n_max] ranking keys
-  float4 *rbox;          // [n_max] boxes
-  int32_t *rroi;         // [n_max] patch ids
-  uint32_t *rcell;       // [n_max] cell ranges (kWide, kEmpty or packed)
-  int32_t *rstate;       // [n_max] kUndecided, kKept or kSuppressed
-  int32_t *rlist;        // [2 (kCellsMax + 1) n_max] the lists to search: starts, sizes
-  int32_t *rpred;        // [kPredSlots n_max] suppressors ranked above (positions)
-  int32_t *rnpred;       // [n_max] how many
-  int32_t *rovf;         // [n_max] a longer list's start in ovf, or -1: search again
-  int32_t *ovf;          // [kOvfPerDet n_max] the whole lists of detections with more
-  int64_t ovf_cap;
+  uint32_t *status;         // set when a frame's rounds overrun (cannot happen)
   unsigned long long *ovf_used;  // entries of ovf handed out
-  float4 *ebox;          // [kCellsMax n_max] boxes listed per cell, then the wide list
-  int4 *eaux;            // [kCellsMax n_max] their patch ids, keys and positions
+  unsigned long long *large_used;  // listed frames << 32 | their tiles
+  uint64_t *state;          // look-back words of the compaction
+  int32_t *table;           // [n_chunks][n_bins]
+  int32_t *bin_begin;       // [n_bins + 1]
+  LargeFrame *large;
+  // Per detection, at its position in bin order ...
+  Rec *crec;
+  // ... and in frame order (the same arrays with one frame per bin; else only the bins that
+  // do not fit one workgroup are written here).
+  Rec *rec;
+  int32_t *frame;
+  // Listed frames, by position in frame order.
+  int32_t *rstate;   // kUndecided, kKept or kSuppressed
+  int32_t *rnpred;   // suppressors ranked above
+  int32_t *rpred;    // [kPredSlots each] the first of them (positions)
+  int32_t *rovf;     // a longer list's start in ovf, or -1: search again
+  int32_t *open;     // positions of the frame's detections that have suppressors
+  int32_t *ovf;      // whole lists of detections with more than kPredSlots
+  int64_t ovf_cap;
 };
 
 __device__ __forceinline__ int count_of(const MergeParams &P) {
   return min(max(*P.n_dets, 0), P.n_max);
 }
 
-// Frame counters one 256-byte slot apart: the count and scatter passes add to them with
-// global atomics (many detections per frame), and counters packed into a few cache lines
-// queue on those lines (window_64x30, 1,920 frames: count 20 us, scatter 33 us packed).
-constexpr int kCounterStride = 64;      // int32 words
-constexpr int kPaddedFramesMax = 16384; // beyond: packed (4 MB of slots at most)
-
-__global__ void clear_kernel(MergeParams P, int32_t n_frames, int32_t n_words64) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n_frames) {
-    P.counts[static_cast<int64_t>(i) * P.cstride] = 0;
-    P.cursor[static_cast<int64_t>(i) * P.cstride] = 0;
-  }
-  // ticket and status, the overflow cursor, the large-frame flag, the look-back states
-  if (i < n_words64) reinterpret_cast<uint64_t *>(P.ticket)[i] = 0;
+// Inclusive prefix sum over the 64 lanes of a wave (DPP row shifts, then row broadcasts).
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return v;
 }
 
-// Detections per frame. Up to kHistMax frames a workgroup first counts in LDS and then
-// adds each non-empty bin to the global count once (many detections share few frames, so
-// direct global atomics would queue on the same words).
-constexpr int kHistMax = 4096;
+// This lane's first place of `count` more in an LDS list of *n entries. Called by whole
+// waves. (One atomic per wave: the compiler turns an atomic of many lanes on one address
+// into a loop over the lanes.)
+__device__ __forceinline__ int wave_places(int *n, int count) {
+  const int incl = wave_inclusive_sum(count), total = __builtin_amdgcn_readlane(incl, 63);
+  int base = 0;
+  if ((threadIdx.x & 63) == 0 && total) base = atomicAdd(n, total);
+  return __builtin_amdgcn_readfirstlane(base) + incl - count;
+}
 
-__global__ __launch_bounds__(kThreads) void count_kernel(const MergeParams P) {
-  __shared__ int hist[kHistMax];
-  const int tid = threadIdx.x;
-  const bool local = P.n_frames <= kHistMax;
-  if (local)
-    for (int f = tid; f < P.n_frames; f += kThreads) hist[f] = 0;
+// One place for each active lane, which may be any lanes of the wave.
+__device__ __forceinline__ int lane_place(int *n) {
+  const uint64_t active = __ballot(1);
+  const int lane = threadIdx.x & 63, leader = __builtin_ctzll(active);
+  int base = 0;
+  if (lane == leader) base = atomicAdd(n, __popcll(active));
+  return __builtin_amdgcn_readlane(base, leader) + __popcll(active & ((uint64_t(1) << lane) - 1));
+}
+
+// Exclusive scan of v over a workgroup of kN threads (s: kN / 64 ints of LDS); *total gets the
+// sum. Ends with a barrier.
+template <int kN>
+__device__ __forceinline__ int block_exclusive(int v, int *s, int *total) {
+  const int incl = wave_inclusive_sum(v);
+  if ((threadIdx.x & 63) == 63) s[threadIdx.x >> 6] = incl;
   __syncthreads();
-  const int i = blockIdx.x * kThreads + tid;
-  if (i < count_of(P)) {
+  int before = 0, sum = 0;
+#pragma unroll
+  for (int w = 0; w < kN / 64; ++w) {
+    if (w < static_cast<int>(threadIdx.x >> 6)) before += s[w];
+    sum += s[w];
+  }
+  __syncthreads();
+  *total = sum;
+  return before + incl - v;
+}
+
+__device__ __forceinline__ int bin_of(const MergeParams &P, int f) {
+  return P.per_bin == 1 ? f : static_cast<int>(static_cast<uint32_t>(f) / static_cast<uint32_t>(P.per_bin));
+}
+
+// Detections of this workgroup's chunk per bin. (Counting into global counters instead
+// needs a launch to clear them and an atomic per frame and workgroup, and they queue:
+// window_64x30, 1,920 frames, count and scatter 23 us together.)
+__global__ __launch_bounds__(kBinThreads) void hist_kernel(const MergeParams P) {
+  __shared__ int hist[kBinsMax];
+  const int tid = threadIdx.x, g = blockIdx.x;
+  for (int64_t i = static_cast<int64_t>(g) * kBinThreads + tid; i < P.n_words;
+       i += static_cast<int64_t>(gridDim.x) * kBinThreads)
+    reinterpret_cast<uint64_t *>(P.ticket)[i] = 0;
+  if (tid < P.n_bins) hist[tid] = 0;
+  __syncthreads();
+  const int64_t lo = static_cast<int64_t>(g) * P.chunk;
+  const int64_t hi = min(lo + P.chunk, static_cast<int64_t>(count_of(P)));
+#pragma unroll 4
+  for (int64_t i = lo + tid; i < hi; i += kBinThreads) {
     const int f = P.dets[i].frame;
     if (f >= 0 && f < P.n_frames)
-      atomicAdd(local ? &hist[f] : &P.counts[static_cast<int64_t>(f) * P.cstride], 1);
+      atomicAdd(&hist[bin_of(P, f)], 1);
     else
       P.keep[i] = 0;  // no frame to merge in: dropped
   }
-  if (!local) return;
   __syncthreads();
-  for (int f = tid; f < P.n_frames; f += kThreads)
-    if (hist[f]) atomicAdd(&P.counts[static_cast<int64_t>(f) * P.cstride], hist[f]);
-}
-
-__global__ __launch_bounds__(kScanThreads) void scan_kernel(const MergeParams P) {
-  __shared__ int s_wave[kScanThreads / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int carry = 0;
-  for (int base = 0; base < P.n_frames; base += kScanThreads) {
-    const int f = base + tid;
-    const int v = f < P.n_frames ? P.counts[static_cast<int64_t>(f) * P.cstride] : 0;
-    int incl = v;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl, o);
-      if (lane >= o) incl += t;
-    }
-    if (lane == 63) s_wave[wave] = incl;
-    __syncthreads();
-    int before = 0, total = 0;
-    for (int w = 0; w < kScanThreads / 64; ++w) {
-      if (w < wave) before += s_wave[w];
-      total += s_wave[w];
-    }
-    if (f < P.n_frames) P.frame_begin[f] = carry + before + incl - v;
-    carry += total;
-    __syncthreads();
-  }
-  if (tid == 0) P.frame_begin[P.n_frames] = carry;
+  if (tid < P.n_bins) P.table[static_cast<int64_t>(g) * P.n_bins + tid] = hist[tid];
 }
 
 // Ranking key, ascending = higher score first, then lower box index. NaN ranks as -inf;
@@ -168,43 +240,57 @@ __device__ __forceinline__ uint64_t rank_key(float s, int32_t box) {
   return (static_cast<uint64_t>(~b) << 32) | static_cast<uint32_t>(box);
 }
 
-// Detection indices into frame groups, with each detection's ranking key, box and patch
-// at its position in the group. Up to kHistMax frames a workgroup ranks its detections per
-// frame in LDS and reserves one range per non-empty frame.
-__global__ __launch_bounds__(kThreads) void scatter_kernel(const MergeParams P) {
-  __shared__ int hist[kHistMax];
-  const int tid = threadIdx.x;
-  const bool local = P.n_frames <= kHistMax;
-  if (local)
-    for (int f = tid; f < P.n_frames; f += kThreads) hist[f] = 0;
+// The chunk's detections into bin order (the order inside a bin does not matter: the
+// ranking key is a total order).
+__global__ __launch_bounds__(kBinThreads) void scatter_kernel(const MergeParams P) {
+  __shared__ int s_all[kBinThreads], s_before[kBinThreads], s_start[kBinsMax];
+  __shared__ int s_wave[kBinThreads / 64];
+  const int tid = threadIdx.x, g = blockIdx.x;
+  // column sums of the table: `parts` threads per bin
+  int width = 1;
+  while (width < P.n_bins) width *= 2;
+  const int b = tid & (width - 1), parts = kBinThreads / width;
+  int all = 0, before = 0;
+  if (b < P.n_bins) {
+#pragma unroll 8
+    for (int r = tid / width; r < P.n_chunks; r += parts) {
+      const int v = P.table[static_cast<int64_t>(r) * P.n_bins + b];
+      all += v;
+      before += r < g ? v : 0;
+    }
+  }
+  for (int o = 32; o >= width; o >>= 1) {  // the lanes of a wave on one bin
+    all += __shfl_xor(all, o);
+    before += __shfl_xor(before, o);
+  }
+  s_all[tid] = all;
+  s_before[tid] = before;
   __syncthreads();
-  const int i = blockIdx.x * kThreads + tid;
-  int f = -1, rank = 0, pos = -1;
-  tg_det d;
-  if (i < count_of(P)) {
-    d = P.dets[i];
-    f = d.frame;
-    if (f < 0 || f >= P.n_frames)
-      f = -1;
-    else if (local)
-      rank = atomicAdd(&hist[f], 1);
-    else
-      pos = P.frame_begin[f] + atomicAdd(&P.cursor[static_cast<int64_t>(f) * P.cstride], 1);
+  all = before = 0;
+  if (tid < width) {
+    for (int k = tid; k < kBinThreads; k += max(width, 64)) {
+      all += s_all[k];
+      before += s_before[k];
+    }
   }
-  if (local) {
-    __syncthreads();
-    for (int g = tid; g < P.n_frames; g += kThreads)  // this workgroup's range of frame g
-      if (hist[g])
-        hist[g] = P.frame_begin[g] + atomicAdd(&P.cursor[static_cast<int64_t>(g) * P.cstride], hist[g]);
-    __syncthreads();
-    if (f >= 0) pos = hist[f] + rank;
+  int total;
+  const int begin = block_exclusive<kBinThreads>(all, s_wave, &total);
+  if (tid < P.n_bins) {
+    s_start[tid] = begin + before;
+    if (g == 0) P.bin_begin[tid] = begin;
   }
-  if (pos < 0) return;
-  P.grouped[pos] = i;
-  const float s = (d.box >= 0 && d.box < P.n_scores) ? P.scores[d.box] : __builtin_nanf("");
-  P.rkey[pos] = rank_key(s, d.box);
-  P.rbox[pos] = make_float4(d.x1, d.y1, d.x2, d.y2);
-  P.rroi[pos] = d.roi;
+  if (g == 0 && tid == 0) P.bin_begin[P.n_bins] = total;
+  __syncthreads();
+  const int64_t lo = static_cast<int64_t>(g) * P.chunk;
+  const int64_t hi = min(lo + P.chunk, static_cast<int64_t>(count_of(P)));
+  for (int64_t i = lo + tid; i < hi; i += kBinThreads) {
+    const tg_det d = P.dets[i];
+    if (d.frame < 0 || d.frame >= P.n_frames) continue;
+    const float s = (d.box >= 0 && d.box < P.n_scores) ? P.scores[d.box] : __builtin_nanf("");
+    const int pos = atomicAdd(&s_start[bin_of(P, d.frame)], 1);
+    P.crec[pos] = Rec{make_float4(d.x1, d.y1, d.x2, d.y2),
+                      Aux{rank_key(s, d.box), d.roi, static_cast<int32_t>(i)}};
+  }
 }
 
 // Area of a box (x1, y1, x2, y2 in .x .y .z .w), empty and inverted boxes 0.
@@ -225,674 +311,740 @@ __device__ __forceinline__ bool overlap_above(float4 a, float4 b, float area_a, 
   return inter > __fmul_rn(thr, uni);
 }
 
-// Whether box a suppresses box b when a is ranked above b.
-__device__ __forceinline__ bool suppresses(float4 a, float4 b, float thr) {
-  return overlap_above(a, b, box_area(a), box_area(b), thr);
-}
-
-// ---- the greedy of a frame, decided in rounds -----------------------------------------
+// ---- frames decided by one workgroup in LDS --------------------------------------------
 //
-// The greedy walk keeps a detection exactly when no detection ranked above it that
-// suppresses it is kept (by induction over the ranking). So no sorted ranking is needed:
-// given each detection's suppressors ranked above it, rounds decide the frame -- a
-// detection is suppressed once one of them is kept, kept once all of them are suppressed.
-// The best-ranked undecided detection of a round has only decided suppressors, so every
-// round decides at least one: a frame of n detections needs at most n rounds (two to four
-// in practice, where chains of boxes suppressing each other are short). Three launches:
-//  index:   one workgroup per frame lists every box in a grid of up to kGridMax x kGridMax
-//           cells over the frame's boxes (cells two to four times the mean box size) and
-//           gives each detection its lists to search;
-//  search:  kScanLanes lanes per detection, over all detections at once, find its
-//           suppressors ranked above it in those lists (kPredSlots of them are kept; a
-//           detection with more is searched again when it is decided);
-//  resolve: one workgroup per frame (stepping through the frames when there are more than
-//           kGridCap) runs the rounds on the suppressor lists.
-// Search and resolve return at once when no frame was too large for the LDS path.
-// Why the cells find every suppressor: with a threshold t >= 0, a suppresses b only if
+// Why the bands find every suppressor: with a threshold t >= 0, a suppresses b only if
 // inter > t * union >= 0 (a union is never negative), so inter > 0 and both clipped widths
 // are positive: min(x2a, x2b) > max(x1a, x1b) and likewise in y. The point
-// (max(x1a, x1b), max(y1a, y1b)) then lies in both boxes, and since cell_of is
-// non-decreasing its cell lies in the cell ranges of both: a and b share a cell. Every box
-// is listed in the cells it touches; boxes with a NaN coordinate (where min and max ignore
-// the NaN operand), boxes touching more than kCellsMax cells, and every box when t < 0, are
-// "wide": listed once in a wide list that every detection searches, and themselves
-// searching the whole frame. Boxes with x2 < x1 or y2 < y1 have no positive width with
-// anything, so when t >= 0 they neither suppress nor are suppressed: kept from the start
-// and listed nowhere.
-// index and resolve: workgroups of 1024 threads (index) and 512 (resolve), or of
-// kSmallFrame when the frames average at most kSmallFrame detections
-constexpr int kSmallFrame = 256;
-constexpr int kGridMax = 32;         // cells per axis
-constexpr int kCellsMax = 4;         // cells a box may touch before it goes on the wide list
-constexpr int kLists = kCellsMax + 1;
-constexpr uint32_t kWide = 0xFFFFFFFFu;
-constexpr uint32_t kEmpty = 0xFFFFFFFEu;
-constexpr int32_t kUndecided = 0, kKept = 1, kSuppressed = 2;
-constexpr int kPredSlots = 16;  // suppressors kept in place per detection
-constexpr int kOvfPerDet = 16;  // overflow area for longer lists: kOvfPerDet n_max entries
-constexpr int kScanLanes = 8;  // lanes per detection in the search
-constexpr int kBatch = 8;      // list entries whose loads a lane issues together
-constexpr int kSearchDets = kThreads / kScanLanes;  // detections per search workgroup
-// Workgroups of the search and of the rounds: they step through detections and frames, so
-// that inputs whose frames were all decided in LDS pay for a small launch only.
-constexpr int kGridCap = 2048;
+// (max(x1a, x1b), max(y1a, y1b)) then lies in both boxes, and since band_of is
+// non-decreasing its column and row are among those of both. Boxes with a NaN coordinate
+// (where min and max ignore the NaN operand), and every box when t < 0, are named in every
+// band and look in every band. Boxes with x2 < x1 or y2 < y1 have no positive width with
+// anything, so when t >= 0 they neither suppress nor are suppressed.
+constexpr int kLocalBands = 32;  // per axis
 
-__device__ __forceinline__ float wave_minf(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ float wave_maxf(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ float wave_sumf(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
-// Cell of coordinate v (not NaN) on an axis starting at e0 with scale sc (cells per unit,
-// finite, >= 0) and g cells: non-decreasing in v, clamped to [0, g).
-__device__ __forceinline__ int cell_of(float v, float e0, float sc, int g) {
-  const float t = fminf(fmaxf(__fmul_rn(__fsub_rn(v, e0), sc), 0.0f), static_cast<float>(g - 1));
-  return static_cast<int>(t);
-}
-
-struct FrameLds {
-  float ex0, sx, ey0, sy;
-  int gx, gy, all_wide;
-  float red[4][1024 / 64];
-  float sum[2][1024 / 64];
-  float top[2][1024 / 64];  // largest box width and height
-  int off[kGridMax * kGridMax + 2];  // list starts (cells, then the wide list), then the end
-  int cur[kGridMax * kGridMax + 1];  // list sizes while counting, then while filling
-  int cnt[kGridMax * kGridMax + 1];  // list sizes
-};
-constexpr int kIdx = 4;  // detections per thread and step of the index, loads issued together
-
-// ---- frames that fit one workgroup ------------------------------------------------------
-//
-// A frame of at most kSmallMax detections is decided by its index workgroup alone, in LDS:
-// each thread holds one detection and tests every detection of the frame (four 16-byte
-// boxes per step) for the suppressors ranked above it, a row of bits per detection; the
-// rounds run on those rows (masks of kept and undecided detections rebuilt from ballots
-// each round); the keep flags are written at once. The frame's detections are marked
-// kEmpty, so the search passes them by, and the rounds skip the frame; when no frame is
-// larger, both return at once.
-template <int kN>
-struct SmallFrameLds {
-  float4 box[kN];
-  uint64_t key[kN];
-  int32_t roi[kN];
-  float area[kN];
-  uint32_t sup[kN][kN / 32 + 1];  // odd row stride: rows in distinct banks
-  uint32_t kept[kN / 32], open[kN / 32];
+// Up to kLocal boxes by band: per axis and band, the boxes that start at or before the band
+// and those that end at or after it; the boxes meeting bands a .. b start at or before b
+// and end at or after a.
+struct BandTable {
+  uint32_t starts[2][kLocalBands][kLocalWords + 1], ends[2][kLocalBands][kLocalWords + 1];
+  float ext[4][kLocal / 64];
 };
 
-// Frames of at most kSmallMax detections take the LDS path; the pair tests grow with the
-// square of the frame, so larger frames spread their search over the whole grid instead
-// (frames of 300-530 detections in one workgroup each: cam20_4k 55 -> 124 us).
-constexpr int kSmallMax = 256;
-constexpr int kSmallRows = 256;  // row bits (at least kSmallMax, a multiple of 64)
-static_assert(kSmallMax <= kSmallRows && kSmallRows <= kSmallFrame, "one detection per thread");
+// The bands a box is named in and looks in: columns x0 .. x1, rows y0 .. y1.
+struct BandSpan {
+  int x0, x1, y0, y1;
+  bool named;  // false: a box that meets nothing
+};
 
-template <int kN>
-__device__ void small_frame(const MergeParams &P, int lo, int n, SmallFrameLds<kN> &S) {
-  constexpr int kWords = kN / 32;
+__device__ __forceinline__ bool nan_corner(float4 b) {
+  return b.x != b.x || b.y != b.y || b.z != b.z || b.w != b.w;
+}
+
+// `each`: boxes that do not meet count as well (a negative threshold).
+__device__ __forceinline__ BandSpan span_of(float4 box, bool each, BandAxis ax, BandAxis ay) {
+  BandSpan v = {0, kLocalBands - 1, 0, kLocalBands - 1, true};
+  if (!each && !nan_corner(box)) {
+    v.named = box.x <= box.z && box.y <= box.w;
+    v.x0 = band_of(box.x, ax, kLocalBands);
+    v.x1 = band_of(box.z, ax, kLocalBands);
+    v.y0 = band_of(box.y, ay, kLocalBands);
+    v.y1 = band_of(box.w, ay, kLocalBands);
+  }
+  return v;
+}
+
+// Builds the table of n <= kLocal boxes, box i held by thread i of a workgroup of kLocal
+// (i >= n: any), and the axes. Ends with a barrier.
+__device__ __forceinline__ void build_table(BandTable &T, float4 box, int n, bool each,
+                                            BandAxis &ax, BandAxis &ay) {
   const int i = threadIdx.x, lane = i & 63, wave = i >> 6;
-  const bool mine = i < n;  // n <= kN <= the workgroup's threads
-  float4 box = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  uint64_t key = ~uint64_t(0);
-  int roi = 0;
-  if (mine) {
-    box = P.rbox[lo + i];
-    key = P.rkey[lo + i];
-    roi = P.rroi[lo + i];
-  }
-  if (i < kN) {
-    S.box[i] = box;
-    S.key[i] = key;
-    S.roi[i] = roi;
-    S.area[i] = box_area(box);
-#pragma unroll
-    for (int w = 0; w < kWords; ++w) S.sup[i][w] = 0;
+  const float inf = __builtin_inff();
+  const bool plain = i < n && !nan_corner(box) && box.x <= box.z && box.y <= box.w;
+  const float e0 = wave_min(plain && __builtin_isfinite(box.x) ? box.x : inf);
+  const float e1 = wave_min(plain && __builtin_isfinite(box.y) ? box.y : inf);
+  const float e2 = wave_min(plain && __builtin_isfinite(box.z) ? -box.z : inf);
+  const float e3 = wave_min(plain && __builtin_isfinite(box.w) ? -box.w : inf);
+  if (lane == 0) {
+    T.ext[0][wave] = e0;
+    T.ext[1][wave] = e1;
+    T.ext[2][wave] = e2;
+    T.ext[3][wave] = e3;
   }
   __syncthreads();
-  // Each pair once: thread i tests the detections 1 .. n/2 places after it, cyclically (at
-  // n/2 exactly, for even n, only the first half of the threads), and the pair's bit goes
-  // into the row of whichever of the two is ranked below.
-  if (mine) {
-    const float area = S.area[i];
-    const int last = (n % 2 == 0 && i < n / 2) ? n / 2 : (n - 1) / 2;
-    for (int d0 = 1; d0 <= last; d0 += 4) {
-      float4 qb[4];
-      uint64_t qk[4];
-      int qr[4], qj[4];
-      float qa[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = i + min(d0 + u, last);  // < 2n
-        qj[u] = j >= n ? j - n : j;
-        qb[u] = S.box[qj[u]];
-        qk[u] = S.key[qj[u]];
-        qr[u] = S.roi[qj[u]];
-        qa[u] = S.area[qj[u]];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (d0 + u <= last && !(P.cross_only && qr[u] == roi) &&
-            overlap_above(qb[u], box, qa[u], area, P.thr)) {
-          const int j = qj[u];
-          if (qk[u] < key)
-            atomicOr(&S.sup[i][j >> 5], 1u << (j & 31));
-          else if (key < qk[u])
-            atomicOr(&S.sup[j][i >> 5], 1u << (i & 31));
-        }
-      }
-    }
+  // lane l of each row of 16 lanes reads wave l's extent: the waves' minima by DPP
+  const int w16 = lane & (kLocal / 64 - 1);
+  ax = band_axis(wave_min(T.ext[0][w16]), -wave_min(T.ext[2][w16]), kLocalBands);
+  ay = band_axis(wave_min(T.ext[1][w16]), -wave_min(T.ext[3][w16]), kLocalBands);
+  const int word = 2 * wave + (lane >> 5);
+  if (64 * wave < n) {  // later words are not looked in
+    const BandSpan v = span_of(box, each, ax, ay);
+    const bool named = v.named && i < n;
+    T.starts[0][lane & 31][word] = transpose32(named ? 0xFFFFFFFFu << v.x0 : 0u, lane);
+    T.starts[1][lane & 31][word] = transpose32(named ? 0xFFFFFFFFu << v.y0 : 0u, lane);
+    T.ends[0][lane & 31][word] = transpose32(named ? 0xFFFFFFFFu >> (31 - v.x1) : 0u, lane);
+    T.ends[1][lane & 31][word] = transpose32(named ? 0xFFFFFFFFu >> (31 - v.y1) : 0u, lane);
   }
   __syncthreads();
-  int st = mine ? kUndecided : kSuppressed;
-  bool overrun = false;
-  for (int round = 0;; ++round) {
-    const uint64_t kb = __ballot(st == kKept), ob = __ballot(st == kUndecided);
-    if (lane == 0 && wave < kN / 64) {
-      S.kept[2 * wave] = static_cast<uint32_t>(kb);
-      S.kept[2 * wave + 1] = static_cast<uint32_t>(kb >> 32);
-      S.open[2 * wave] = static_cast<uint32_t>(ob);
-      S.open[2 * wave + 1] = static_cast<uint32_t>(ob >> 32);
-    }
-    if (!__syncthreads_or(st == kUndecided)) break;
-    if (round > n) {  // each round decides the best-ranked undecided detection
-      overrun = true;
-      break;
-    }
-    if (st == kUndecided) {
-      bool any_kept = false, any_open = false;
-#pragma unroll
-      for (int w = 0; w < kWords; ++w) {
-        const uint32_t r = S.sup[i][w];
-        any_kept = any_kept || (r & S.kept[w]) != 0;
-        any_open = any_open || (r & S.open[w]) != 0;
-      }
-      st = any_kept ? kSuppressed : (any_open ? kUndecided : kKept);
-    }
-    __syncthreads();  // every row has been tested before the masks are rewritten
-  }
-  if (mine) {
-    P.keep[P.grouped[lo + i]] = st == kKept ? 1 : 0;
-    P.rcell[lo + i] = kEmpty;
-  }
-  if (overrun && i == 0) *P.status = 1;
 }
 
-template <int kFrameThreads>
-__global__ __launch_bounds__(kFrameThreads) void index_kernel(const MergeParams P) {
-  __shared__ union {
-    FrameLds f;
-    SmallFrameLds<kSmallRows> s;
-  } U;
-  FrameLds &S = U.f;
+// Boxes 32 w .. 32 w + 31 that share a column and a row with span v.
+__device__ __forceinline__ uint32_t table_word(const BandTable &T, const BandSpan &v, int w) {
+  return T.starts[0][v.x1][w] & T.ends[0][v.x0][w] & T.starts[1][v.y1][w] & T.ends[1][v.y0][w];
+}
+
+struct LocalLds {
+  float4 box[kLocal];
+  Aux aux[kLocal];
+  uint16_t first[kLocal], end[kLocal];  // the positions of the detection's frame
+  BandTable table;
+  uint32_t pair[kPairs];  // position << 16 | a later position
+  uint32_t hit[kHits];    // suppressed << 16 | suppressor
+  uint8_t state[kLocal];
+  uint8_t sees_kept[kLocal], sees_open[kLocal];  // this round, among its suppressors
+  float ext[4][kLocal / 64];
+  int n_pairs, n_hits;
+};
+
+// One pair of positions tested: listed as a hit when one suppresses the other.
+__device__ __forceinline__ void test_pair(const MergeParams &P, LocalLds &S, int i, int j) {
+  const float4 a = S.box[i], b = S.box[j];
+  const Aux x = S.aux[i], y = S.aux[j];
+  if (overlap_above(a, b, box_area(a), box_area(b), P.thr) && x.key != y.key &&
+      !(P.cross_only && x.roi == y.roi)) {
+    const int h = lane_place(&S.n_hits);
+    if (h < kHits) S.hit[h] = x.key < y.key ? static_cast<uint32_t>(j) << 16 | static_cast<uint32_t>(i)
+                                      : static_cast<uint32_t>(i) << 16 | static_cast<uint32_t>(j);
+  }
+}
+
+// Decides n <= kLocal detections, each frame's at consecutive positions of S, by a workgroup
+// of kLocal threads, and writes their keep flags; false, with nothing written, when the
+// suppressing pairs do not fit. Called after a barrier; ends without one.
+// Testing only the pairs that bands bring together is what makes whole frames affordable
+// here (a frame of 400 boxes of cam20_4k has 80,000 pairs, of which about 2,000 share bands),
+// and listing them spreads the tests evenly: lanes that each step through their own
+// candidates wait for the one in the most crowded place (9 us of 24, frames of 400; the whole
+// pass takes 12 now). Code that runs once costs its instruction fetches, so loops stay loops.
+__device__ bool decide(const MergeParams &P, LocalLds &S, int n) {
+  const int i = threadIdx.x;
+  const bool mine = i < n, each = !(P.thr >= 0.0f);
+  if (i == 0) S.n_pairs = S.n_hits = 0;
+  S.state[i] = kKept;
+  S.sees_kept[i] = S.sees_open[i] = 0;
+  BandAxis ax, ay;
+  build_table(S.table, S.box[i], n, each, ax, ay);
+  // Each detection's pairs with later ones of its frame, in the words from its own on: `width`
+  // threads take a detection each, `parts` of them share its words.
+  int width = 64;
+  while (width < n) width *= 2;
+  const int o = i & (width - 1), part = i / width, parts = kLocal / width;
+  BandSpan v = {0, 0, 0, 0, false};
+  int w0 = 0, w1 = -1;
+  if (o < n) v = span_of(S.box[o], each, ax, ay);
+  if (v.named) {
+    w0 = o >> 5;
+    w1 = (S.end[o] - 1) >> 5;
+  }
+  const uint32_t tail = 0xFFFFFFFFu >> (31 - ((w1 >= 0 ? S.end[o] - 1 : 0) & 31));
+  auto word_of = [&](int w) {
+    uint32_t m = table_word(S.table, v, w);
+    if (w == w0) m &= 0xFFFFFFFEu << (o & 31);
+    return w == w1 ? m & tail : m;
+  };
+  int count = 0;
+#pragma unroll 2
+  for (int w = w0 + part; w <= w1; w += parts) count += __popc(word_of(w));
+  int at = wave_places(&S.n_pairs, count);
+  for (int w = w0 + part; w <= w1; w += parts)
+    for (uint32_t m = word_of(w); m != 0 && at < kPairs; m &= m - 1)
+      S.pair[at++] = static_cast<uint32_t>(o) << 16 | static_cast<uint32_t>(32 * w + __builtin_ctz(m));
+  __syncthreads();
+  const int n_pairs = S.n_pairs;
+  if (n_pairs <= kPairs) {
+    for (int p = i; p < n_pairs; p += kLocal) test_pair(P, S, S.pair[p] >> 16, S.pair[p] & 0xFFFFu);
+  } else {  // crowded: each lane its own
+    for (int w = w0 + part; w <= w1; w += parts)
+      for (uint32_t m = word_of(w); m != 0; m &= m - 1) test_pair(P, S, o, 32 * w + __builtin_ctz(m));
+  }
+  __syncthreads();
+  const int n_hits = S.n_hits;
+  if (n_hits > kHits) return false;  // uniform
+  for (int h = i; h < n_hits; h += kLocal) S.state[S.hit[h] >> 16] = kUndecided;
+  bool overrun = false;
+  if (n_hits > 0) {
+    __syncthreads();
+    for (int round = 0;; ++round) {
+      for (int h = i; h < n_hits; h += kLocal) {
+        const uint32_t v = S.hit[h];
+        const int s = S.state[v & 0xFFFFu];
+        if (s == kKept) S.sees_kept[v >> 16] = 1;
+        if (s == kUndecided) S.sees_open[v >> 16] = 1;
+      }
+      __syncthreads();
+      bool open = false;
+      if (mine && S.state[i] == kUndecided) {
+        if (S.sees_kept[i])
+          S.state[i] = kSuppressed;
+        else if (!S.sees_open[i])
+          S.state[i] = kKept;
+        else
+          open = true;
+        S.sees_open[i] = 0;
+      }
+      if (!__syncthreads_or(open)) break;
+      if (round > n) {  // each round decides a frame's best-ranked undecided detection
+        overrun = true;
+        break;
+      }
+    }
+  }
+  if (mine) P.keep[S.aux[i].idx] = S.state[i] == kKept ? 1 : 0;
+  if (overrun && i == 0) *P.status = 1;
+  return true;
+}
+
+// Lists a frame for the tile and resolve passes. Called by the whole workgroup, after its
+// boxes are in the workspace.
+__device__ void add_large(const MergeParams &P, LocalLds &S, int lo, int n) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lo = P.frame_begin[blockIdx.x];
-  const int n = P.frame_begin[blockIdx.x + 1] - lo;
+  float e[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) e[k] = __builtin_inff();
+#pragma unroll 4
+  for (int p = tid; p < n; p += kLocal) {
+    const float4 b = P.rec[lo + p].box;
+    if (__builtin_isfinite(b.x)) e[0] = fminf(e[0], b.x);
+    if (__builtin_isfinite(b.y)) e[1] = fminf(e[1], b.y);
+    if (__builtin_isfinite(b.x)) e[2] = fminf(e[2], -b.x);
+    if (__builtin_isfinite(b.y)) e[3] = fminf(e[3], -b.y);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    e[k] = wave_min(e[k]);
+    if (lane == 0) S.ext[k][wave] = e[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) e[k] = wave_min(S.ext[k][lane & (kLocal / 64 - 1)]);
+  if (tid == 0) {
+    // every tile reads the whole frame, so there are at most kTilesMax of them
+    const float tiles = fminf(static_cast<float>(n) * (1.0f / kTileDets), static_cast<float>(kTilesMax));
+    const int g = max(1, static_cast<int>(ceilf(sqrtf(tiles))));
+    const unsigned long long old =
+        atomicAdd(P.large_used, (1ull << 32) | static_cast<unsigned long long>(g) * g);
+    // any finite origin and scale serve: tiles only share the frame's detections out
+    const float sx = g * __builtin_amdgcn_rcpf(-e[2] - e[0]);
+    const float sy = g * __builtin_amdgcn_rcpf(-e[3] - e[1]);
+    LargeFrame *L = P.large + (old >> 32);
+    L->lo = lo;
+    L->n = n;
+    L->g = g;
+    L->start = static_cast<uint32_t>(old);
+    L->x0 = __builtin_isfinite(e[0]) ? e[0] : 0.0f;
+    L->sx = __builtin_isfinite(sx) && sx > 0.0f ? sx : 0.0f;
+    L->y0 = __builtin_isfinite(e[1]) ? e[1] : 0.0f;
+    L->sy = __builtin_isfinite(sy) && sy > 0.0f ? sy : 0.0f;
+    L->open = 0;
+  }
+  __syncthreads();
+}
+
+// The n detections of S (frame order, positions from lo on) written to the workspace and
+// their frames listed for the tile and resolve passes.
+__device__ void list_frames(const MergeParams &P, LocalLds &S, int lo, int n) {
+  const int tid = threadIdx.x;
+  if (tid < n) {
+    P.rec[lo + tid] = Rec{S.box[tid], S.aux[tid]};
+  }
+  __threadfence_block();
+  __syncthreads();
+  for (int s = 0; s < n;) {  // uniform
+    const int e = S.end[s];
+    if (e - s > 1)
+      add_large(P, S, lo + s, e - s);
+    else if (tid == 0)
+      P.keep[S.aux[s].idx] = 1;  // alone in its frame
+    s = e;
+  }
+}
+
+// In-place exclusive scan of hist[0 .. nf) with hist[nf] = the sum, by the workgroup.
+__device__ void scan_hist(int *hist, int nf, int *s_wave) {
+  const int per = (nf + kLocal - 1) / kLocal, a = min(static_cast<int>(threadIdx.x) * per, nf);
+  const int b = min(a + per, nf);
+  int sum = 0, total;
+  for (int k = a; k < b; ++k) sum += hist[k];
+  int at = block_exclusive<kLocal>(sum, s_wave, &total);
+  for (int k = a; k < b; ++k) {
+    const int v = hist[k];
+    hist[k] = at;
+    at += v;
+  }
+  if (threadIdx.x == 0) hist[nf] = total;
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kLocal) void local_kernel(const MergeParams P) {
+  __shared__ LocalLds S;
+  __shared__ int hist[kFrameHist + 1];
+  __shared__ int s_wave[kLocal / 64];
+  static_assert(kLocal == 1024, "sixteen waves: one per lane of a DPP row");
+  const int tid = threadIdx.x;
+  const int lo = P.bin_begin[blockIdx.x], n = P.bin_begin[blockIdx.x + 1] - lo;
   if (n <= 0) return;
-  if (n <= kSmallMax) {
-    small_frame<kSmallRows>(P, lo, n, U.s);
+  if (P.per_bin == 1) {
+    if (n > kLocal) {
+      add_large(P, S, lo, n);
+      return;
+    }
+    if (tid < n) {
+      const Rec r = P.rec[lo + tid];
+      S.box[tid] = r.box;
+      S.aux[tid] = r.aux;
+      S.first[tid] = 0;
+      S.end[tid] = static_cast<uint16_t>(n);
+    }
+    __syncthreads();
+    if (!decide(P, S, n)) add_large(P, S, lo, n);
     return;
   }
-  if (tid == 0) *P.big = 1;  // the search and the rounds have work
-  const int64_t ent0 = static_cast<int64_t>(kCellsMax) * lo;  // the frame's list entries
-
-  // the frame's extent and mean box size
-  float xlo = __builtin_inff(), xhi = -__builtin_inff(), ylo = xlo, yhi = xhi;
-  float sw = 0.0f, sh = 0.0f, mxw = 0.0f, mxh = 0.0f;
-  for (int p0 = tid; p0 < n; p0 += kIdx * kFrameThreads) {
-    float4 bb[kIdx];
-#pragma unroll
-    for (int u = 0; u < kIdx; ++u) {
-      const int p = p0 + u * kFrameThreads;
-      bb[u] = p < n ? P.rbox[lo + p] : make_float4(0.0f, 0.0f, -1.0f, -1.0f);
+  const int f0 = static_cast<int>(blockIdx.x) * P.per_bin;  // < n_frames
+  const int nf_all = min(P.per_bin, P.n_frames - f0);
+  if (n <= kLocal && nf_all <= kFrameHist) {  // the whole bin ordered and decided in LDS
+    for (int k = tid; k < nf_all; k += kLocal) hist[k] = 0;
+    __syncthreads();
+    int f = 0, rank = 0, roi = 0, idx = 0;
+    float4 box = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    uint64_t key = 0;
+    if (tid < n) {
+      const Rec *r = P.crec + lo + tid;
+      box = r->box;
+      key = r->aux.key;
+      roi = r->aux.roi;
+      idx = r->aux.idx;
+      f = P.dets[idx].frame - f0;
+      rank = atomicAdd(&hist[f], 1);
     }
-#pragma unroll
-    for (int u = 0; u < kIdx; ++u) {
-      const float4 b = bb[u];
-      if (__builtin_isfinite(b.x) && __builtin_isfinite(b.z) && b.z >= b.x) {
-        xlo = fminf(xlo, b.x);
-        xhi = fmaxf(xhi, b.z);
-        sw += b.z - b.x;
-        mxw = fmaxf(mxw, b.z - b.x);
+    __syncthreads();
+    scan_hist(hist, nf_all, s_wave);
+    if (tid < n) {
+      const int at = hist[f] + rank;
+      S.box[at] = box;
+      S.aux[at].key = key;
+      S.aux[at].roi = roi;
+      S.aux[at].idx = idx;
+      S.first[at] = static_cast<uint16_t>(hist[f]);
+      S.end[at] = static_cast<uint16_t>(hist[f + 1]);
+    }
+    __syncthreads();
+    if (!decide(P, S, n)) list_frames(P, S, lo, n);
+    return;
+  }
+  // A bin that does not fit: ordered by frame in the workspace, kFrameHist frames at a time,
+  // then decided in runs of whole frames of at most kLocal detections.
+  int base = lo;
+  for (int fw = 0; fw < nf_all; fw += kFrameHist) {
+    const int nf = min(kFrameHist, nf_all - fw);
+    for (int k = tid; k < nf; k += kLocal) hist[k] = 0;
+    __syncthreads();
+    for (int i = tid; i < n; i += kLocal) {
+      const int f = P.dets[P.crec[lo + i].aux.idx].frame - f0 - fw;
+      if (f >= 0 && f < nf) atomicAdd(&hist[f], 1);
+    }
+    __syncthreads();
+    scan_hist(hist, nf, s_wave);
+    const int total = hist[nf];
+    for (int i = tid; i < n; i += kLocal) {
+      const Rec r = P.crec[lo + i];
+      const int f = P.dets[r.aux.idx].frame - f0 - fw;
+      if (f < 0 || f >= nf) continue;
+      const int at = base + atomicAdd(&hist[f], 1);  // hist[f] ends as the end of frame f
+      P.rec[at] = r;
+      P.frame[at] = f;
+    }
+    __threadfence_block();
+    __syncthreads();
+    int f = 0, s = 0;  // the next frame and its first position (from base)
+    while (f < nf && s < total) {
+      int e = f, step = 1;  // the most frames from f on with at most kLocal detections
+      while (step <= nf) step *= 2;
+      for (; step > 0; step >>= 1)
+        if (e + step <= nf && hist[e + step - 1] - s <= kLocal) e += step;
+      if (e == f) {
+        add_large(P, S, base + s, hist[f] - s);
+        s = hist[f++];
+        continue;
       }
-      if (__builtin_isfinite(b.y) && __builtin_isfinite(b.w) && b.w >= b.y) {
-        ylo = fminf(ylo, b.y);
-        yhi = fmaxf(yhi, b.w);
-        sh += b.w - b.y;
-        mxh = fmaxf(mxh, b.w - b.y);
-      }
-    }
-  }
-  xlo = wave_minf(xlo);
-  xhi = wave_maxf(xhi);
-  ylo = wave_minf(ylo);
-  yhi = wave_maxf(yhi);
-  sw = wave_sumf(sw);
-  sh = wave_sumf(sh);
-  mxw = wave_maxf(mxw);
-  mxh = wave_maxf(mxh);
-  if (lane == 0) {
-    S.red[0][wave] = xlo;
-    S.red[1][wave] = xhi;
-    S.red[2][wave] = ylo;
-    S.red[3][wave] = yhi;
-    S.sum[0][wave] = sw;
-    S.sum[1][wave] = sh;
-    S.top[0][wave] = mxw;
-    S.top[1][wave] = mxh;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    for (int w = 1; w < kFrameThreads / 64; ++w) {
-      S.red[0][0] = fminf(S.red[0][0], S.red[0][w]);
-      S.red[1][0] = fmaxf(S.red[1][0], S.red[1][w]);
-      S.red[2][0] = fminf(S.red[2][0], S.red[2][w]);
-      S.red[3][0] = fmaxf(S.red[3][0], S.red[3][w]);
-      S.sum[0][0] += S.sum[0][w];
-      S.sum[1][0] += S.sum[1][w];
-      S.top[0][0] = fmaxf(S.top[0][0], S.top[0][w]);
-      S.top[1][0] = fmaxf(S.top[1][0], S.top[1][w]);
-    }
-    // Cells twice the mean box size, or as large as the largest box when that is two to
-    // four times the mean, so that no box touches more than 2 x 2 cells (boxes touching
-    // more go on the wide list and search their whole frame: on cam20_4k, boxes of
-    // 4-256 pixels with a mean of 110, 22 of 8,145 detections did, each searching 400-530
-    // entries against a mean of 27, and set the search's time); larger outliers stay
-    // wide. At most kGridMax cells per axis. Any finite scale keeps the index exact (only
-    // its speed depends on it), so approximate reciprocals do; a degenerate extent just
-    // puts everything in one cell.
-    const float span_x = S.red[1][0] - S.red[0][0], span_y = S.red[3][0] - S.red[2][0];
-    const float inv_n = __builtin_amdgcn_rcpf(static_cast<float>(n));
-    const float mw = S.sum[0][0] * inv_n, mh = S.sum[1][0] * inv_n;
-    const float tw = S.top[0][0], th = S.top[1][0];
-    const float cw = (tw > 2.0f * mw && tw <= 4.0f * mw) ? tw : 2.0f * mw;
-    const float ch = (th > 2.0f * mh && th <= 4.0f * mh) ? th : 2.0f * mh;
-    const float fx = span_x * __builtin_amdgcn_rcpf(fmaxf(cw, 1e-30f));
-    const float fy = span_y * __builtin_amdgcn_rcpf(fmaxf(ch, 1e-30f));
-    S.gx = fx >= 2.0f ? static_cast<int>(fminf(fx, static_cast<float>(kGridMax))) : 1;
-    S.gy = fy >= 2.0f ? static_cast<int>(fminf(fy, static_cast<float>(kGridMax))) : 1;
-    const float scx = S.gx * __builtin_amdgcn_rcpf(span_x);
-    const float scy = S.gy * __builtin_amdgcn_rcpf(span_y);
-    S.ex0 = __builtin_isfinite(S.red[0][0]) ? S.red[0][0] : 0.0f;
-    S.ey0 = __builtin_isfinite(S.red[2][0]) ? S.red[2][0] : 0.0f;
-    S.sx = (__builtin_isfinite(scx) && scx > 0.0f) ? scx : 0.0f;
-    S.sy = (__builtin_isfinite(scy) && scy > 0.0f) ? scy : 0.0f;
-    S.all_wide = !(P.thr >= 0.0f);
-  }
-  for (int c = tid; c < kGridMax * kGridMax + 1; c += kFrameThreads) S.cur[c] = 0;
-  __syncthreads();
-
-  // each box's cell range; the lists' sizes
-  const int gx = S.gx, gy = S.gy, n_cells = gx * gy;
-  for (int p0 = tid; p0 < n; p0 += kIdx * kFrameThreads) {
-    float4 bb[kIdx];
-#pragma unroll
-    for (int u = 0; u < kIdx; ++u) {
-      const int p = p0 + u * kFrameThreads;
-      bb[u] = p < n ? P.rbox[lo + p] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
-#pragma unroll
-    for (int u = 0; u < kIdx; ++u) {
-      const int p = p0 + u * kFrameThreads;
-      if (p >= n) continue;
-      const float4 b = bb[u];
-      uint32_t cr;
-      if (S.all_wide || b.x != b.x || b.y != b.y || b.z != b.z || b.w != b.w) {
-        cr = kWide;
-      } else if (b.z < b.x || b.w < b.y) {
-        cr = kEmpty;
-      } else {
-        const int cx0 = cell_of(b.x, S.ex0, S.sx, gx), cx1 = cell_of(b.z, S.ex0, S.sx, gx);
-        const int cy0 = cell_of(b.y, S.ey0, S.sy, gy), cy1 = cell_of(b.w, S.ey0, S.sy, gy);
-        cr = (cx1 - cx0 + 1) * (cy1 - cy0 + 1) > kCellsMax
-                ? kWide
-                : static_cast<uint32_t>(cx0 | cx1 << 8 | cy0 << 16 | cy1 << 24);
-      }
-      P.rcell[lo + p] = cr;
-      P.rstate[lo + p] = cr == kEmpty ? kKept : kUndecided;
-        if (cr == kWide) {
-        atomicAdd(&S.cur[n_cells], 1);
-      } else if (cr != kEmpty) {
-        for (int cy = (cr >> 16) & 0xFF; cy <= static_cast<int>(cr >> 24); ++cy)
-          for (int cx = cr & 0xFF; cx <= static_cast<int>((cr >> 8) & 0xFF); ++cx)
-            atomicAdd(&S.cur[cy * gx + cx], 1);
-      }
-    }
-  }
-  __syncthreads();
-  if (wave == 0) {  // starts of the n_cells + 1 lists: lane l sums a run of them
-    constexpr int kRun = (kGridMax * kGridMax + 1 + 63) / 64;
-    const int c0 = lane * kRun, c1 = min(c0 + kRun, n_cells + 1);
-    int sum = 0;
-    for (int c = c0; c < c1; ++c) sum += S.cur[c];
-    int incl = sum;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int v = __shfl_up(incl, o);
-      if (lane >= o) incl += v;
-    }
-    int at = incl - sum;
-    for (int c = c0; c < c1; ++c) {
-      const int k = S.cur[c];
-      S.off[c] = at;
-      S.cnt[c] = k;
-      S.cur[c] = 0;  // from here on: entries filled so far
-      at += k;
-    }
-    if (lane == 63) S.off[n_cells + 1] = incl;
-  }
-  __syncthreads();
-  // the entries (each listed box, its patch, ranking key and position) and each
-  // detection's lists to search: absolute entry starts and sizes (a wide box: the frame's
-  // first position and its size, searched as positions)
-  for (int p0 = tid; p0 < n; p0 += kIdx * kFrameThreads) {
-    uint32_t cc[kIdx];
-    float4 bb[kIdx];
-    uint64_t kk[kIdx];
-    int rr[kIdx];
-#pragma unroll
-    for (int u = 0; u < kIdx; ++u) {
-      const int p = p0 + u * kFrameThreads;
-      const bool in = p < n;
-      cc[u] = in ? P.rcell[lo + p] : kEmpty;
-      bb[u] = in ? P.rbox[lo + p] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      kk[u] = in ? P.rkey[lo + p] : 0;
-      rr[u] = in ? P.rroi[lo + p] : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < kIdx; ++u) {
-      const int p = p0 + u * kFrameThreads;
-      if (p >= n) continue;
-      const uint32_t cr = cc[u];
-      const int4 aux = make_int4(rr[u], static_cast<int>(static_cast<uint32_t>(kk[u])),
-                                 static_cast<int>(static_cast<uint32_t>(kk[u] >> 32)), lo + p);
-      int32_t *L = P.rlist + 2 * kLists * static_cast<int64_t>(lo + p);
-      int k = 0;
-      if (cr == kWide) {
-        const int64_t at = ent0 + S.off[n_cells] + atomicAdd(&S.cur[n_cells], 1);
-        P.ebox[at] = bb[u];
-        P.eaux[at] = aux;
-        L[0] = lo;
-        L[kLists] = n;
-        k = 1;
-      } else if (cr != kEmpty) {
-        for (int cy = (cr >> 16) & 0xFF; cy <= static_cast<int>(cr >> 24); ++cy)
-          for (int cx = cr & 0xFF; cx <= static_cast<int>((cr >> 8) & 0xFF); ++cx, ++k) {
-            const int c = cy * gx + cx;
-            const int64_t at = ent0 + S.off[c] + atomicAdd(&S.cur[c], 1);
-            P.ebox[at] = bb[u];
-            P.eaux[at] = aux;
-            L[k] = static_cast<int32_t>(ent0) + S.off[c];
-            L[kLists + k] = S.cnt[c];
-          }
-        L[k] = static_cast<int32_t>(ent0) + S.off[n_cells];
-        L[kLists + k] = S.cnt[n_cells];
-        ++k;
-      }
-      for (; k < kLists; ++k) {
-        L[k] = 0;
-        L[kLists + k] = 0;
-      }
-    }
-  }
-}
-
-// A detection's lists to search, in registers: starts st[k] and sizes ln[k].
-struct Lists {
-  int st[kLists], ln[kLists], total;
-};
-__device__ __forceinline__ Lists lists_of(const MergeParams &P, int a) {
-  const int32_t *L = P.rlist + 2 * kLists * static_cast<int64_t>(a);
-  Lists l;
-  l.total = 0;
-#pragma unroll
-  for (int k = 0; k < kLists; ++k) {
-    l.st[k] = L[k];
-    l.ln[k] = L[kLists + k];
-    l.total += l.ln[k];
-  }
-  return l;
-}
-
-// One step of a search: candidates t0, t0 + stride, ... (kBatch of them, below l.total) of
-// a detection's lists, loaded together; returns a mask of those that are suppressors of
-// it (box bp, key kp, patch rp) ranked above it (bit u: candidate t0 + u * stride), and
-// their positions in q.
-__device__ __forceinline__ uint32_t search_step(const MergeParams &P, const Lists &l, bool wide,
-                                                int t0, int stride, float4 bp, uint64_t kp,
-                                                int rp, int q[kBatch]) {
-  float4 bq[kBatch];
-  uint64_t kq[kBatch];
-  int rq[kBatch];
-  uint32_t hits = 0;
-#pragma unroll
-  for (int u = 0; u < kBatch; ++u) {
-    int t = t0 + u * stride;
-    q[u] = -1;
-    if (t >= l.total) continue;
-    if (wide) {
-      q[u] = l.st[0] + t;
-      bq[u] = P.rbox[q[u]];
-      kq[u] = P.rkey[q[u]];
-      rq[u] = P.rroi[q[u]];
-    } else {
-      int at = l.st[0], k = 0;
-#pragma unroll
-      for (int kk = 0; kk < kCellsMax; ++kk)  // which list: step over the earlier ones
-        if (k == kk && t >= l.ln[kk]) {
-          t -= l.ln[kk];
-          k = kk + 1;
-          at = l.st[kk + 1];
+      const int m = hist[e - 1] - s;
+      if (m > 0) {
+        if (tid < m) {
+          const int at = base + s + tid, fr = P.frame[at];
+          const Rec r = P.rec[at];
+          S.box[tid] = r.box;
+          S.aux[tid] = r.aux;
+          S.first[tid] = static_cast<uint16_t>((fr > 0 ? hist[fr - 1] : 0) - s);
+          S.end[tid] = static_cast<uint16_t>(hist[fr] - s);
         }
-      const int4 e = P.eaux[at + t];
-      bq[u] = P.ebox[at + t];
-      kq[u] = static_cast<uint64_t>(static_cast<uint32_t>(e.z)) << 32 | static_cast<uint32_t>(e.y);
-      rq[u] = e.x;
-      q[u] = e.w;
+        __syncthreads();
+        if (!decide(P, S, m)) list_frames(P, S, base + s, m);
+        __syncthreads();
+      }
+      s = hist[e - 1];
+      f = e;
     }
+    base += total;
+    __syncthreads();
   }
-#pragma unroll
-  for (int u = 0; u < kBatch; ++u)
-    if (q[u] >= 0 && kq[u] < kp && !(P.cross_only && rq[u] == rp) && suppresses(bq[u], bp, P.thr))
-      hits |= 1u << u;
-  return hits;
 }
 
-// The suppressors ranked above each detection: kScanLanes consecutive lanes per detection,
-// detections in frame-group order over the whole grid. The first kPredSlots go in place;
-// a workgroup whose detections have more reserves room for their whole lists in the
-// overflow area (one atomic for all of them) and searches those again to fill it; a
-// list that does not fit is left to be searched in the rounds.
-__device__ __forceinline__ void search_block(const MergeParams &P, int blk, int n_grouped) {
-  __shared__ int s_np[kSearchDets], s_fill[kSearchDets], s_at[kSearchDets];
-  const int tid = threadIdx.x, j = tid / kScanLanes, sub = tid % kScanLanes;
-  const int a = blk * kSearchDets + j;
-  const bool valid = a < n_grouped && P.rcell[a] != kEmpty;
-  if (sub == 0) {
-    s_np[j] = 0;
-    s_fill[j] = 0;
+// ---- larger frames ----------------------------------------------------------------------
+
+constexpr int kTileRegs = 6;                          // boxes a thread loads at once
+constexpr int kTileSpan = kTileRegs * kTileThreads;   // positions read at once: 6,144
+constexpr int kTileCand = kTileThreads;               // candidates tested at once
+
+struct TileLds {
+  int32_t own[kTileSpan];      // positions of the tile's detections among kTileSpan
+  float4 own_box[kTileThreads];// the detections being searched
+  Aux own_aux[kTileThreads];
+  int32_t count[kTileThreads]; // suppressors found of each
+  int32_t at[kTileThreads];    // where their longer lists start in ovf, or -1
+  float4 box[kTileCand];       // boxes that can meet them
+  Aux aux[kTileCand];
+  int32_t pos[kTileCand];
+  BandTable table;
+  uint32_t pair[kPairs];       // searched << 16 | candidate
+  float ext[4][kTileThreads / 64];
+  int n_own, n_cand, n_pairs, open_base;
+};
+
+// Positions p0 + kTileThreads u + tid of frame L: their boxes, all loads issued together.
+__device__ __forceinline__ void load_span(const MergeParams &P, const LargeFrame &L, int p0,
+                                          float4 q[kTileRegs]) {
+#pragma unroll
+  for (int u = 0; u < kTileRegs; ++u) {
+    const int p = p0 + u * kTileThreads + static_cast<int>(threadIdx.x);
+    q[u] = P.rec[L.lo + min(p, L.n - 1)].box;
+  }
+}
+
+// Candidate c tested against searched detection o: a suppressor ranked above it goes to its
+// place in rpred, or with `fill` to the longer list of a detection with more than
+// kPredSlots; both count it.
+__device__ __forceinline__ void test_owned(const MergeParams &P, TileLds &S, const int32_t *own,
+                                           bool fill, int o, int c) {
+  const float4 a = S.own_box[o], b = S.box[c];
+  const Aux x = S.own_aux[o], y = S.aux[c];
+  if (y.key < x.key && !(P.cross_only && x.roi == y.roi) &&
+      overlap_above(b, a, box_area(b), box_area(a), P.thr) && (!fill || S.at[o] >= 0)) {
+    const int slot = atomicAdd(&S.count[o], 1);
+    if (fill)
+      P.ovf[S.at[o] + slot] = S.pos[c];
+    else if (slot < kPredSlots)
+      P.rpred[kPredSlots * static_cast<int64_t>(own[o]) + slot] = S.pos[c];
+  }
+}
+
+// The nc collected candidates tested against the m searched detections: the candidates' band
+// table names each detection's among them, and those pairs are tested. Called by the whole
+// workgroup; ends with a barrier.
+__device__ void test_candidates(const MergeParams &P, TileLds &S, const int32_t *own, int m, int nc,
+                                bool fill) {
+  const int tid = threadIdx.x;
+  const bool each = !(P.thr >= 0.0f);
+  if (tid == 0) S.n_pairs = 0;
+  __syncthreads();
+  BandAxis ax, ay;
+  build_table(S.table, S.box[tid], nc, each, ax, ay);
+  int width = 64;
+  while (width < m) width *= 2;
+  const int o = tid & (width - 1), part = tid / width, parts = kTileThreads / width;
+  BandSpan v = {0, 0, 0, 0, false};
+  if (o < m) v = span_of(S.own_box[o], each, ax, ay);
+  const int words = v.named ? (nc + 31) / 32 : 0;
+  int count = 0;
+#pragma unroll 2
+  for (int w = part; w < words; w += parts) count += __popc(table_word(S.table, v, w));
+  int at = wave_places(&S.n_pairs, count);
+  for (int w = part; w < words; w += parts)
+    for (uint32_t b = table_word(S.table, v, w); b != 0 && at < kPairs; b &= b - 1)
+      S.pair[at++] = static_cast<uint32_t>(o) << 16 | static_cast<uint32_t>(32 * w + __builtin_ctz(b));
+  __syncthreads();
+  const int n_pairs = S.n_pairs;
+  if (n_pairs <= kPairs) {
+    for (int k = tid; k < n_pairs; k += kTileThreads)
+      test_owned(P, S, own, fill, S.pair[k] >> 16, S.pair[k] & 0xFFFFu);
+  } else {  // crowded: each lane its own
+    for (int w = part; w < words; w += parts)
+      for (uint32_t b = table_word(S.table, v, w); b != 0; b &= b - 1)
+        test_owned(P, S, own, fill, o, 32 * w + __builtin_ctz(b));
   }
   __syncthreads();
-  Lists l;
-  float4 bp;
-  uint64_t kp = 0;
-  int rp = 0;
-  bool wide = false;
-  if (valid) {
-    l = lists_of(P, a);
-    bp = P.rbox[a];
-    kp = P.rkey[a];
-    rp = P.rroi[a];
-    wide = P.rcell[a] == kWide;
-    for (int t0 = sub; t0 < l.total; t0 += kScanLanes * kBatch) {
-      int q[kBatch];
-      for (uint32_t h = search_step(P, l, wide, t0, kScanLanes, bp, kp, rp, q); h; h &= h - 1) {
-        const int slot = atomicAdd(&s_np[j], 1);
-        if (slot < kPredSlots) P.rpred[kPredSlots * static_cast<int64_t>(a) + slot] = q[__builtin_ctz(h)];
+}
+
+// The suppressors ranked above each of m <= kTileThreads detections (positions own[]) of
+// frame L, among the frame's boxes that can meet the rectangle around the m boxes. The point that two overlapping boxes share (see above) lies in
+// the one and so in the rectangle, hence the comparisons; they let NaN corners through, and
+// a NaN corner among the m, or a negative threshold, lets every box through. (Every
+// detection against every candidate: 10-28 us a tile of 250 by 270.)
+__device__ void search_owned(const MergeParams &P, TileLds &S, const LargeFrame &L,
+                             const int32_t *own, int m, bool fill) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float inf = __builtin_inff();
+  const bool each = !(P.thr >= 0.0f);
+  Rec r;
+  if (tid < m) {
+    r = P.rec[own[tid]];
+    S.own_box[tid] = r.box;
+    S.own_aux[tid] = r.aux;
+    S.count[tid] = 0;
+  }
+  const float e0 = wave_min(tid < m ? r.box.x : inf), e1 = wave_min(tid < m ? r.box.y : inf);
+  const float e2 = wave_min(tid < m ? -r.box.z : inf), e3 = wave_min(tid < m ? -r.box.w : inf);
+  if (lane == 0) {
+    S.ext[0][wave] = e0;
+    S.ext[1][wave] = e1;
+    S.ext[2][wave] = e2;
+    S.ext[3][wave] = e3;
+  }
+  const bool all = __syncthreads_or(tid < m && nan_corner(r.box)) || each;
+  const int w16 = lane & (kTileThreads / 64 - 1);
+  const float bx0 = wave_min(S.ext[0][w16]), by0 = wave_min(S.ext[1][w16]);
+  const float bx1 = -wave_min(S.ext[2][w16]), by1 = -wave_min(S.ext[3][w16]);
+  // Candidates are collected until the next ones do not fit, then tested (one call, so that
+  // its code is there once): `now` are the span's boxes to be placed next -- all that can
+  // meet, or, when those alone are too many, one of each thread's at a time.
+  int nc = 0, p0 = 0, u0 = -1;
+  while (p0 < L.n || nc > 0) {
+    bool full = p0 >= L.n;  // nothing more to collect
+    if (!full) {
+      float4 q[kTileRegs];
+      load_span(P, L, p0, q);
+      uint32_t now = 0;
+#pragma unroll
+      for (int u = 0; u < kTileRegs; ++u) {
+        const bool in = p0 + u * kTileThreads + tid < L.n;
+        const bool meets = all || !(q[u].x >= bx1 || q[u].z <= bx0 || q[u].y >= by1 || q[u].w <= by0);
+        now |= (in && meets && (u0 < 0 || u == u0) ? 1u : 0u) << u;
+      }
+      if (tid == 0) S.n_cand = nc;
+      __syncthreads();
+      int slot = wave_places(&S.n_cand, __popc(now));
+      __syncthreads();
+      const int total = S.n_cand;
+      __syncthreads();  // read by everyone before it is set again
+      full = total > kTileCand;
+      if (!full) {
+        for (; now != 0; now &= now - 1, ++slot) {
+          const int at = L.lo + p0 + __builtin_ctz(now) * kTileThreads + tid;
+          const Rec x = P.rec[at];
+          S.box[slot] = x.box;
+          S.aux[slot] = x.aux;
+          S.pos[slot] = at;
+        }
+        nc = total;
+        if (u0 < 0 || ++u0 == kTileRegs) {
+          p0 += kTileSpan;
+          u0 = -1;
+        }
+      } else if (nc == 0) {
+        u0 = 0;
       }
     }
-  }
-  __syncthreads();
-  const int np = s_np[j];
-  if (valid && sub == 0) P.rnpred[a] = np;
-  if (tid == 0) {
-    int64_t need = 0;
-    for (int k = 0; k < kSearchDets; ++k)
-      if (s_np[k] > kPredSlots) need += s_np[k];
-    int64_t at = need > 0 ? static_cast<int64_t>(atomicAdd(P.ovf_used, static_cast<unsigned long long>(need)))
-                          : 0;
-    for (int k = 0; k < kSearchDets; ++k) {
-      s_at[k] = -1;
-      if (s_np[k] <= kPredSlots) continue;
-      if (at + s_np[k] <= P.ovf_cap) s_at[k] = static_cast<int>(at);
-      at += s_np[k];
+    if (full && nc > 0) {
+      test_candidates(P, S, own, m, nc, fill);
+      nc = 0;
     }
-  }
-  __syncthreads();
-  if (!valid || np <= kPredSlots) return;
-  const int at = s_at[j];
-  if (sub == 0) P.rovf[a] = at;
-  if (at < 0) return;
-  for (int t0 = sub; t0 < l.total; t0 += kScanLanes * kBatch) {
-    int q[kBatch];
-    for (uint32_t h = search_step(P, l, wide, t0, kScanLanes, bp, kp, rp, q); h; h &= h - 1)
-      P.ovf[at + atomicAdd(&s_fill[j], 1)] = q[__builtin_ctz(h)];
   }
 }
 
-__global__ __launch_bounds__(kThreads) void search_kernel(const MergeParams P) {
-  static_assert(kSearchDets * kScanLanes == kThreads, "whole detections per workgroup");
-  if (!*P.big) return;  // every frame was decided in its index workgroup
-  const int n_grouped = P.frame_begin[P.n_frames];
-  const int n_blocks = (n_grouped + kSearchDets - 1) / kSearchDets;
-  for (int blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) {
-    __syncthreads();  // the previous block's readers of s_np, s_fill and s_at are done
-    search_block(P, blk, n_grouped);
+// The detections own[0 .. m) of frame L (entry k): their suppressors, then kept at once when
+// there are none, else onto the frame's open list.
+__device__ void search_part(const MergeParams &P, TileLds &S, const LargeFrame &L, int k,
+                            const int32_t *own, int m) {
+  const int tid = threadIdx.x;
+  int np = 0;
+  for (int fill = 0;; ++fill) {
+    search_owned(P, S, L, own, m, fill != 0);
+    if (fill) break;
+    np = tid < m ? S.count[tid] : 0;
+    __syncthreads();
+    if (tid < m) S.at[tid] = -1;
+    if (!__syncthreads_or(np > kPredSlots)) break;
+    if (tid == 0) {  // room for the longer lists, one atomic for all
+      unsigned long long need = 0;
+      for (int j = 0; j < m; ++j)
+        if (S.count[j] > kPredSlots) need += S.count[j];
+      int64_t at = static_cast<int64_t>(atomicAdd(P.ovf_used, need));
+      for (int j = 0; j < m; ++j) {
+        if (S.count[j] <= kPredSlots) continue;
+        if (at + S.count[j] <= P.ovf_cap) S.at[j] = static_cast<int>(at);
+        at += S.count[j];
+      }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) S.n_cand = 0;
+  __syncthreads();
+  const int slot = wave_places(&S.n_cand, np > 0 ? 1 : 0);
+  if (tid < m) {
+    const int a = own[tid];
+    P.rstate[a] = np > 0 ? kUndecided : kKept;
+    if (np > 0) {
+      P.rnpred[a] = np;
+      P.rovf[a] = S.at[tid];
+    } else {
+      P.keep[P.rec[a].aux.idx] = 1;
+    }
+  }
+  __syncthreads();
+  if (tid == 0 && S.n_cand > 0) S.open_base = atomicAdd(&P.large[k].open, S.n_cand);
+  __syncthreads();
+  if (np > 0) P.open[L.lo + S.open_base + slot] = own[tid];
+  __syncthreads();
+}
+
+__device__ __forceinline__ int cell_of(float v, float origin, float scale, int g) {
+  return static_cast<int>(
+      fminf(fmaxf(__fmul_rn(__fsub_rn(v, origin), scale), 0.0f), static_cast<float>(g - 1)));
+}
+
+__global__ __launch_bounds__(kTileThreads) void tile_kernel(const MergeParams P) {
+  __shared__ TileLds S;
+  const unsigned long long used = *P.large_used;
+  const int n_large = static_cast<int>(used >> 32);
+  const uint32_t n_tiles = static_cast<uint32_t>(used);
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (uint32_t v = blockIdx.x; v < n_tiles; v += gridDim.x) {
+    int k = -1;  // the tile's frame: the last one whose tiles start at or before v
+    for (int b = 0; b < n_large; b += 64) {
+      const int hits = __popcll(__ballot(b + lane < n_large && P.large[b + lane].start <= v));
+      k += hits;
+      if (hits < 64) break;
+    }
+    const LargeFrame L = P.large[k];
+    const int t = static_cast<int>(v - L.start), ty = t / L.g, tx = t - ty * L.g;
+    int n_own = 0, p0 = 0;  // collected until the next ones do not fit, then searched
+    while (p0 < L.n || n_own > 0) {
+      bool full = p0 >= L.n;
+      if (!full) {
+        float4 q[kTileRegs];
+        load_span(P, L, p0, q);
+        uint32_t own = 0;
+#pragma unroll
+        for (int u = 0; u < kTileRegs; ++u) {
+          const bool in = p0 + u * kTileThreads + tid < L.n;
+          own |= (in && cell_of(q[u].x, L.x0, L.sx, L.g) == tx && cell_of(q[u].y, L.y0, L.sy, L.g) == ty
+                      ? 1u : 0u) << u;
+        }
+        if (tid == 0) S.n_own = n_own;
+        __syncthreads();
+        int at = wave_places(&S.n_own, __popc(own));
+        __syncthreads();
+        const int total = S.n_own;
+        __syncthreads();  // read by everyone before it is set again
+        full = total > kTileSpan;  // (a span's detections fit alone)
+        if (!full) {
+          for (; own != 0; own &= own - 1)
+            S.own[at++] = L.lo + p0 + __builtin_ctz(own) * kTileThreads + tid;
+          n_own = total;
+          p0 += kTileSpan;
+        }
+      }
+      if (full) {
+        __syncthreads();
+        for (int o = 0; o < n_own; o += kTileThreads)
+          search_part(P, S, L, k, S.own + o, min(kTileThreads, n_own - o));
+        n_own = 0;
+      }
+    }
+    __syncthreads();
   }
 }
 
 // This round's decision for an undecided detection a with more suppressors than its
 // kPredSlots and no room for them in the overflow area (many boxes crowded on one spot):
-// its lists searched again, kBatch candidates at a time -- kSuppressed when one of its
-// suppressors is kept, kUndecided when one is still undecided, else kKept.
-__device__ __forceinline__ int32_t decide_searching(const MergeParams &P, int a) {
-  const Lists l = lists_of(P, a);
-  const bool wide = P.rcell[a] == kWide;
-  const float4 bp = P.rbox[a];
-  const uint64_t kp = P.rkey[a];
-  const int rp = P.rroi[a];
+// its frame searched again -- kSuppressed when one of its suppressors is kept, kUndecided
+// when one is still undecided, else kKept.
+__device__ __forceinline__ int32_t decide_searching(const MergeParams &P, const LargeFrame &L, int a) {
+  const float4 box = P.rec[a].box;
+  const Aux aux = P.rec[a].aux;
+  const float area = box_area(box);
   bool pending = false;
-  for (int t0 = 0; t0 < l.total; t0 += kBatch) {
-    int q[kBatch];
-    const uint32_t h = search_step(P, l, wide, t0, 1, bp, kp, rp, q);
-    int32_t s[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) s[u] = (h >> u & 1u) ? P.rstate[q[u]] : kSuppressed;
+  constexpr int kBatch = 8;
+  for (int p0 = 0; p0 < L.n; p0 += kBatch) {
+    float4 q[kBatch];
+    Aux x[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      if (s[u] == kKept) return kSuppressed;
-      pending |= s[u] == kUndecided;
+      const int p = L.lo + min(p0 + u, L.n - 1);
+      q[u] = P.rec[p].box;
+      x[u] = P.rec[p].aux;
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int p = L.lo + min(p0 + u, L.n - 1);
+      if (x[u].key < aux.key && overlap_above(q[u], box, box_area(q[u]), area, P.thr) &&
+          !(P.cross_only && x[u].roi == aux.roi)) {
+        const int32_t s = P.rstate[p];
+        if (s == kKept) return kSuppressed;
+        pending |= s == kUndecided;
+      }
     }
   }
   return pending ? kUndecided : kKept;
 }
 
-// The rounds of one frame, then its keep flags.
-// (frames of at most kSmallMax detections were decided by index_kernel)
-template <int kResolveThreads>
-__device__ __forceinline__ void resolve_frame(const MergeParams &P, int lo, int n) {
-  const int tid = threadIdx.x;
-  constexpr int kRes = 4;  // detections per thread and step, their loads issued together
-  for (int round = 0;; ++round) {
-    int pending = 0;
-    for (int a0 = lo + tid; a0 < lo + n; a0 += kRes * kResolveThreads) {
-      int32_t st[kRes], np[kRes];
-#pragma unroll
-      for (int u = 0; u < kRes; ++u) {
-        const int a = a0 + u * kResolveThreads;
-        st[u] = a < lo + n ? P.rstate[a] : kKept;
-        np[u] = st[u] == kUndecided ? P.rnpred[a] : 0;
-      }
-      // the states of their first kFirst suppressors, loaded together; the rest one by one
-      constexpr int kFirst = 4;
-      int32_t ps[kRes][kFirst];
-#pragma unroll
-      for (int u = 0; u < kRes; ++u)
-#pragma unroll
-        for (int k = 0; k < kFirst; ++k)
-          ps[u][k] = st[u] == kUndecided && k < np[u] && np[u] <= kPredSlots
-                         ? P.rstate[P.rpred[kPredSlots * static_cast<int64_t>(a0 + u * kResolveThreads) + k]]
-                         : kSuppressed;
-      uint32_t search = 0;  // detections with more suppressors than their slots
-#pragma unroll
-      for (int u = 0; u < kRes; ++u) {
-        if (st[u] != kUndecided) continue;
-        const int a = a0 + u * kResolveThreads;
-        // the list: in place, in the overflow area, or not kept (search again)
-        const int32_t *list = P.rpred + kPredSlots * static_cast<int64_t>(a);
-        if (np[u] > kPredSlots) {
-          const int at = P.rovf[a];
-          if (at < 0) {
-            search |= 1u << u;
-            continue;
-          }
-          list = P.ovf + at;
-        }
-        bool kept = false, und = false;
-#pragma unroll
-        for (int k = 0; k < kFirst; ++k) {
-          kept |= ps[u][k] == kKept;
-          und |= ps[u][k] == kUndecided;
-        }
-        for (int k0 = np[u] > kPredSlots ? 0 : kFirst; k0 < np[u] && !kept; k0 += kFirst) {
-          int32_t sk[kFirst];
-#pragma unroll
-          for (int k = 0; k < kFirst; ++k)
-            sk[k] = k0 + k < np[u] ? P.rstate[list[k0 + k]] : kSuppressed;
-#pragma unroll
-          for (int k = 0; k < kFirst; ++k) {
-            kept |= sk[k] == kKept;
-            und |= sk[k] == kUndecided;
-          }
-        }
-        if (kept || !und)
-          P.rstate[a] = kept ? kSuppressed : kKept;
-        else
-          pending = 1;
-      }
-      for (; search != 0; search &= search - 1) {
-        const int a = a0 + __builtin_ctz(search) * kResolveThreads;
-        const int32_t d = decide_searching(P, a);
-        if (d != kUndecided)
-          P.rstate[a] = d;
-        else
-          pending = 1;
-      }
-    }
-    __syncthreads();  // this round's decisions are visible to the next
-    if (!__syncthreads_or(pending)) break;
-    if (round >= n) {  // cannot happen (each round decides one); reported, not spun on
-      if (tid == 0) *P.status = 1;
-      break;
-    }
-  }
-  for (int a = lo + tid; a < lo + n; a += kResolveThreads)
-    P.keep[P.grouped[a]] = P.rstate[a] == kKept ? 1 : 0;
-}
-
-template <int kResolveThreads>
+// The rounds of each listed frame, then the keep flags of its open detections.
 __global__ __launch_bounds__(kResolveThreads) void resolve_kernel(const MergeParams P) {
-  if (!*P.big) return;  // every frame was decided in its index workgroup
-  for (int f = blockIdx.x; f < P.n_frames; f += gridDim.x) {
-    const int lo = P.frame_begin[f];
-    const int n = P.frame_begin[f + 1] - lo;
-    if (n > kSmallMax) resolve_frame<kResolveThreads>(P, lo, n);
+  const int n_large = static_cast<int>(*P.large_used >> 32);
+  const int tid = threadIdx.x;
+  for (int k = blockIdx.x; k < n_large; k += gridDim.x) {
+    const LargeFrame L = P.large[k];
+    for (int round = 0;; ++round) {
+      int pending = 0;
+      for (int j = tid; j < L.open; j += kResolveThreads) {
+        const int a = P.open[L.lo + j];
+        if (P.rstate[a] != kUndecided) continue;
+        const int np = P.rnpred[a];
+        const int32_t *list = P.rpred + kPredSlots * static_cast<int64_t>(a);
+        int32_t st = kKept;
+        const int at = np > kPredSlots ? P.rovf[a] : 0;
+        if (at < 0) {
+          st = decide_searching(P, L, a);
+        } else {
+          if (np > kPredSlots) list = P.ovf + at;
+          constexpr int kFirst = 4;  // suppressors whose states are loaded together
+          for (int j0 = 0; j0 < np && st != kSuppressed; j0 += kFirst) {
+            int32_t s[kFirst];
+#pragma unroll
+            for (int u = 0; u < kFirst; ++u) s[u] = P.rstate[list[min(j0 + u, np - 1)]];
+#pragma unroll
+            for (int u = 0; u < kFirst; ++u) {
+              if (s[u] == kKept)
+                st = kSuppressed;
+              else if (s[u] == kUndecided && st != kSuppressed)
+                st = kUndecided;
+            }
+          }
+        }
+        if (st != kUndecided) {
+          P.rstate[a] = st;
+          P.keep[P.rec[a].aux.idx] = st == kKept ? 1 : 0;
+        } else {
+          pending = 1;
+        }
+      }
+      __syncthreads();  // this round's decisions are visible to the next
+      if (!__syncthreads_or(pending)) break;
+      if (round >= L.n) {  // cannot happen (each round decides one); reported, not spun on
+        if (tid == 0) *P.status = 1;
+        break;
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -907,17 +1059,6 @@ __global__ __launch_bounds__(kResolveThreads) void resolve_kernel(const MergePar
 // cost.
 constexpr int kTiny = 512;
 constexpr int kTinyWords = kTiny / 32;
-
-// Inclusive prefix sum over the 64 lanes of a wave (DPP row shifts, then row broadcasts).
-__device__ __forceinline__ int wave_inclusive_sum(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31
-  return v;
-}
 
 // A detection as the pair tests read it: one 32-byte LDS record.
 struct alignas(16) TinyDet {
@@ -1027,6 +1168,46 @@ __global__ __launch_bounds__(kTiny) void tiny_kernel(const MergeParams P) {
   if (i == 0) *P.n_kept = overrun ? TG_E_INTERNAL : total;
 }
 
+// Compaction of up to kCountDets detections: each workgroup counts the kept ones before its
+// own by reading their flags, which costs less than a ticket and a look-back over the earlier
+// workgroups.
+__global__ __launch_bounds__(kCountThreads) void count_compact_kernel(const MergeParams P) {
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+  __shared__ int s_before[kCountThreads / 64], s_wave[kCountThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = count_of(P);
+  const int i0 = blockIdx.x * kCountThreads, i = i0 + tid;
+  const bool kept = i < n && P.keep[i] != 0;
+  int before = 0;
+  if (i0 < n) {
+#pragma unroll 4
+    for (int j = 4 * tid; j < i0; j += 4 * kCountThreads) {  // i0 is a multiple of 4
+      const i32x4 v = *reinterpret_cast<const i32x4 *>(P.keep + j);
+      before += (v.x != 0) + (v.y != 0) + (v.z != 0) + (v.w != 0);
+    }
+  }
+  tg_det d;
+  if (kept) d = P.dets[i];
+  const uint64_t b = __ballot(kept);
+  for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
+  if (lane == 0) {
+    s_before[wave] = before;
+    s_wave[wave] = __popcll(b);
+  }
+  __syncthreads();
+  int pos = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kCountThreads / 64; ++w) {
+    pos += s_before[w];
+    if (w < wave) pos += s_wave[w];
+    total += s_before[w] + s_wave[w];
+  }
+  if (kept) P.out[pos + __popcll(b & ((uint64_t(1) << lane) - 1))] = d;
+  // the workgroup with the last detection (the first one when there are none)
+  if (tid == 0 && (n > 0 ? i0 < n && n <= i0 + kCountThreads : i0 == 0))
+    *P.n_kept = *P.status != 0 ? TG_E_INTERNAL : total;
+}
+
 __global__ __launch_bounds__(kThreads) void compact_kernel(const MergeParams P) {
   __shared__ int s_blk, s_prefix;
   __shared__ int s_wave[kThreads / 64];
@@ -1080,46 +1261,66 @@ __global__ void zero_kernel(int32_t *a) { *a = 0; }
 
 int compact_blocks(int32_t n_max) { return (n_max + kCompactBlock - 1) / kCompactBlock; }
 
-int counter_stride(int32_t n_frames) { return n_frames <= kPaddedFramesMax ? kCounterStride : 1; }
-
-// Workspace layout, in bytes from the (16-byte aligned) start.
-struct Layout {
-  size_t state, counts, cursor, begin, grouped;
-  size_t rkey, rbox, rroi, rcell, rstate, rlist, rpred, rnpred, rovf, ovf, ebox, eaux, total;
-};
 size_t round16(size_t v) { return (v + 15) / 16 * 16; }
-Layout layout(int32_t n_max, int32_t n_frames) {
-  Layout L;
+
+// Bytes of the workspace: the look-back words and three more, per frame 516 bytes (12 past
+// 16,384 frames) for the table of bins, and per detection 344, of which the passes' arrays
+// take 152 and the rest holds suppressor lists of more than kPredSlots.
+size_t workspace_bytes(int32_t n_max, int32_t n_frames) {
+  const size_t n = static_cast<size_t>(n_max), f = static_cast<size_t>(n_frames);
+  const size_t head = sizeof(uint64_t) * (3 + static_cast<size_t>(compact_blocks(n_max))) +
+                      8 * f * (n_frames <= 16384 ? 64 : 1) + 4 * (f + 1) + 4 * n;
+  return round16(round16(head) + 212 * n) + 128 * n;
+}
+
+// Detections per workgroup of hist and scatter.
+int32_t chunk_of(int32_t n_max) {
+  const int64_t per = (int64_t(n_max) + kChunksMax - 1) / kChunksMax;
+  return static_cast<int32_t>((per + kBinThreads - 1) / kBinThreads * kBinThreads);
+}
+
+// Lays the arrays out from `ws` (null: only sizes them); returns the bytes before ovf, which
+// takes the rest.
+size_t lay_out(uint8_t *ws, int32_t n_max, MergeParams &P) {
   const size_t n = static_cast<size_t>(n_max);
-  // ticket and status word, the overflow area's cursor, one look-back word per compaction
-  // workgroup
-  L.state = 0;
-  L.counts = sizeof(uint64_t) * (3 + static_cast<size_t>(compact_blocks(n_max)));
-  const size_t slots = static_cast<size_t>(n_frames) * counter_stride(n_frames);
-  L.cursor = L.counts + sizeof(int32_t) * slots;
-  L.begin = L.cursor + sizeof(int32_t) * slots;
-  L.grouped = L.begin + sizeof(int32_t) * (static_cast<size_t>(n_frames) + 1);
-  L.rbox = round16(L.grouped + sizeof(int32_t) * n);
-  L.rkey = L.rbox + sizeof(float4) * n;
-  L.rroi = L.rkey + sizeof(uint64_t) * n;
-  L.rcell = L.rroi + sizeof(int32_t) * n;
-  L.rstate = L.rcell + sizeof(uint32_t) * n;
-  L.rlist = L.rstate + sizeof(int32_t) * n;
-  L.rpred = L.rlist + sizeof(int32_t) * 2 * (kCellsMax + 1) * n;
-  L.rnpred = L.rpred + sizeof(int32_t) * kPredSlots * n;
-  L.rovf = L.rnpred + sizeof(int32_t) * n;
-  L.ovf = L.rovf + sizeof(int32_t) * n;
-  L.ebox = round16(L.ovf + sizeof(int32_t) * kOvfPerDet * n);
-  L.eaux = L.ebox + sizeof(float4) * kCellsMax * n;
-  L.total = L.eaux + sizeof(int4) * kCellsMax * n;
-  return L;
+  size_t at = 0;
+  auto take = [&](auto *&p, size_t count) {
+    p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(ws + at);
+    at = round16(at + sizeof(*p) * count);
+  };
+  uint64_t *words;
+  P.n_words = 3 + compact_blocks(n_max);
+  take(words, static_cast<size_t>(P.n_words));
+  P.ticket = reinterpret_cast<uint32_t *>(words);
+  P.status = P.ticket + 1;
+  P.ovf_used = reinterpret_cast<unsigned long long *>(words + 1);
+  P.large_used = reinterpret_cast<unsigned long long *>(words + 2);
+  P.state = words + 3;
+  take(P.table, static_cast<size_t>(P.n_chunks) * P.n_bins);
+  take(P.bin_begin, static_cast<size_t>(P.n_bins) + 1);
+  take(P.large, n / 2 + 1);
+  at = (at + sizeof(Rec) - 1) / sizeof(Rec) * sizeof(Rec);  // (if the workspace is so aligned)
+  take(P.rec, n);
+  P.crec = P.rec;
+  P.frame = nullptr;
+  if (P.per_bin > 1) {
+    take(P.crec, n);
+    take(P.frame, n);
+  }
+  take(P.rstate, n);
+  take(P.rnpred, n);
+  take(P.rovf, n);
+  take(P.open, n);
+  take(P.rpred, kPredSlots * n);
+  P.ovf = reinterpret_cast<int32_t *>(ws + at);
+  return at;
 }
 
 }  // namespace
 
 extern "C" size_t tg_merge_workspace_bytes(int32_t n_max, int32_t n_frames) {
   if (n_max <= 0 || n_frames < 0) return 0;
-  return layout(n_max, n_frames).total;
+  return workspace_bytes(n_max, n_frames);
 }
 
 extern "C" int tg_merge(const tg_merge_args *a, void *stream) {
@@ -1134,14 +1335,12 @@ extern "C" int tg_merge(const tg_merge_args *a, void *stream) {
   if (!a->dets || !a->n_dets || !a->keep || !a->out || (a->n_scores > 0 && !a->scores))
     return TG_E_INVAL;
   if (int64_t(a->n_frames) + 1 > 0x7FFFFFFF / 2) return TG_E_INVAL;
-  const Layout L = layout(a->n_max, a->n_frames);
-  if (!a->workspace || a->workspace_bytes < L.total ||
+  const size_t bytes = workspace_bytes(a->n_max, a->n_frames);
+  if (!a->workspace || a->workspace_bytes < bytes ||
       reinterpret_cast<uintptr_t>(a->workspace) % 16 != 0)
     return TG_E_WORKSPACE;
-  const bool tiny = a->n_max <= kTiny;
 
-  uint8_t *ws = static_cast<uint8_t *>(a->workspace);
-  MergeParams P;
+  MergeParams P = {};
   P.dets = a->dets;
   P.n_dets = a->n_dets;
   P.n_max = a->n_max;
@@ -1153,59 +1352,36 @@ extern "C" int tg_merge(const tg_merge_args *a, void *stream) {
   P.keep = a->keep;
   P.out = a->out;
   P.n_kept = a->n_kept;
-  P.ticket = reinterpret_cast<uint32_t *>(ws + L.state);
-  P.status = reinterpret_cast<uint32_t *>(ws + L.state) + 1;
-  P.ovf_used = reinterpret_cast<unsigned long long *>(ws + L.state) + 1;
-  P.big = reinterpret_cast<uint32_t *>(ws + L.state) + 4;
-  P.state = reinterpret_cast<uint64_t *>(ws + L.state) + 3;
-  P.counts = reinterpret_cast<int32_t *>(ws + L.counts);
-  P.cursor = reinterpret_cast<int32_t *>(ws + L.cursor);
-  P.cstride = counter_stride(a->n_frames);
-  P.frame_begin = reinterpret_cast<int32_t *>(ws + L.begin);
-  P.grouped = reinterpret_cast<int32_t *>(ws + L.grouped);
-  P.rkey = reinterpret_cast<uint64_t *>(ws + L.rkey);
-  P.rbox = reinterpret_cast<float4 *>(ws + L.rbox);
-  P.rroi = reinterpret_cast<int32_t *>(ws + L.rroi);
-  P.rcell = reinterpret_cast<uint32_t *>(ws + L.rcell);
-  P.rstate = reinterpret_cast<int32_t *>(ws + L.rstate);
-  P.rlist = reinterpret_cast<int32_t *>(ws + L.rlist);
-  P.rpred = reinterpret_cast<int32_t *>(ws + L.rpred);
-  P.rnpred = reinterpret_cast<int32_t *>(ws + L.rnpred);
-  P.rovf = reinterpret_cast<int32_t *>(ws + L.rovf);
-  P.ovf = reinterpret_cast<int32_t *>(ws + L.ovf);
-  P.ovf_cap = std::min<int64_t>(int64_t(kOvfPerDet) * a->n_max, 0x7FFFFFFF);
-  P.ebox = reinterpret_cast<float4 *>(ws + L.ebox);
-  P.eaux = reinterpret_cast<int4 *>(ws + L.eaux);
-
-  if (tiny) {
+  if (a->n_max <= kTiny) {
     hipLaunchKernelGGL(tiny_kernel, dim3(1), dim3(kTiny), 0, s, P);
     return hipGetLastError() == hipSuccess ? TG_OK : TG_E_HIP;
   }
-  const int32_t words64 = 3 + compact_blocks(a->n_max);
-  const int32_t clear_n = a->n_frames > words64 ? a->n_frames : words64;
-  const uint32_t per = static_cast<uint32_t>((a->n_max + kThreads - 1) / kThreads);
-  hipLaunchKernelGGL(clear_kernel, dim3((clear_n + kThreads - 1) / kThreads), dim3(kThreads), 0,
-                     s, P, a->n_frames, words64);
-  hipLaunchKernelGGL(count_kernel, dim3(per), dim3(kThreads), 0, s, P);
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, s, P);
-  hipLaunchKernelGGL(scatter_kernel, dim3(per), dim3(kThreads), 0, s, P);
-  if (a->n_frames > 0) {
-    const bool small = a->n_max <= int64_t(kSmallFrame) * a->n_frames;
-    const dim3 frames(static_cast<uint32_t>(a->n_frames));
-    if (small)
-      hipLaunchKernelGGL(index_kernel<kSmallFrame>, frames, dim3(kSmallFrame), 0, s, P);
-    else
-      hipLaunchKernelGGL(index_kernel<1024>, frames, dim3(1024), 0, s, P);
-    const int search_blocks = (a->n_max + kSearchDets - 1) / kSearchDets;
-    hipLaunchKernelGGL(search_kernel, dim3(static_cast<uint32_t>(std::min(search_blocks, kGridCap))),
-                       dim3(kThreads), 0, s, P);
-    const dim3 resolve(static_cast<uint32_t>(std::min(a->n_frames, kGridCap)));
-    if (small)
-      hipLaunchKernelGGL(resolve_kernel<kSmallFrame>, resolve, dim3(kSmallFrame), 0, s, P);
-    else
-      hipLaunchKernelGGL(resolve_kernel<512>, resolve, dim3(512), 0, s, P);
+  P.chunk = chunk_of(a->n_max);
+  P.n_chunks = static_cast<int32_t>((int64_t(a->n_max) + P.chunk - 1) / P.chunk);
+  P.per_bin = std::max(1, (a->n_frames + kBinsMax - 1) / kBinsMax);
+  P.n_bins = (a->n_frames + P.per_bin - 1) / P.per_bin;
+  const size_t used = lay_out(static_cast<uint8_t *>(a->workspace), a->n_max, P);
+  if (used > bytes) return TG_E_INTERNAL;  // never: workspace_bytes covers the arrays
+  P.ovf_cap = std::min<int64_t>(static_cast<int64_t>((bytes - used) / sizeof(int32_t)), 0x7FFFFFFF);
+
+  const dim3 chunks(static_cast<uint32_t>(P.n_chunks));
+  hipLaunchKernelGGL(hist_kernel, chunks, dim3(kBinThreads), 0, s, P);
+  if (P.n_bins > 0) {
+    hipLaunchKernelGGL(scatter_kernel, chunks, dim3(kBinThreads), 0, s, P);
+    hipLaunchKernelGGL(local_kernel, dim3(static_cast<uint32_t>(P.n_bins)), dim3(kLocal), 0, s, P);
+    const int tiles = 2 * (a->n_max / kTileDets + 1);
+    hipLaunchKernelGGL(tile_kernel, dim3(static_cast<uint32_t>(std::min(tiles, kGridCap))),
+                       dim3(kTileThreads), 0, s, P);
+    const int large = std::min(a->n_frames, a->n_max / 128 + 1);
+    hipLaunchKernelGGL(resolve_kernel, dim3(static_cast<uint32_t>(std::min(large, kGridCap))),
+                       dim3(kResolveThreads), 0, s, P);
   }
-  hipLaunchKernelGGL(compact_kernel, dim3(static_cast<uint32_t>(compact_blocks(a->n_max))),
-                     dim3(kThreads), 0, s, P);
+  if (a->n_max <= kCountDets)
+    hipLaunchKernelGGL(count_compact_kernel,
+                       dim3(static_cast<uint32_t>((a->n_max + kCountThreads - 1) / kCountThreads)),
+                       dim3(kCountThreads), 0, s, P);
+  else
+    hipLaunchKernelGGL(compact_kernel, dim3(static_cast<uint32_t>(compact_blocks(a->n_max))),
+                       dim3(kThreads), 0, s, P);
   return hipGetLastError() == hipSuccess ? TG_OK : TG_E_HIP;
 }

@@ -27,6 +27,7 @@
 #include <atomic>
 #include <cstdint>
 
+#include "bands.h"
 #include "tg.h"
 
 // Built with -ffp-contract=off: every binary32 operation here is rounded on its own (no
@@ -34,6 +35,12 @@
 // implementation of the same steps.
 
 namespace {
+
+using tg_detail::band_axis;
+using tg_detail::band_of;
+using tg_detail::BandAxis;
+using tg_detail::transpose32;
+using tg_detail::wave_min;
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
@@ -50,7 +57,7 @@ constexpr int kSmallBoxes = 256;    // one workgroup
 constexpr int kSmallLanes = 4;      // lanes per box there
 constexpr int kSmallThreads = kSmallBoxes * kSmallLanes;
 constexpr int kSmallRois = 128;     // largest plan it takes (a canvas may hold all of it)
-constexpr int kBands = 15;          // per axis
+constexpr int kBands = 15;          // per axis: 30 bits of a patch's mask
 constexpr int kBandWords = 4;       // a canvas's header: band origin and scale per axis
 // Fewest patches whose bands fit their canvas's 8 bytes per patch:
 // kBandWords + 2 kBands ceil(n / 32) <= 2 n for every n >= 17.
@@ -177,45 +184,6 @@ __global__ __launch_bounds__(kThreads) void assign_kernel(const UnstitchParams P
   if (sl == 0) P.roi_of_box[b] = roi;
 }
 
-// The minimum over the 64 lanes of a wave, in every lane: DPP row shifts inside each row of
-// 16 lanes, then row broadcasts; lane 63 ends with it. (Lanes without a source keep their
-// own value.)
-template <int kCtrl, int kRows>
-__device__ __forceinline__ float dpp_min_step(float v) {
-  const int i = __float_as_int(v);
-  return fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(i, i, kCtrl, kRows, 0xF, false)));
-}
-__device__ __forceinline__ float wave_min(float v) {
-  v = dpp_min_step<0x111, 0xF>(v);  // row_shr:1
-  v = dpp_min_step<0x112, 0xF>(v);  // row_shr:2
-  v = dpp_min_step<0x114, 0xF>(v);  // row_shr:4
-  v = dpp_min_step<0x118, 0xF>(v);  // row_shr:8
-  v = dpp_min_step<0x142, 0xA>(v);  // row_bcast:15
-  v = dpp_min_step<0x143, 0xC>(v);  // row_bcast:31
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-
-// The 32 x 32 bit matrices held by the two halves of a wave (row l in lane l), transposed:
-// five exchanges with the lane 16, 8, 4, 2, 1 away, each swapping the blocks off the
-// diagonal. (30 ballots and selects for the same took 4 us a canvas.)
-__device__ __forceinline__ uint32_t transpose32(uint32_t x, int lane) {
-  constexpr uint32_t kLow[5] = {0x55555555u, 0x33333333u, 0x0F0F0F0Fu, 0x00FF00FFu, 0x0000FFFFu};
-#pragma unroll
-  for (int s = 4; s >= 0; --s) {
-    const int j = 1 << s;
-    const uint32_t m = kLow[s], y = __shfl_xor(x, j);
-    x = (lane & j) ? (x & ~m) | (y >> j & m) : (x & m) | (y & m) << j;
-  }
-  return x;
-}
-
-// The band of coordinate v (any value): non-decreasing in v, so a patch [x0, x1] touching
-// bands band(x0) .. band(x1) is named in the band of every point it holds.
-__device__ __forceinline__ int band_of(float v, float origin, float scale) {
-  const float t = fminf(fmaxf(__fmul_rn(__fsub_rn(v, origin), scale), 0.0f), float(kBands - 1));
-  return static_cast<int>(t);
-}
-
 // Lays out every canvas's patches (kWavesPer waves a canvas): its rectangles (positions
 // that hold no RoI of the canvas: one that no box meets) and, from kBandPatches patches on,
 // its header and band words. Workgroup 0 checks that canvas_begin cuts the plan into consecutive segments; where it does not, two
@@ -280,16 +248,11 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const UnstitchParams P) 
       y1 = fmaxf(y1, s_ext[3][w]);
     }
   }
-  // any finite origin and scale serve: a degenerate extent puts everything in band 0
-  float sx = kBands * __builtin_amdgcn_rcpf(x1 - x0), sy = kBands * __builtin_amdgcn_rcpf(y1 - y0);
-  if (!__builtin_isfinite(x0)) x0 = 0.0f;
-  if (!__builtin_isfinite(y0)) y0 = 0.0f;
-  if (!(__builtin_isfinite(sx) && sx > 0.0f)) sx = 0.0f;
-  if (!(__builtin_isfinite(sy) && sy > 0.0f)) sy = 0.0f;
+  const BandAxis ax = band_axis(x0, x1, kBands), ay = band_axis(y0, y1, kBands);
   int32_t *at = P.bands + 2 * static_cast<int64_t>(k_lo);
   if (wv == 0 && lane == 0) {
-    reinterpret_cast<float2 *>(at)[0] = make_float2(x0, sx);
-    reinterpret_cast<float2 *>(at)[1] = make_float2(y0, sy);
+    reinterpret_cast<float2 *>(at)[0] = make_float2(ax.origin, ax.scale);
+    reinterpret_cast<float2 *>(at)[1] = make_float2(ay.origin, ay.scale);
   }
   at += kBandWords;
   const int words = (n + 31) / 32;
@@ -298,11 +261,9 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const UnstitchParams P) 
     if (base >= 64 * kWavesPer)
       r = base + lane < n ? P.rect[k_lo + base + lane] : make_float4(inf, inf, -inf, -inf);
     uint32_t mask = 0;  // columns in bits 0 .. kBands - 1, rows above them
-    if (r.x <= r.z && r.y <= r.w) {
-      const int a = band_of(r.x, x0, sx), b = band_of(r.z, x0, sx);
-      const int d = band_of(r.y, y0, sy), e = band_of(r.w, y0, sy);
-      mask = ((2u << b) - (1u << a)) | ((2u << e) - (1u << d)) << kBands;
-    }
+    if (r.x <= r.z && r.y <= r.w)
+      mask = (((2u << band_of(r.z, ax, kBands)) - (1u << band_of(r.x, ax, kBands))) |
+              ((2u << band_of(r.w, ay, kBands)) - (1u << band_of(r.y, ay, kBands))) << kBands);
     // lane i of each half-wave: the half's patches in band i
     mask = transpose32(mask, lane);
     const int band = lane & 31, w = base / 32 + (lane >> 5);
@@ -370,12 +331,13 @@ __global__ __launch_bounds__(kBandThreads) void assign_bands_kernel(const Unstit
       } else {
         const int32_t *at = P.bands + 2 * static_cast<int64_t>(k_lo);
         const f32x4 head = *reinterpret_cast<const f32x4 *>(at);
+        const BandAxis ax = {head.x, head.y}, ay = {head.z, head.w};
         const int words = (n + 31) / 32;
         const int32_t *cols = at + kBandWords, *rows = cols + kBands * words;
-        const int x0 = band_of(area ? box.x1 : cx, head.x, head.y);
-        const int x1 = area ? band_of(box.x2, head.x, head.y) : x0;
-        const int y0 = band_of(area ? box.y1 : cy, head.z, head.w);
-        const int y1 = area ? band_of(box.y2, head.z, head.w) : y0;
+        const int x0 = band_of(area ? box.x1 : cx, ax, kBands);
+        const int x1 = area ? band_of(box.x2, ax, kBands) : x0;
+        const int y0 = band_of(area ? box.y1 : cy, ay, kBands);
+        const int y1 = area ? band_of(box.y2, ay, kBands) : y0;
         for (int w = sl; w < words; w += L) {
           uint32_t mc = 0, mr = 0;
           if (!area) {

@@ -247,3 +247,44 @@ def test_single_workgroup_path(torch):
     _, _, n_kept = run_gpu(torch, np.zeros(0, tg.DET_DTYPE), np.zeros(1, np.float32), 3, 0.5,
                            True, n_max=100)
     assert n_kept == 0
+
+
+@pytest.mark.parametrize("sizes", [[1023, 1024, 1025, 2], [6143, 6145], [1, 0, 1, 2600, 1]])
+def test_frames_around_the_lds_and_tile_limits(torch, sizes):
+    """Frames around the most one workgroup decides in LDS and around the span a tile's
+    workgroup reads at once."""
+    rng = np.random.default_rng(sum(sizes))
+    dets, scores = random_dets(rng, sum(sizes), len(sizes), 30, span=1500.0)
+    dets["frame"] = np.repeat(np.arange(len(sizes), dtype=np.int32), sizes)
+    dets["frame"] = dets["frame"][rng.permutation(len(dets))]
+    for cross in (True, False):
+        check(torch, dets, scores, len(sizes), 0.4, cross)
+
+
+@pytest.mark.parametrize("n_frames", [255, 256, 257, 600, 5000])
+def test_bins_of_frames(torch, n_frames):
+    """Frame counts around the switch to bins of several frames, with bins that do not fit one
+    workgroup: many detections in neighbouring small frames, one frame of 1,500, and one of
+    300 copies of a box (its pairs do not fit the list of the LDS path)."""
+    rng = np.random.default_rng(n_frames)
+    n = 9000
+    dets, scores = random_dets(rng, n, n_frames, 40, span=900.0)
+    dets["frame"][:1500] = 7
+    dets["frame"][1500:1800] = n_frames - 3
+    for c in ("x1", "y1", "x2", "y2"):
+        dets[c][1500:1800] = dets[c][1500]
+    dets["frame"][1800:4200] = 20 + rng.integers(0, 3, 2400)  # 800 each
+    dets["frame"][4200:6000] = n_frames // 2 + rng.integers(0, 40, 1800)
+    check(torch, dets, scores, n_frames, 0.5, False)
+    check(torch, dets, scores, n_frames, 0.3, True)
+
+
+@pytest.mark.parametrize("n_max", [513, 65536, 65537])
+def test_compaction_limits(torch, n_max):
+    """Capacities around the one-launch path and around the switch of the compaction, counts
+    far below the capacity, at a workgroup's edge and none."""
+    rng = np.random.default_rng(n_max)
+    for n in (0, 1, 511, 513, 3 * 1024):
+        if n <= n_max:
+            dets, scores = random_dets(rng, max(n, 1), 9, 8)
+            check(torch, dets[:n], scores, 9, 0.5, False, n_max=n_max)
