@@ -531,7 +531,7 @@ __device__ void add_large(const MergeParams &P, LocalLds &S, int lo, int n) {
   if (tid == 0) {
     // every tile reads the whole frame, so there are at most kTilesMax of them
     const float tiles = fminf(static_cast<float>(n) * (1.0f / kTileDets), static_cast<float>(kTilesMax));
-    const int g = max(1, static_cast<int>(ceilf(sqrtf(tiles))));
+    const int g = max(1, static_cast<int>(ceilf(__builtin_amdgcn_sqrtf(tiles))));
     const unsigned long long old =
         atomicAdd(P.large_used, (1ull << 32) | static_cast<unsigned long long>(g) * g);
     // any finite origin and scale serve: tiles only share the frame's detections out
