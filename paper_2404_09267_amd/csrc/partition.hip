@@ -9,14 +9,17 @@
 // an overlap tie goes to the lower number; patches are listed frame by frame, zones in
 // row-major order.
 //
-// Three launches on the caller's stream, with no atomics outside LDS:
+// Two launches on the caller's stream (three with more than kDirectFrames frames), with no
+// atomics outside LDS:
 //  1. count: one 256-thread workgroup per frame scores the frame's RoIs against the zones
 //     they touch, folds each into the winning zone's enclosing rectangle with LDS atomic
 //     min/max, and stores the frame's number of non-empty zones.
-//  2. scan: one workgroup turns the counts into each frame's first output position and
-//     writes the total.
+//  2. scan (more than kDirectFrames frames only): one workgroup turns the counts into each
+//     frame's first output position and writes the total.
 //  3. write: the per-frame pass of launch 1 again, then the frame's non-empty zones are
-//     written from its first position in zone order (ranks from ballots and mbcnt).
+//     written from its first position in zone order (ranks from ballots and mbcnt). Up to
+//     kDirectFrames frames its workgroup sums the earlier frames' counts itself, which costs
+//     less than the launch in between (1,920 frames: 11.7 -> 9.6 us).
 // Launch 3 recomputes the rectangles instead of keeping them: a frame's RoIs are a few
 // hundred bytes, while keeping its rectangles would take workspace by the zone count.
 // (A single launch that orders frames by an atomic ticket and finds each frame's position
@@ -35,6 +38,7 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxZones = 1024;  // zones per frame, e.g. 32 x 32
 constexpr int kScanThreads = 1024;
+constexpr int kDirectFrames = 4096;
 
 struct PartitionParams {
   const tg_roi *boxes;
@@ -153,13 +157,28 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(const PartitionParam
   if (tid == kScanThreads - 1) *P.n_patches = run;
 }
 
+template <bool kDirect>
 __global__ __launch_bounds__(kThreads) void write_kernel(const PartitionParams P) {
   __shared__ int acc[kMaxZones][4];
-  __shared__ int s_wave[kWaves];
+  __shared__ int s_wave[kWaves], s_before[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int f = blockIdx.x, Z = P.zones_x * P.zones_y;
+  int before_f = 0;
+  if (kDirect) {  // loaded ahead of the frame's own pass, which hides it
+#pragma unroll 8
+    for (int i = tid; i < f; i += kThreads) before_f += P.first[i];
+    for (int o = 32; o > 0; o >>= 1) before_f += __shfl_xor(before_f, o);
+    if (lane == 0) s_before[wave] = before_f;
+  }
   fold_frame(P, f, acc, P.zone_of_box != nullptr);
-  int pos = P.first[f];
+  int pos = 0;
+  if (kDirect) {
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) pos += s_before[w];
+    if (f == P.n_frames - 1 && tid == 0) *P.n_patches = pos + P.first[f];
+  } else {
+    pos = P.first[f];
+  }
   for (int base = 0; base < Z; base += kThreads) {
     const int r = base + tid;
     const bool u = r < Z && acc[r][0] != INT_MAX;
@@ -227,7 +246,11 @@ extern "C" int tg_partition(const tg_partition_args *a, void *stream) {
 
   const dim3 frames(static_cast<uint32_t>(a->n_frames));
   hipLaunchKernelGGL(count_kernel, frames, dim3(kThreads), 0, s, P);
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, s, P);
-  hipLaunchKernelGGL(write_kernel, frames, dim3(kThreads), 0, s, P);
+  if (a->n_frames <= kDirectFrames) {
+    hipLaunchKernelGGL(write_kernel<true>, frames, dim3(kThreads), 0, s, P);
+  } else {
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, s, P);
+    hipLaunchKernelGGL(write_kernel<false>, frames, dim3(kThreads), 0, s, P);
+  }
   return hipGetLastError() == hipSuccess ? TG_OK : TG_E_HIP;
 }
