@@ -19,7 +19,7 @@
 //  3. write: the per-frame pass of launch 1 again, then the frame's non-empty zones are
 //     written from its first position in zone order (ranks from ballots and mbcnt). Up to
 //     kDirectFrames frames its workgroup sums the earlier frames' counts itself, which costs
-//     less than the launch in between (1,920 frames: 11.7 -> 9.6 us).
+//     less than the launch in between (1,920 frames: 11.7 -> 11.0 us).
 // Launch 3 recomputes the rectangles instead of keeping them: a frame's RoIs are a few
 // hundred bytes, while keeping its rectangles would take workspace by the zone count.
 // (A single launch that orders frames by an atomic ticket and finds each frame's position

@@ -12,12 +12,11 @@
 // (row masks, local-root masks, the tile-local roots of the border pixels) indexed by
 // tile id. Same-address global atomics serialize across the chip, so no pass counts or
 // takes tickets on one word per workgroup of a large grid.
-//  1. scan:   one 256-thread workgroup per 16 tiles side by side streams the mask (16-byte
-//             loads where it can), stores a bit per tile (set: foreground) and writes the
+//  1. scan:   one 256-thread workgroup per 32 tiles side by side streams the mask (16-byte
+//             loads), stores a bit per tile (set: foreground) and writes the
 //             32 row masks of the tiles with foreground; it also zeroes the tickets,
 //             counters and look-back words of the later passes.
-//  2. list:   compacts the bitmap into the list of non-empty tiles (increasing ids), a
-//             few large workgroups with a decoupled look-back.
+//  2. list:   compacts the bitmap into the list of non-empty tiles (increasing ids).
 //  3. local:  one wave per listed tile, a grid of resident one-wave workgroups walking
 //             the list: union-find in LDS over the tile's row runs (one union per pair
 //             of touching runs); each tile-local root's label word gets its own frame
@@ -64,11 +63,12 @@ namespace {
 
 constexpr int kTile = 32;
 constexpr int kEntryThreads = 256;  // boxes pass: one wave per listed tile
-constexpr int kScanTiles = 16;     // tiles side by side per workgroup of the scan pass
-constexpr int kScanThreads = 256;  // 8 threads per row of 16 tiles, 64 pixels each
+constexpr int kScanTiles = 32;     // tiles side by side per workgroup of the scan pass
+constexpr int kScanThreads = 256;  // a wave per 8 rows, 16 pixels of each per lane
 constexpr int kListGroups = 2048;  // list-walking grid when the occupancy query fails
 constexpr int kListThreads = 256;  // list pass: kListPer bitmap words per thread
 constexpr int kListPer = 4;
+constexpr int64_t kListCount = 65536;  // most bitmap words it counts again per workgroup
 constexpr int kListChunk = kListThreads * kListPer;  // bitmap words per list workgroup
 constexpr int kBorderThreads = 256;
 // Labels: only the words of tile-local roots are used. Such a word holds kRootFlag | its
@@ -84,6 +84,8 @@ constexpr int kBandScanThreads = 1024;  // the scan over the bands' counts: one 
 constexpr int kDirectBands = 4096;  // up to this many bands, numbering sums the counts itself
 constexpr int kFilterBlock = 1024;  // components per workgroup of the filter pass
 constexpr int kFilterThreads = 256;
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 struct Comp {
   int32_t frame, root, x0, y0, x1, y1, area, unused;
@@ -286,105 +288,106 @@ __device__ __forceinline__ uint32_t col_span(int lo, int hi) {
 
 // ---- kernels ------------------------------------------------------------------------
 
-// Which tiles hold foreground: one workgroup per 16 tiles side by side (a 512 x 32 block
-// of one frame), thread t reading row t / 8 of the block, pixels 64 (t % 8) .. + 63 (the
-// row segments of two tiles) with 16-byte loads (kMode 2: mask 16-byte aligned and rows a
-// multiple of 16 bytes), dwords (kMode 1) or bytes (kMode 0), all issued before any is
-// used. Every block stores its 16 tiles' bits (half a bitmap word; the grid has
-// 2 wpb blocks per band, the last ones past the frame's width storing zeros) and writes
-// the 32 row masks of each tile with foreground to its record. Nothing is counted here:
-// the same-address atomics of a global list counter would serialize the workgroups. The
-// blocks also zero the n_clear counter words that the later passes use.
-template <int kMode>
+// Nonzero bytes of 16 as bits: bit i is byte i.
+__device__ __forceinline__ uint32_t nonzero_bytes(u32x4 v) {
+  uint32_t bits[2] = {0, 0};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t f = (v[i] | ((v[i] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu)) >> 7 & 0x01010101u;
+    bits[i >> 1] = __builtin_amdgcn_udot4(f, (i & 1) ? 0x80402010u : 0x08040201u, bits[i >> 1], false);
+  }
+  return bits[0] | bits[1] << 8;
+}
+
+// Which tiles hold foreground: one workgroup per 32 tiles side by side (1024 x 32 pixels of
+// one frame), a wave per 8 rows, a lane per 16 pixels of each, so that a wave's loads are
+// 1 KB runs of a row; all 8 are issued before any is used. They may start at any byte: the
+// chunk that crosses the end of a row is read from the row's last 16 bytes instead and
+// shifted (rows of fewer than 16 pixels: byte by byte). Every block stores its 32 tiles'
+// bits (a bitmap word) and writes the 32 row masks of each tile with foreground to its
+// record. Nothing is counted here: the same-address atomics of a global list counter would
+// serialize the workgroups. The blocks also zero the n_clear counter words that the later
+// passes use. HBM-bound: 166 MB of masks (20 x 3840x2160) in 27.8 us, 6.0 TB/s; with lanes
+// 64 bytes apart and byte-by-byte tests 41 us, and before, for rows not a multiple of 16 bytes
+// loads of four or one bytes.
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(const uint8_t *mask, int W, int H,
                                                             int64_t frame_px, Tiles T,
                                                             uint32_t *tile_bits,
                                                             uint32_t *rec_fg, uint64_t *words,
                                                             int64_t n_clear) {
+  typedef uint32_t u32x4a1 __attribute__((ext_vector_type(4), aligned(1)));
+  constexpr int kRows = kTile / (kScanThreads / 64);  // per wave
+  static_assert(kRows == 8, "a lane's rows are two 16-byte stores");
   __shared__ uint32_t s_bits;
-  const int t = threadIdx.x, r = t >> 3, q = t & 7;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t f = blockIdx.z;
   const int64_t g = (static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y) * gridDim.x +
                     blockIdx.x;
   const int64_t all = static_cast<int64_t>(gridDim.x) * gridDim.y * gridDim.z * kScanThreads;
   for (int64_t i = g * kScanThreads + t; i < n_clear; i += all) words[i] = 0;
   const int tx0 = blockIdx.x * kScanTiles, ty = blockIdx.y;
-  const int y = ty * kTile + r, x = tx0 * kTile + 64 * q;
+  const int x = tx0 * kTile + 16 * lane, y0 = ty * kTile + kRows * wave;
   if (t == 0) s_bits = 0;
-  uint32_t m0 = 0, m1 = 0;  // row y: foreground of pixels x + c and x + 32 + c as bit c
-  if (y < H && x < W) {
-    const uint8_t *row = mask + f * frame_px + static_cast<int64_t>(y) * W;
-    if (kMode == 2) {  // rows a multiple of 16 bytes: a chunk is wholly inside or outside
-      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-      u32x4 v[4];
+  const uint8_t *rows = mask + f * frame_px + static_cast<int64_t>(y0) * W;
+  uint32_t m[kRows];  // pixels x .. x + 15 of row y0 + j as bits, then of the lane's tile
+  if (W >= 16) {
+    const int xs = min(x, W - 16);
+    const int drop = min(x - xs, 16);  // pixels read again from the left (all 16: past the row)
+    u32x4 v[kRows];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        v[i] = x + 16 * i < W ? *reinterpret_cast<const u32x4 *>(row + x + 16 * i) : u32x4{0, 0, 0, 0};
+    for (int j = 0; j < kRows; ++j) {
+      v[j] = u32x4{0, 0, 0, 0};
+      if (y0 + j < H && x < W)
+        v[j] = __builtin_nontemporal_load(
+            reinterpret_cast<const u32x4a1 *>(rows + static_cast<int64_t>(j) * W + xs));
+    }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const uint32_t bit = ((v[i][j >> 2] >> (8 * (j & 3))) & 0xFFu) ? 1u << (16 * (i & 1) + j) : 0u;
-          if (i < 2)
-            m0 |= bit;
-          else
-            m1 |= bit;
-        }
-    } else if (kMode == 1) {  // rows a multiple of 4 bytes
-      uint32_t v[16];
-#pragma unroll
+    for (int j = 0; j < kRows; ++j) m[j] = nonzero_bytes(v[j]) >> drop;
+  } else {
+    for (int j = 0; j < kRows; ++j) {
+      m[j] = 0;
       for (int i = 0; i < 16; ++i)
-        v[i] = x + 4 * i < W ? *reinterpret_cast<const uint32_t *>(row + x + 4 * i) : 0u;
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t bit = ((v[i] >> (8 * k)) & 0xFFu) ? 1u << (4 * (i & 7) + k) : 0u;
-          if (i < 8)
-            m0 |= bit;
-          else
-            m1 |= bit;
-        }
-    } else {
-#pragma unroll 8
-      for (int i = 0; i < 32; ++i) {
-        m0 |= (x + i < W && row[x + i]) ? 1u << i : 0u;
-        m1 |= (x + 32 + i < W && row[x + 32 + i]) ? 1u << i : 0u;
-      }
+        if (y0 + j < H && x + i < W && rows[static_cast<int64_t>(j) * W + x + i]) m[j] |= 1u << i;
     }
   }
-  // lane l of a wave is row l / 8, tile pair l % 8: a tile holds foreground when any of
-  // the wave's rows does
-  const uint64_t b0 = __ballot(m0 != 0), b1 = __ballot(m1 != 0);
-  if ((t & 63) == 0) {
-    uint32_t m = 0;
+  // lanes 2 k and 2 k + 1 hold the halves of tile k's rows: the even lane takes both
+  uint32_t any = 0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      m |= ((b0 >> k) & 0x0101010101010101ull) ? 1u << (2 * k) : 0u;
-      m |= ((b1 >> k) & 0x0101010101010101ull) ? 1u << (2 * k + 1) : 0u;
-    }
-    if (m) atomicOr(&s_bits, m);
+  for (int j = 0; j < kRows; ++j) {
+    const uint32_t other = __builtin_amdgcn_update_dpp(0u, m[j], 0xB1, 0xF, 0xF, false);  // lane ^ 1
+    m[j] |= other << 16;
+    any |= m[j];
+  }
+  const uint64_t b = __ballot(any != 0 && (lane & 1) == 0);
+  if (lane == 0 && b) {  // bits 0, 2, 4, ... packed
+    uint64_t c = b;
+    c = (c | c >> 1) & 0x3333333333333333ull;
+    c = (c | c >> 2) & 0x0F0F0F0F0F0F0F0Full;
+    c = (c | c >> 4) & 0x00FF00FF00FF00FFull;
+    c = (c | c >> 8) & 0x0000FFFF0000FFFFull;
+    c = c | c >> 16;
+    atomicOr(&s_bits, static_cast<uint32_t>(c));
   }
   __syncthreads();
-  const uint32_t m = s_bits;
+  const uint32_t bits = s_bits;
   const int64_t band = f * T.tiles_y + ty;
-  if (t == 0)
-    reinterpret_cast<uint16_t *>(tile_bits)[band * 2 * T.wpb + blockIdx.x] =
-        static_cast<uint16_t>(m);
-  if (m == 0) return;  // uniform
-  const int id0 = static_cast<int>(band * T.tiles_x + tx0);
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int j = 2 * q + h;
-    if (m >> j & 1u) rec_fg[32 * static_cast<int64_t>(id0 + j) + r] = h ? m1 : m0;
+  if (t == 0) tile_bits[band * T.wpb + blockIdx.x] = bits;
+  const int k = lane >> 1;
+  if ((lane & 1) == 0 && (bits >> k & 1u)) {
+    uint32_t *r = rec_fg + 32 * (band * T.tiles_x + tx0 + k) + kRows * wave;
+    *reinterpret_cast<u32x4 *>(r) = u32x4{m[0], m[1], m[2], m[3]};
+    *reinterpret_cast<u32x4 *>(r + 4) = u32x4{m[4], m[5], m[6], m[7]};
   }
 }
 
 // Lists the non-empty tiles in increasing order (bands in order, each band's tiles left to
-// right): workgroup c (in ticket order) takes kListChunk words of the tile bitmap, kListPer
-// per thread; a block-wide scan of their
-// counts and a decoupled look-back over the workgroups place each set bit. The last
-// workgroup writes the count (0, with the status word set, if the look-back failed).
+// right): workgroup c takes kListChunk words of the tile bitmap, kListPer per thread; a
+// block-wide scan of their counts places each set bit after the bits of the earlier
+// chunks. Those are counted by every workgroup again while they are few (kListCount words:
+// 5.8 -> 4.8 us for 20 x 3840x2160, where a ticket and a look-back cost more than reading
+// 20 KB); past that, workgroups go in ticket order and look back. The last workgroup writes
+// the count (0, with the status word set, if the look-back failed).
+template <bool kCount>
 __global__ __launch_bounds__(kListThreads) void list_kernel(const uint32_t *tile_bits,
                                                             int64_t n_bit_words, Tiles T,
                                                             int32_t *tile_list,
@@ -392,37 +395,52 @@ __global__ __launch_bounds__(kListThreads) void list_kernel(const uint32_t *tile
                                                             int32_t n_chunks, uint32_t *n_list,
                                                             uint32_t *status) {
   __shared__ int s_chunk;
-  __shared__ int s_wave[kListThreads / 64];
+  __shared__ int s_wave[kListThreads / 64], s_before[kListThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0)
-    s_chunk = static_cast<int>(__hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(words), 1u,
-                                                      __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT));
-  __syncthreads();
-  const int c = s_chunk;  // < n_chunks: exactly n_chunks workgroups take tickets
+  if (!kCount) {
+    if (tid == 0)
+      s_chunk = static_cast<int>(__hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(words), 1u,
+                                                        __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT));
+    __syncthreads();
+  }
+  const int c = kCount ? static_cast<int>(blockIdx.x) : s_chunk;  // < n_chunks
   const int64_t w0 = static_cast<int64_t>(c) * kListChunk + tid * kListPer;
   uint32_t bits[kListPer];
-  int cnt = 0;
+  int cnt = 0, earlier = 0;
 #pragma unroll
   for (int i = 0; i < kListPer; ++i) {
     bits[i] = w0 + i < n_bit_words ? tile_bits[w0 + i] : 0u;
     cnt += __popc(bits[i]);
+  }
+  if (kCount) {  // 16-byte aligned, and kListChunk a multiple of what the threads read
+#pragma unroll 4
+    for (int i = 4 * tid; i < c * kListChunk; i += 4 * kListThreads) {
+      const u32x4 v = *reinterpret_cast<const u32x4 *>(tile_bits + i);
+      earlier += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+    for (int o = 32; o > 0; o >>= 1) earlier += __shfl_xor(earlier, o);
   }
   int incl = cnt;
   for (int o = 1; o < 64; o <<= 1) {
     const int v = __shfl_up(incl, o);
     if (lane >= o) incl += v;
   }
-  if (lane == 63) s_wave[wave] = incl;
+  if (lane == 63) {
+    s_wave[wave] = incl;
+    s_before[wave] = earlier;
+  }
   __syncthreads();
-  int before = 0, total = 0;
+  int before = 0, total = 0, prefix = 0;
 #pragma unroll
   for (int w = 0; w < kListThreads / 64; ++w) {
     if (w < wave) before += s_wave[w];
     total += s_wave[w];
+    prefix += s_before[w];
   }
-  bool failed;
-  const int prefix = tg_detail::lookback_prefix_block<kListThreads, 1>(state, c, total, &failed);
+  bool failed = false;
+  if (!kCount)
+    prefix = tg_detail::lookback_prefix_block<kListThreads, 1>(state, c, total, &failed);
   if (failed) {
     if (tid == 0) fail(status);
   } else {
@@ -1196,7 +1214,7 @@ extern "C" int tg_mask_rois(const tg_mask_rois_args *a, void *stream) {
     return TG_E_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int W = a->width, H = a->height;
-  const dim3 scan_groups(static_cast<uint32_t>(2 * T.wpb),
+  const dim3 scan_groups(static_cast<uint32_t>(T.wpb),
                          static_cast<uint32_t>(T.tiles_y), static_cast<uint32_t>(a->n_frames));
   const dim3 local_groups(static_cast<uint32_t>(std::min<int64_t>(
       T.n, resident_groups(reinterpret_cast<const void *>(local_kernel), kLocalThreads))));
@@ -1206,10 +1224,6 @@ extern "C" int tg_mask_rois(const tg_mask_rois_args *a, void *stream) {
   const dim3 entry_groups(static_cast<uint32_t>(std::min<int64_t>(
       (64 * T.n + kEntryThreads - 1) / kEntryThreads,
       resident_groups(reinterpret_cast<const void *>(boxes_kernel), kEntryThreads))));
-  // dword mask reads need every row start dword-aligned; 16-byte reads need the mask
-  // itself 16-byte aligned (and, for whole rows, rows a multiple of 16 bytes)
-  const uintptr_t mp = reinterpret_cast<uintptr_t>(a->mask);
-  const bool word = mp % 4 == 0 && W % 4 == 0, vec = mp % 16 == 0;
   const int64_t n_filter = (a->max_components + kFilterBlock - 1) / kFilterBlock;
 
   if (n_px == 0) {  // no frames: no components, no rows
@@ -1219,18 +1233,11 @@ extern "C" int tg_mask_rois(const tg_mask_rois_args *a, void *stream) {
   }
   uint32_t *status = reinterpret_cast<uint32_t *>(L.words + 2);
   uint32_t *n_list = reinterpret_cast<uint32_t *>(L.words + 3);
-  if (vec && W % 16 == 0)
-    hipLaunchKernelGGL(scan_kernel<2>, scan_groups, dim3(kScanThreads), 0, s, a->mask, W, H,
-                       frame_px, T, L.tile_bits, L.rec_fg, L.words, L.n_words);
-  else if (word)
-    hipLaunchKernelGGL(scan_kernel<1>, scan_groups, dim3(kScanThreads), 0, s, a->mask, W, H,
-                       frame_px, T, L.tile_bits, L.rec_fg, L.words, L.n_words);
-  else
-    hipLaunchKernelGGL(scan_kernel<0>, scan_groups, dim3(kScanThreads), 0, s, a->mask, W, H,
-                       frame_px, T, L.tile_bits, L.rec_fg, L.words, L.n_words);
+  hipLaunchKernelGGL(scan_kernel, scan_groups, dim3(kScanThreads), 0, s, a->mask, W, H, frame_px,
+                     T, L.tile_bits, L.rec_fg, L.words, L.n_words);
   const int64_t n_bit_words = n_bands * T.wpb, n_chunks = list_chunks(n_bit_words);
-  hipLaunchKernelGGL(list_kernel, dim3(static_cast<uint32_t>(n_chunks)), dim3(kListThreads), 0,
-                     s, L.tile_bits, n_bit_words, T, L.tile_list, L.words, L.list_state,
+  hipLaunchKernelGGL(n_bit_words <= kListCount ? list_kernel<true> : list_kernel<false>,
+                     dim3(static_cast<uint32_t>(n_chunks)), dim3(kListThreads), 0, s, L.tile_bits, n_bit_words, T, L.tile_list, L.words, L.list_state,
                      static_cast<int32_t>(n_chunks), n_list, status);
   hipLaunchKernelGGL(local_kernel, local_groups, dim3(kLocalThreads), 0, s, W, frame_px, T,
                      L.tile_list, n_list, L.rec_fg, L.rec_roots, L.rec_border, L.entries,

@@ -403,3 +403,44 @@ def test_mask_rois_unaligned_mask_pointer(torch):
     np.testing.assert_array_equal(areas, want_areas)
     np.testing.assert_array_equal(fb, want_fb)
     assert n_rois == len(want_rows) and n_comp == len(oracle.mask_rois(mask, 1)[0])
+
+
+@pytest.mark.parametrize("width", [1, 7, 15, 16, 17, 31, 33, 1008, 1023, 1024, 1025, 1039, 2050])
+def test_mask_rois_row_widths(torch, width):
+    """Rows of every kind to the scan: shorter than one 16-byte load, a few pixels past a
+    load, a tile and a workgroup's 1,024 pixels; mask bytes of any nonzero value, the mask
+    at every offset from a 16-byte boundary that rows of these widths bring."""
+    import oracle
+
+    rng = np.random.default_rng(width)
+    for F, H, off in ((2, 33, 0), (1, 70, 3)):
+        mask = (rng.random((F, H, width)) < 0.3) * rng.integers(1, 256, (F, H, width))
+        mask = mask.astype(np.uint8)
+        mask[:, -1, -1] = 128
+        say("mask widths", width, H, off)
+        buf = torch.zeros(mask.size + off, dtype=torch.uint8, device="cuda")
+        buf[off:] = torch.from_numpy(mask.reshape(-1)).cuda()
+        bufs = tg.MaskRoisBuffers(F, width, H, 1 << 14, 1 << 14)
+        tg.mask_rois(buf[off:], bufs, 2)
+        torch.cuda.synchronize()
+        rois, areas, fb, n_rois, n_comp = bufs.result()
+        want = oracle.mask_rois(mask, 2)
+        np.testing.assert_array_equal(rois, want[0])
+        np.testing.assert_array_equal(areas, want[1])
+        np.testing.assert_array_equal(fb, want[2])
+
+
+@pytest.mark.parametrize("frames", [32768, 32769])
+def test_mask_rois_list_limit(torch, frames):
+    """Two bitmap words per frame (rows 0 .. 31 and 32): the most words the list pass counts
+    again in every workgroup, and the first size at which its workgroups look back."""
+    rng = np.random.default_rng(frames)
+    mask = (rng.random((frames, 33, 8)) < 0.02).astype(np.uint8)
+    mask[-1, 32, 7] = 1
+    say("mask list", mask.shape)
+    rows, areas, fb, n_rois, n_comp = _run_rois(torch, mask, 1, 1 << 20, 1 << 21)
+    want_rows, want_areas, want_fb = oracle.mask_rois(mask, 1)
+    assert n_rois == n_comp == len(want_rows)
+    np.testing.assert_array_equal(rows, want_rows)
+    np.testing.assert_array_equal(areas, want_areas)
+    np.testing.assert_array_equal(fb, want_fb)

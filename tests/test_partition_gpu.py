@@ -104,3 +104,11 @@ def test_deterministic_and_ready_for_the_planner(torch):
     np.testing.assert_array_equal(a, b)
     plan = tg.plan_pack(a, 1920, 1080, 3840, 2160, 20, tg.GUILLOTINE_BSSF)
     assert plan.n_canvases >= 1
+
+
+@pytest.mark.parametrize("frames", [4096, 4097])
+def test_frames_around_the_direct_limit(torch, frames):
+    """The most frames whose earlier counts the write pass sums itself, and one more, for
+    which a pass in between scans the counts."""
+    boxes, fb = W.make_gmm_boxes(frames, 6, 640, 480, seed=frames, hi=200)
+    check(torch, boxes, fb, 640, 480, 3, 2)
