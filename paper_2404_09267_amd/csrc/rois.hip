@@ -178,11 +178,13 @@ __device__ __forceinline__ int g_load(const int32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Union-find over a tile's labels in LDS (unionfind.h).
+// Union-find over a tile's runs in LDS (unionfind.h), a run named by the position of its
+// first pixel (RunTile).
+__device__ __forceinline__ int run_slot(int pos) { return (pos >> 1) + (pos >> 5); }
 struct LdsLabels {
   int *L;
-  __device__ int parent(int i) const { return lds_load(&L[i]); }
-  __device__ int link(int i, int p) { return atomicMin(&L[i], p); }
+  __device__ int parent(int i) const { return lds_load(&L[run_slot(i)]); }
+  __device__ int link(int i, int p) { return atomicMin(&L[run_slot(i)], p); }
 };
 
 // Union-find over the flagged words of tile-local roots in global memory (one frame's
@@ -213,6 +215,9 @@ struct RootLabels {
       }
     }
     return old;
+  }
+  __device__ void relink(int i, int p) {  // i is no root: nothing waits for the old link
+    __hip_atomic_fetch_min(&L[i], p | kRootFlag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __device__ void flush() {
     if (n0) atomicSub(&band_count[band0], n0);
@@ -253,26 +258,26 @@ __device__ __forceinline__ TileAt tile_at(const Tiles &T, int t) {
 }
 
 // Run-based labelling of one 32x32 tile by one wave. A row's foreground is a 32-bit
-// word; its runs (maximal horizontal segments) are the union-find nodes, run j of row r
-// being node 16 r + j (a row holds at most 16 runs), so node order is raster order of the
-// runs' first pixels and every set ends rooted at the run holding its first pixel. A run
+// word; its runs (maximal horizontal segments) are the union-find nodes, a run being named
+// by the position 32 r + s of its first pixel, so node order is raster order and every set
+// ends rooted at its first pixel. At most one of two adjacent pixels starts a run: run
+// 32 r + s has slot 17 r + s / 2, the 17 spreading the rows over the LDS banks. A run
 // of row r touches, 8-connected, the runs of row r - 1 that meet columns s - 1 .. e + 1
-// of its span s .. e: consecutive runs of that row, from the one holding the lowest
-// foreground column of the window to the one holding the highest.
+// of its span s .. e: those from the one holding the lowest foreground column of the
+// window to the last that starts in it.
 constexpr int kLocalThreads = 64;  // one wave per tile: lane l on row l % 32
-constexpr int kRunNodes = kTile * 16;
+constexpr int kRunSlots = kTile * 17;
 
 struct RunTile {
-  int L[kRunNodes];                    // union-find links over the runs
-  unsigned long long span[kRunNodes];  // per root: row bits << 32 | column bits
-  int count[kRunNodes];                // per root: pixels
-  uint8_t col[kRunNodes];              // first column of each run
+  int L[kRunSlots];                    // union-find links over the runs
+  unsigned long long span[kRunSlots];  // per root: row bits << 32 | column bits
+  int count[kRunSlots];                // per root: pixels
 };
 
-// Ordinal of the run of row word `starts` (its runs' first columns as bits) that holds
+// First column of the run of row word `starts` (its runs' first columns as bits) that holds
 // column c, c being foreground.
-__device__ __forceinline__ int run_ordinal(uint32_t starts, int c) {
-  return __popc(starts & (0xFFFFFFFFu >> (31 - c))) - 1;
+__device__ __forceinline__ int run_start(uint32_t starts, int c) {
+  return 31 - __builtin_clz(starts & (0xFFFFFFFFu >> (31 - c)));
 }
 
 // Last column of the run that starts at column s of a row whose runs end at the bits of
@@ -458,15 +463,19 @@ __global__ __launch_bounds__(kListThreads) void list_kernel(const uint32_t *tile
 }
 
 // Labels the listed tiles, one wave per tile, a grid of resident one-wave workgroups
-// walking the list (each tile's list entry and row mask loaded one tile ahead). Lane l
+// walking the list (list entries loaded two tiles ahead, row masks one). Lane l
 // holds row l % 32; the row's runs are shared between the two halves of the wave by the
-// parity of their ordinal. Per tile: union-find over the runs in LDS (one union per pair
-// of touching runs of adjacent rows), each run resolved to its root, and the root's rows,
-// columns and pixel count folded in LDS. Written: the frame index of each tile-local root
+// parity of their ordinal. Per tile: each run starts out linked to the first run it touches
+// in the row above, and only a run that touches more of them joins sets (unionfind.h); each
+// run is then resolved to its root, and the root's rows, columns and pixel count folded in
+// LDS. Written: the frame index of each tile-local root
 // (flagged) in the label array -- the only label words any later pass reads --, the
 // tile's local-root row masks and border roots in its record, and one entry per local
 // component (its box in tile coordinates and its pixel count) in the tile's slots; the
 // number of local roots is added to the band's count of components.
+// Bound by the latency of its steps in LDS, 18 waves to a CU: 36.8 us for the 11,300 tiles
+// with foreground of 20 x 3840x2160; with a join per pair of touching runs, runs counted off
+// by ordinal and rows 16 words apart (8 rows to a bank) 45.4 us.
 __global__ __launch_bounds__(kLocalThreads) void local_kernel(int W, int64_t frame_px, Tiles T,
                                                               const int32_t *tile_list,
                                                               const uint32_t *n_list,
@@ -477,25 +486,24 @@ __global__ __launch_bounds__(kLocalThreads) void local_kernel(int W, int64_t fra
                                                               int32_t *label, int32_t *band_count,
                                                               uint32_t *status) {
   __shared__ RunTile S;
-  const int n = static_cast<int>(*n_list);
+  const int n = static_cast<int>(*n_list), step = static_cast<int>(gridDim.x);
   const int lane = threadIdx.x, r = lane & 31, half = lane >> 5;
-  int next_id = 0;
-  uint32_t next_row = 0;
-  if (static_cast<int>(blockIdx.x) < n) {
-    next_id = tile_list[blockIdx.x];
-    next_row = rec_fg[32 * static_cast<int64_t>(next_id) + r];
-  }
-  for (int it = blockIdx.x; it < n; it += gridDim.x) {
-    const int id = next_id;
+  int id1 = 0, id2 = 0;
+  uint32_t row1 = 0;
+  if (static_cast<int>(blockIdx.x) < n) id1 = tile_list[blockIdx.x];
+  if (static_cast<int>(blockIdx.x) + step < n) id2 = tile_list[blockIdx.x + step];
+  if (static_cast<int>(blockIdx.x) < n) row1 = rec_fg[32 * static_cast<int64_t>(id1) + r];
+  for (int it = blockIdx.x; it < n; it += step) {
+    const int id = id1;
+    const uint32_t w = row1;
+    id1 = id2;
+    if (it + 2 * step < n) id2 = tile_list[it + 2 * step];
+    if (it + step < n) row1 = rec_fg[32 * static_cast<int64_t>(id1) + r];
     const TileAt a = tile_at(T, id);
-    const uint32_t w = next_row;
-    if (it + static_cast<int>(gridDim.x) < n) {
-      next_id = tile_list[it + gridDim.x];
-      next_row = rec_fg[32 * static_cast<int64_t>(next_id) + r];
-    }
     const int tx0 = a.tx * kTile, ty0 = a.ty * kTile;
     int32_t *lf = label + a.f * frame_px;
-    const uint32_t up = __shfl(w, (lane + 63) & 63);  // row r - 1 (used for r > 0)
+    uint32_t up = __shfl(w, (lane + 63) & 63);  // row r - 1
+    if (r == 0) up = 0;
     const uint32_t st = w & ~(w << 1), en = w & ~(w >> 1), ust = up & ~(up << 1);
     // the runs of even ordinal go to half 0, odd to half 1: bit s of the prefix parity
     // of st is set when the run starting at s has an even ordinal
@@ -507,42 +515,49 @@ __global__ __launch_bounds__(kLocalThreads) void local_kernel(int W, int64_t fra
     par ^= par << 16;
     const uint32_t mine = half ? st & ~par : st & par;
     lds_barrier();  // the previous tile's reads of S are over
+    uint32_t more = 0;  // own runs that touch several runs of the row above
     for (uint32_t m = mine; m; m &= m - 1) {
-      const int s = __builtin_ctz(m), node = 16 * r + run_ordinal(st, s);
-      S.L[node] = node;
-      S.span[node] = 0;
-      S.count[node] = 0;
-      S.col[node] = static_cast<uint8_t>(s);
+      const int s = __builtin_ctz(m), e = run_end(en, s), pos = 32 * r + s, at = run_slot(pos);
+      const uint32_t x = up & col_span(s > 0 ? s - 1 : 0, e < kTile - 1 ? e + 1 : kTile - 1);
+      int parent = pos;
+      if (x) {
+        const int first = run_start(ust, __builtin_ctz(x));
+        parent = pos - s - 32 + first;
+        if (x & ust & ~(1u << first)) more |= 1u << s;
+      }
+      S.L[at] = parent;
+      S.span[at] = 0;
+      S.count[at] = 0;
     }
     lds_barrier();
     LdsLabels lab{S.L};
     bool ok = true;
-    if (r > 0) {
-      for (uint32_t m = mine; m; m &= m - 1) {
-        const int s = __builtin_ctz(m), e = run_end(en, s);
-        const uint32_t x = up & col_span(s > 0 ? s - 1 : 0, e < kTile - 1 ? e + 1 : kTile - 1);
-        if (!x) continue;
-        const int node = 16 * r + run_ordinal(st, s);
-        const int kb = run_ordinal(ust, __builtin_ctz(x)), ke = run_ordinal(ust, 31 - __builtin_clz(x));
-        for (int k = kb; k <= ke; ++k) ok &= tg_detail::uf_unite(lab, node, 16 * (r - 1) + k);
-      }
+    for (uint32_t m = more; m; m &= m - 1) {
+      const int s = __builtin_ctz(m), e = run_end(en, s);
+      const uint32_t x = up & col_span(s > 0 ? s - 1 : 0, e < kTile - 1 ? e + 1 : kTile - 1);
+      const int first = run_start(ust, __builtin_ctz(x));
+      for (uint32_t q = x & ust & ~(1u << first); q; q &= q - 1)
+        ok &= tg_detail::uf_unite(lab, 32 * r + s, 32 * (r - 1) + __builtin_ctz(q));
     }
     if (!ok) fail(status);
+    // the next tile's loads are taken here, before the stores below are in their way
+    asm volatile("" : "+v"(id2), "+v"(row1));
     lds_barrier();  // every union is in
     // each run to its root (left in L, so that after the barrier L maps a run to its root),
     // folded into the root's rows, columns and count; the roots written to the label array
     uint32_t roots = 0;
     for (uint32_t m = mine; m; m &= m - 1) {
-      const int s = __builtin_ctz(m), e = run_end(en, s), node = 16 * r + run_ordinal(st, s);
-      int R = tg_detail::uf_find(lab, node);
+      const int s = __builtin_ctz(m), e = run_end(en, s), pos = 32 * r + s;
+      int R = tg_detail::uf_find(lab, pos);
       if (R < 0) {
         fail(status);
-        R = node;
+        R = pos;
       }
-      if (R != node) lab.link(node, R);
-      atomicOr(&S.span[R], static_cast<unsigned long long>(1u << r) << 32 | col_span(s, e));
-      atomicAdd(&S.count[R], e - s + 1);
-      if (R == node) {
+      if (R != pos) lab.link(pos, R);
+      const int at = run_slot(R);
+      atomicOr(&S.span[at], static_cast<unsigned long long>(1u << r) << 32 | col_span(s, e));
+      atomicAdd(&S.count[at], e - s + 1);
+      if (R == pos) {
         roots |= 1u << s;
         const int P = (ty0 + r) * W + tx0 + s;
         lf[P] = P | kRootFlag;
@@ -560,8 +575,8 @@ __global__ __launch_bounds__(kLocalThreads) void local_kernel(int W, int64_t fra
       const uint32_t rw = pass ? w : __shfl(w, half ? kTile - 1 : 0);
       int32_t v = -1;
       if (rw >> c & 1u) {
-        const int R = S.L[16 * row + run_ordinal(rw & ~(rw << 1), c)];
-        v = (ty0 + (R >> 4)) * W + tx0 + S.col[R];
+        const int R = S.L[run_slot(32 * row + run_start(rw & ~(rw << 1), c))];
+        v = (ty0 + (R >> 5)) * W + tx0 + (R & 31);
       }
       border[64 * pass + lane] = v;
     }
@@ -580,14 +595,14 @@ __global__ __launch_bounds__(kLocalThreads) void local_kernel(int W, int64_t fra
     uint64_t *ent = entries + 256 * static_cast<int64_t>(id) + (incl - mine_roots);
     if (half == 0) {
       for (uint32_t m = roots; m; m &= m - 1) {
-        const int s = __builtin_ctz(m), node = 16 * r + run_ordinal(st, s);
-        const unsigned long long sp = S.span[node];
+        const int s = __builtin_ctz(m), pos = 32 * r + s, at = run_slot(pos);
+        const unsigned long long sp = S.span[at];
         const uint32_t cols = static_cast<uint32_t>(sp), rows = static_cast<uint32_t>(sp >> 32);
-        *ent++ = static_cast<uint64_t>(r * kTile + s) << 26 |
+        *ent++ = static_cast<uint64_t>(pos) << 26 |
                  static_cast<uint64_t>(__builtin_ctz(cols)) << 21 |
                  static_cast<uint64_t>(31 - __builtin_clz(cols)) << 16 |
                  static_cast<uint64_t>(31 - __builtin_clz(rows)) << 11 |
-                 static_cast<uint64_t>(S.count[node]);
+                 static_cast<uint64_t>(S.count[at]);
       }
     }
   }
@@ -607,7 +622,9 @@ __global__ __launch_bounds__(kLocalThreads) void local_kernel(int W, int64_t fra
 // tile (between offsets 0 and 1 of the first half, 16 and 17 of the second). Each pair of
 // touching runs is one union, the two roots loaded from the records only then -- a lane
 // has one or two pairs where a pixel-by-pixel walk had up to 48 positions, which a wave
-// would step through one union at a time.
+// would step through one union at a time. Bound by the dependent loads of its longest walks
+// (the unite's one load per step, no wait for the links it lowers on the way): 25.5 us for
+// 20 x 3840x2160; with finds to both roots before each link 34.7 us.
 __global__ __launch_bounds__(kBorderThreads) void merge_kernel(
     int W, int64_t frame_px, Tiles T, const uint32_t *tile_bits, const int32_t *tile_list,
     const uint32_t *n_list, const uint32_t *rec_fg, const int32_t *rec_border, int32_t *label,
@@ -649,8 +666,12 @@ __global__ __launch_bounds__(kBorderThreads) void merge_kernel(
       const bool lu = h == 0 && a.ty > 0 && tile_set(tile_bits, T, band - 1, a.tx - 1);
       const bool ld = h == 1 && a.ty + 1 < T.tiles_y && tile_set(tile_bits, T, band + 1, a.tx - 1);
       if (!(l || lu || ld)) continue;
+      const u32x4 *f4 = reinterpret_cast<const u32x4 *>(fs + 16 * h);
 #pragma unroll
-      for (int j = 0; j < 16; ++j) fg |= (fs[16 * h + j] & 1u) << j;
+      for (int j = 0; j < 4; ++j) {
+        const u32x4 v = f4[j];
+        fg |= ((v.x & 1u) | (v.y & 1u) << 1 | (v.z & 1u) << 2 | (v.w & 1u) << 3) << (4 * j);
+      }
       if (fg == 0) continue;
       own = 128 * static_cast<int64_t>(id) + 64 + 16 * h;
       main = 128 * static_cast<int64_t>(left) + 96 + 16 * h - 1;  // column 31, row 16 h - 1 + j
@@ -658,12 +679,13 @@ __global__ __launch_bounds__(kBorderThreads) void merge_kernel(
       corner_hi = 128 * static_cast<int64_t>(left + T.tiles_x) + 96;
       if (l) {  // neighbour j is row 16 h - 1 + j of the tile to the left
         const uint32_t *f = rec_fg + 32 * static_cast<int64_t>(left);
+        const u32x4 *g4 = reinterpret_cast<const u32x4 *>(f + 16 * h);
 #pragma unroll
-        for (int j = 0; j < 18; ++j) {
-          const int rr = 16 * h - 1 + j;
-          if (rr < 0 || rr >= kTile) continue;
-          nb |= (f[rr] >> 31) << j;
+        for (int j = 0; j < 4; ++j) {
+          const u32x4 v = g4[j];
+          nb |= (v.x >> 31 | v.y >> 31 << 1 | v.z >> 31 << 2 | v.w >> 31 << 3) << (4 * j + 1);
         }
+        nb |= f[h ? 15 : 16] >> 31 << (h ? 0 : 17);
       }
       if (lu) nb |= rec_fg[32 * static_cast<int64_t>(left - T.tiles_x) + 31] >> 31;
       if (ld) nb |= (rec_fg[32 * static_cast<int64_t>(left + T.tiles_x)] >> 31) << 17;

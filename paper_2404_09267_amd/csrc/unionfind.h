@@ -3,9 +3,9 @@
 //
 // Invariant: a link never points to a larger index -- a root points to itself, and links
 // only ever decrease (every write is an atomic min with a smaller index of the same set).
-// Each step of a find therefore moves to a strictly smaller index, and each retry of a
-// unite lowers the larger of its two roots, so both walks end; concurrent walks may see a
-// link lowered under them but never raised. The walks also check the invariant as they
+// Each step of a find therefore moves to a strictly smaller index, and each step of a unite
+// lowers one of its two nodes, so both walks end; concurrent walks may see a link lowered
+// under them but never raised. The walks also check the invariant as they
 // go: a link that points upwards, or below zero, can only come from an inconsistent array
 // (which the labelling never produces), and ends the walk with a failure instead of a
 // loop.
@@ -43,25 +43,50 @@ TG_UF_FN int uf_find(M &m, int i) {
   }
 }
 
-// Joins the sets of a and b: the larger root is linked under the smaller; if that root
-// was relinked meanwhile, retry from what it now points to. False when the array breaks
-// the invariant.
+// Lowers the link of i, which is no root, to p: M's relink where it has one (a link whose
+// replaced value nobody needs), else its link.
+template <class M>
+TG_UF_FN auto uf_relink(M &m, int i, int p, int) -> decltype(m.relink(i, p)) {
+  m.relink(i, p);
+}
+template <class M>
+TG_UF_FN void uf_relink(M &m, int i, int p, long) {
+  m.link(i, p);
+}
+
+// Joins the sets of a and b (Rem's walk, with splicing): the node whose parent is larger
+// gets the other's parent as its link, then continues from the parent it had. Two nodes with
+// one parent are joined, however far their root is; a root that gets the link is joined too,
+// unless it was linked meanwhile, when the walk goes on from what it then pointed to. Each
+// step loads one link. False when the array breaks the invariant.
+// A relink may replace a link that another walk lowered meanwhile: that walk, as this one,
+// goes on to join what the node pointed to before with what it wrote, so no connection is
+// lost.
 template <class M>
 TG_UF_FN bool uf_unite(M &m, int a, int b) {
+  int pa = m.parent(a), pb = m.parent(b);
+  if (pb < 0 || pb > b) return false;
   for (;;) {
-    a = uf_find(m, a);
-    b = uf_find(m, b);
-    if (a < 0 || b < 0) return false;
-    if (a == b) return true;
-    if (a > b) {
-      const int t = a;
+    if (pa < 0 || pa > a) return false;
+    if (pa == pb) return true;
+    if (pa < pb) {
+      int t = a;
       a = b;
       b = t;
+      t = pa;
+      pa = pb;
+      pb = t;
     }
-    const int old = m.link(b, a);
-    if (old == b) return true;
-    if (old < 0 || old > b) return false;
-    b = old;
+    if (pa == a) {
+      const int old = m.link(a, pb);
+      if (old == a) return true;
+      if (old < 0 || old > a) return false;
+      a = old;
+    } else {
+      uf_relink(m, a, pb, 0);
+      a = pa;
+    }
+    pa = m.parent(a);
   }
 }
 

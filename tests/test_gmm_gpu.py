@@ -444,3 +444,25 @@ def test_mask_rois_list_limit(torch, frames):
     np.testing.assert_array_equal(rows, want_rows)
     np.testing.assert_array_equal(areas, want_areas)
     np.testing.assert_array_equal(fb, want_fb)
+
+
+def test_mask_rois_runs_in_a_tile(torch):
+    """Runs of single pixels and of every column parity in a tile's rows: pairs that share a
+    slot's two columns across rows, rows of 16 runs, combs whose teeth meet in a late row (one
+    run touching 16 of the row above), stairs, and nested rings."""
+    m = np.zeros((6, 64, 96), np.uint8)
+    m[0, :31, 0::2] = 1
+    m[0, 31, :] = 1           # teeth joined at the tile's last row
+    m[1, 1:32, 1::2] = 1
+    m[1, 0, :] = 1            # ... at its first row, and over the border
+    m[1, 40, 1::2] = 1
+    for y in range(64):       # stairs in both directions, three apart
+        m[2, y, (y * 1) % 96] = m[2, y, (95 - 3 * y) % 96] = 1
+        m[3, y, (2 * y + np.arange(0, 96, 7)) % 96] = 1
+    for k in range(0, 16, 2):
+        m[4, k:64 - k, k:96 - k] = 1
+        m[4, k + 1:63 - k, k + 1:95 - k] = 0
+    m[5, 0::2, 0::2] = 1      # isolated pixels: 256 to a tile
+    say("mask runs", m.shape)
+    _assert_rois(torch, m, 1)
+    _assert_rois(torch, np.ascontiguousarray(m[:, ::-1, ::-1]), 1)
