@@ -8,11 +8,12 @@
 // Design for gfx950 (wave64, HBM-bound, write-dominated: 6 bytes written per canvas
 // pixel, 3 bytes read per covered pixel):
 //  - Work units (stitch_units.h): runs of 6144 canvas pixels in raster order, one
-//    256-thread workgroup each, launched in address order. A run is three whole 4 KB
+//    256-thread workgroup each, launched in address order (smaller ones for small launches
+//    and odd planes, kRun). A run is three whole 4 KB
 //    pages of each fp16 plane, so the workgroups resident on the chip write a compact
 //    window of whole pages that sweeps through the output; HBM absorbs writes fastest
-//    that way. (Runs of 2048 pixels on 128 threads were 6-15 % slower: the per-unit plan
-//    scan, list and barriers are then paid three times as often.)
+//    that way. (Runs of 2048 pixels were 20 % slower on 32 canvases of 1024x1024: the
+//    per-unit plan scan, list and barriers are then paid three times as often.)
 //  - A workgroup makes one pass over its run: it prefills its LDS staging row with the
 //    pad pixel (4 bytes per pixel: R, G, B and an unused byte, so that every patch edge
 //    falls on a dword boundary and no two patches ever share a staged dword); lists the
@@ -22,9 +23,10 @@
 //    row, on the run's 4-pixel grid -- as 13 dwords from the dword at or below its first
 //    source byte, realigns them with v_alignbyte, spreads the 3-byte pixels over dwords
 //    with v_perm and writes whole 4-pixel blocks (partial blocks at patch edges pixel by
-//    pixel); finally each lane converts two 8-pixel groups into three 16-byte fp16
-//    stores each, one per plane, nontemporal.
-//  - The footprint is small (under 10 KB of LDS, under 64 VGPRs), so sixteen workgroups
+//    pixel); finally each lane converts its 8-pixel groups into three 16-byte fp16
+//    stores each, one per plane, nontemporal (planes and outputs of any other size or
+//    alignment: the 16-byte chunks of memory that the run meets, below).
+//  - The footprint is small (26 KB of LDS, under 64 VGPRs), so several workgroups
 //    are resident per CU and one workgroup's plan and frame round trips overlap the
 //    others' stores. Every wave loads before it stores, so no wait for a load ever waits
 //    on a store. Lane-dependent choices are selects, not branches.
@@ -50,11 +52,19 @@ using tg_detail::StitchGeometry;
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr int kRun = tg_detail::kStitchRun;  // pixels per unit
-constexpr int kGroups = kRun / 8 / kThreads; // 8-pixel groups per thread
+// Pixels per unit: kRun, the size the unit numbers of a unit_order refer to. Launches without
+// one use smaller runs where those are faster: up to kSmallPixels canvas pixels runs of
+// kRunSmall, since 6144-pixel units would leave CUs idle (2.5 M pixels are 407 of them; one
+// 1024x1024 canvas 6.6 -> 5.4 us, two 7.5 -> 6.2; three cost 7.6 against 8.2 but ten 18.9
+// against 18.7, 32 of them 20 % more), and runs of kRunAny where a plane does not take whole
+// 16-byte groups (19 canvases of 999x667 26.5 -> 24.5 us, one 9.0 -> 7.5: its conversion
+// reads LDS three times, and more, smaller workgroups per CU hide that).
+constexpr int kRun = tg_detail::kStitchRun;
+constexpr int kRunSmall = 2048;
+constexpr int kRunAny = 4096;
+constexpr int64_t kSmallPixels = 2500000;
 constexpr int kRecs = 40;                    // patches one list holds (more: further lists)
 constexpr int kPx = 16;                      // pixels per piece (four 4-pixel blocks)
-static_assert(kRun == 8 * kThreads * kGroups, "whole 8-pixel groups per thread");
 
 struct StitchParams {
   const uint8_t *frames;
@@ -391,8 +401,10 @@ __device__ __forceinline__ uint32_t norm_pair(const StitchParams &P, const uint1
   return norm2(x0, x1, P.fa[k], P.fc[k]);
 }
 
-template <bool kVec, bool kLut>
+template <bool kVec, bool kLut, int kRun>
 __global__ __launch_bounds__(kThreads) void stitch_kernel(const StitchParams P) {
+  constexpr int kGroups = kRun / 8 / kThreads;  // 8-pixel groups per thread
+  static_assert(kRun == 8 * kThreads * kGroups, "whole 8-pixel groups per thread");
   __shared__ __attribute__((aligned(16))) uint32_t s_px[kRun + 8];  // + 8: dummy slot
   __shared__ Shared S;
   __shared__ uint16_t s_lut[kLut ? 3 * 256 : 2];
@@ -479,8 +491,8 @@ __global__ __launch_bounds__(kThreads) void stitch_kernel(const StitchParams P) 
   // whole workgroup, so the selects are on scalars). Only the chunks at the ends of a run
   // are written element by element. (Two-byte stores throughout, as before, kept the store
   // path busy with eight times the instructions: six 2047x1151 frames onto 19 canvases of
-  // 999x667, 102 MB: 59.6 us; as built 26.9 us, 3.8 TB/s. Chunks on 16-byte boundaries
-  // only, joined from neighbouring lanes: 27.6 us.)
+  // 999x667, 102 MB: 59.6 us; as built 26.9 us, and 24.9 us, 4.1 TB/s, in runs of 4096.
+  // Chunks on 16-byte boundaries only, joined from neighbouring lanes: 27.6 us.)
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     uint16_t *base = P.out + (static_cast<int64_t>(c_local) * 3 + k) * P.plane + R.p0;
@@ -588,14 +600,25 @@ extern "C" int tg_stitch(const tg_stitch_args *a, void *stream) {
 
   const bool vec = (g.plane % 8 == 0) && (reinterpret_cast<uintptr_t>(a->out) % 16 == 0);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const dim3 grid(static_cast<uint32_t>(g.n_units));
-  if (vec && nm.affine)
-    hipLaunchKernelGGL((stitch_kernel<true, false>), grid, dim3(kThreads), 0, s, P);
-  else if (vec)
-    hipLaunchKernelGGL((stitch_kernel<true, true>), grid, dim3(kThreads), 0, s, P);
-  else if (nm.affine)
-    hipLaunchKernelGGL((stitch_kernel<false, false>), grid, dim3(kThreads), 0, s, P);
+  // runs of `run` pixels where the units may be numbered freely (never more than fit int32)
+  const auto runs_of = [&](int run) {
+    const int64_t runs = (g.plane + run - 1) / run, units = runs * a->canvas_count;
+    if (a->unit_order || units > 0x7FFFFFFF) return false;
+    P.runs = static_cast<int32_t>(runs);
+    P.n_units = static_cast<int32_t>(units);
+    return true;
+  };
+  const auto launch = [&](auto affine, auto lut) {
+    hipLaunchKernelGGL(nm.affine ? affine : lut, dim3(static_cast<uint32_t>(P.n_units)),
+                       dim3(kThreads), 0, s, P);
+  };
+  if (!vec && runs_of(kRunAny))
+    launch(stitch_kernel<false, false, kRunAny>, stitch_kernel<false, true, kRunAny>);
+  else if (!vec)
+    launch(stitch_kernel<false, false, kRun>, stitch_kernel<false, true, kRun>);
+  else if (g.plane * a->canvas_count <= kSmallPixels && runs_of(kRunSmall))
+    launch(stitch_kernel<true, false, kRunSmall>, stitch_kernel<true, true, kRunSmall>);
   else
-    hipLaunchKernelGGL((stitch_kernel<false, true>), grid, dim3(kThreads), 0, s, P);
+    launch(stitch_kernel<true, false, kRun>, stitch_kernel<true, true, kRun>);
   return hipGetLastError() == hipSuccess ? TG_OK : TG_E_HIP;
 }

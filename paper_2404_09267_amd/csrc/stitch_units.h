@@ -1,5 +1,6 @@
 // Work units of one tg_stitch launch, shared by the kernel launcher (stitch.hip) and the
-// host-side unit count (plan.cpp).
+// host-side unit count (plan.cpp). These are the units that a unit order names; launches
+// without one may be cut finer (stitch.hip).
 //
 // A canvas plane is cut, in raster order, into runs of kStitchRun pixels (the last run
 // of a canvas may be shorter); one unit = one run of one canvas, processed by one

@@ -381,3 +381,25 @@ def test_argument_struct_keeps_its_tensors(torch):
     del a
     gc.collect()
     assert alive() is None
+
+
+@pytest.mark.parametrize("cw,ch,count", [(64, 32, 1), (64, 33, 2), (8, 1, 3), (1250, 1000, 2),
+                                         (1250, 1000, 3), (1250, 1002, 2), (4097, 1, 2),
+                                         (999, 667, 2), (999, 667, 4)])
+def test_run_sizes(torch, cw, ch, count):
+    """Launches around the sizes at which the run length changes (2.5 M canvas pixels, planes
+    of whole runs and a pixel or a row past them), in address order and through a unit order,
+    whose unit numbers always mean runs of 6144 pixels."""
+    rng = np.random.default_rng(cw * ch)
+    rois = W.random_rois(rng, 60 * count, 2, 1300, 700, 1, min(cw, 900), min(ch, 600))
+    frames = W.random_frames_np(2, 700, 1300, 11)
+    plan = tg.plan_pack(rois, cw, ch, 1300, 700, 2, 0)
+    count = min(count, plan.n_canvases)
+    dplan = tg.DevicePlan(rois, plan)
+    frames_d = torch.from_numpy(frames).cuda()
+    want = oracle.stitch(frames, rois, oracle_plan(plan), 0, count, cw, ch, W.MEAN, W.STD, W.PAD)
+    n_units = tg.stitch_units(cw, ch, count)
+    for order in (None, torch.arange(n_units - 1, -1, -1, dtype=torch.int32, device="cuda")):
+        say("run size", cw, ch, count, order is not None)
+        got = run_stitch(frames_d, rois, plan, 0, count, cw, ch, dplan=dplan, unit_order=order)
+        np.testing.assert_array_equal(got, want)
