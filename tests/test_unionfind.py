@@ -124,6 +124,29 @@ def test_random_forests_give_components(harness):
         assert all(low[arr[i]] == low[i] for i in range(n))  # links stay in their set
 
 
+def test_unites_between_the_accesses_of_others(harness):
+    """Unites that run between two accesses of another one, nested: the components are those
+    of the edges, each rooted at its smallest index, and every root that stops being one is
+    linked once (the components are counted by that)."""
+    rng = np.random.default_rng(13)
+    lines, want = [], []
+    for trial in range(400):
+        n = int(rng.integers(2, 60))
+        m = int(rng.integers(1, 3 * n))
+        near = trial % 2  # chains of neighbours, or any pairs
+        a = rng.integers(0, n, m)
+        b = np.clip(a + rng.integers(-3, 4, m), 0, n - 1) if near else rng.integers(0, n, m)
+        edges = list(zip(a.tolist(), b.tolist()))
+        lines.append(f"N {n} {int(rng.integers(1, 2**31))} {m} " +
+                     " ".join(f"{x} {y}" for x, y in edges))
+        want.append((n, _components(n, edges)))
+    for (n, low), g in zip(want, harness(lines)):
+        assert g[0] == 1
+        assert g[1] == n - len(set(low))
+        assert g[2:2 + n] == low
+        assert all(0 <= p <= i for i, p in enumerate(g[2 + n:]))
+
+
 def test_random_arrays_walk_like_the_definition(harness):
     """Arbitrary arrays, most of them broken: the find equals following the links (or
     -1), and its reads stay bounded by the array's size."""

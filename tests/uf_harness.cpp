@@ -7,9 +7,15 @@
 //   E n m a_0 b_0 .. a_m b_m   -> from the identity array, unite every edge in order;
 //                                 "<all ok> r_0 .. r_{n-1} q_0 .. q_{n-1}" with r_i the
 //                                 find of i after all edges and q the array
+//   N n seed m a_0 b_0 .. a_m b_m -> as E, but at any access of a unite the next edges may be
+//                                 united to their end first, nested up to 8 deep (the seed says
+//                                 where), as a concurrent walk would do between two accesses;
+//                                 "<all ok> <root links> r_0 .. r_{n-1} q_0 .. q_{n-1}"
 // The accessor counts parent() reads so that the tests can bound the work of a walk over
 // a broken array.
+#include <cstdint>
 #include <cstdio>
+#include <utility>
 #include <vector>
 
 #include "unionfind.h"
@@ -45,6 +51,44 @@ bool read_array(int n, Plain &m) {
 
 void print_array(const Plain &m) {
   for (int v : m.a) std::printf(" %d", v);
+}
+
+// An array whose accesses let other unites run first.
+struct Nested {
+  std::vector<int> a;
+  std::vector<std::pair<int, int>> edges;
+  size_t next = 0;
+  int depth = 0, root_links = 0;
+  uint32_t state = 1;
+  bool ok = true;
+  void others();
+  int parent(int i) {
+    others();
+    return a[i];
+  }
+  int link(int i, int p) {
+    others();
+    const int old = a[i];
+    if (p < old) a[i] = p;
+    if (old == i && p < i) ++root_links;
+    return old;
+  }
+  void relink(int i, int p) {
+    others();
+    if (a[i] == i) ok = false;  // only a node that is no root is relinked
+    if (p < a[i]) a[i] = p;
+  }
+};
+
+void Nested::others() {
+  while (depth < 8 && next < edges.size()) {
+    state = state * 1664525u + 1013904223u;
+    if (state >> 30 != 0) return;
+    const auto e = edges[next++];
+    ++depth;
+    ok = tg_detail::uf_unite(*this, e.first, e.second) && ok;
+    --depth;
+  }
 }
 
 }  // namespace
@@ -89,6 +133,25 @@ int main() {
       std::printf("%d", ok ? 1 : 0);
       for (int k = 0; k < n; ++k) std::printf(" %d", tg_detail::uf_find(m, k));
       print_array(m);
+      std::printf("\n");
+    } else if (op == 'N') {
+      int e;
+      Nested q;
+      if (std::scanf("%u %d", &q.state, &e) != 2) return 2;
+      for (int k = 0; k < n; ++k) q.a.push_back(k);
+      for (int k = 0; k < e; ++k) {
+        int a, b;
+        if (std::scanf("%d %d", &a, &b) != 2) return 2;
+        q.edges.emplace_back(a, b);
+      }
+      while (q.next < q.edges.size()) {
+        const auto x = q.edges[q.next++];
+        q.ok = tg_detail::uf_unite(q, x.first, x.second) && q.ok;
+      }
+      std::printf("%d %d", q.ok ? 1 : 0, q.root_links);
+      m.a = q.a;
+      for (int k = 0; k < n; ++k) std::printf(" %d", tg_detail::uf_find(m, k));
+      for (int v : q.a) std::printf(" %d", v);
       std::printf("\n");
     } else {
       return 2;
