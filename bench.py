@@ -353,8 +353,8 @@ def merge_cost(tg, W, torch, uargs, ubufs, name, n_frames, with_oracle: bool,
                     f"up to {int(per_frame.max())} per frame), IoU 0.5 across patches",
            "kept": int(mb.n_kept.item()), "us_per_call": round(us, 2),
            "bound": ("latency: one launch (capacities up to 512 detections)" if n_boxes <= 512 else
-                     "latency: 8 launches (frame index and suppression rounds), about 0.3 KB "
-                     "per detection")}
+                     "latency: 6 launches (frames decided in LDS, larger ones by tiles and "
+                     "rounds)")}
     if with_oracle:
         from oracle import merge
 
@@ -606,7 +606,7 @@ def unstitch_cost(tg, torch, uargs, ubufs, launches: int = 50):
     mb = (n_boxes * (16 + 4 + 4) + int(ubufs.n_out.item()) * 28) / 1e6
     return {"boxes": n_boxes, "us_per_call": round(us, 2), "median_us": round(t[launches // 2], 2),
             "mboxes_per_s": round(n_boxes / us, 1),
-            "bound": f"latency: 2 or 3 launches, {mb:.2f} MB moved"}
+            "bound": f"latency: 1 to 3 launches, {mb:.2f} MB moved"}
 
 
 _W = None
@@ -744,9 +744,12 @@ def main():
         if cnt.get("stitch_source_sha256_16") == source_hash() and \
                 cnt.get("workload") == wl.name:
             traffic = cnt.get("hbm_bytes_per_launch")
+    # launches of up to 2.5 M canvas pixels without a unit order run in shorter units
+    small = max(c for _, c in batches) * wl.canvas ** 2 <= 2500000 and args.unit_order == "natural"
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": "stitch_kernel<true, false>", "launches": n_launch,
+                "kernel": f"stitch_kernel<true, false, {2048 if small else 6144}>",
+                "launches": n_launch,
                 "avg_launch_us": round(avg_ms * 1e3, 2),
                 "median_step_launch_us": round(float(np.median(step_ms)) * 1e3 / len(batches), 2),
                 "algorithmic_bytes_per_launch": int(avg_bytes)}

@@ -1265,7 +1265,8 @@ size_t round16(size_t v) { return (v + 15) / 16 * 16; }
 
 // Bytes of the workspace: the look-back words and three more, per frame 516 bytes (12 past
 // 16,384 frames) for the table of bins, and per detection 344, of which the passes' arrays
-// take 152 and the rest holds suppressor lists of more than kPredSlots.
+// take 130 (166 with several frames per bin) and the rest holds suppressor lists of more than
+// kPredSlots.
 size_t workspace_bytes(int32_t n_max, int32_t n_frames) {
   const size_t n = static_cast<size_t>(n_max), f = static_cast<size_t>(n_frames);
   const size_t head = sizeof(uint64_t) * (3 + static_cast<size_t>(compact_blocks(n_max))) +
