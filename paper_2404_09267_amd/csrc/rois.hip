@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(const uint8_t *mask,
   typedef uint32_t u32x4a1 __attribute__((ext_vector_type(4), aligned(1)));
   constexpr int kRows = kTile / (kScanThreads / 64);  // per wave
   static_assert(kRows == 8, "a lane's rows are two 16-byte stores");
-  __shared__ uint32_t s_bits;
+  __shared__ uint32_t s_bits[kScanThreads / 64];  // per wave: its tiles with foreground
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t f = blockIdx.z;
   const int64_t g = (static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y) * gridDim.x +
@@ -332,7 +332,6 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(const uint8_t *mask,
   for (int64_t i = g * kScanThreads + t; i < n_clear; i += all) words[i] = 0;
   const int tx0 = blockIdx.x * kScanTiles, ty = blockIdx.y;
   const int x = tx0 * kTile + 16 * lane, y0 = ty * kTile + kRows * wave;
-  if (t == 0) s_bits = 0;
   const uint8_t *rows = mask + f * frame_px + static_cast<int64_t>(y0) * W;
   uint32_t m[kRows];  // pixels x .. x + 15 of row y0 + j as bits, then of the lane's tile
   if (W >= 16) {
@@ -364,17 +363,19 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(const uint8_t *mask,
     any |= m[j];
   }
   const uint64_t b = __ballot(any != 0 && (lane & 1) == 0);
-  if (lane == 0 && b) {  // bits 0, 2, 4, ... packed
+  if (lane == 0) {  // bits 0, 2, 4, ... packed
     uint64_t c = b;
     c = (c | c >> 1) & 0x3333333333333333ull;
     c = (c | c >> 2) & 0x0F0F0F0F0F0F0F0Full;
     c = (c | c >> 4) & 0x00FF00FF00FF00FFull;
     c = (c | c >> 8) & 0x0000FFFF0000FFFFull;
     c = c | c >> 16;
-    atomicOr(&s_bits, static_cast<uint32_t>(c));
+    s_bits[wave] = static_cast<uint32_t>(c);
   }
   __syncthreads();
-  const uint32_t bits = s_bits;
+  uint32_t bits = 0;
+#pragma unroll
+  for (int w = 0; w < kScanThreads / 64; ++w) bits |= s_bits[w];
   const int64_t band = f * T.tiles_y + ty;
   if (t == 0) tile_bits[band * T.wpb + blockIdx.x] = bits;
   const int k = lane >> 1;
