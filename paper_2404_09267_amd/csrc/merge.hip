@@ -26,8 +26,9 @@
 //  3. local:   one workgroup per bin orders a bin of several frames by frame in LDS and
 //              decides every frame of at most kLocal detections there: band bits (bands.h)
 //              name the few boxes that can meet each box, those pairs are listed and tested,
-//              and the rounds run on the suppressing ones. Larger frames, and crowded ones
-//              whose suppressing pairs do not fit, are put on a list.
+//              and the rounds run on the suppressing ones; where boxes crowd, rows of
+//              suppressor bits take the place of the list. Larger frames, and a frame that
+//              alone is too crowded for the rows, are put on a list.
 //  4. tile:    the listed frames cut into tiles of about kTileDets detections (by their
 //              top-left corners), a workgroup each: its detections' suppressors among the
 //              frame's boxes that meet the rectangle around its own.
@@ -73,7 +74,9 @@ constexpr int kLocal = 1024;          // detections decided in LDS by one workgr
 constexpr int kLocalWords = kLocal / 32;
 constexpr int kFrameHist = 4096;      // frames of a bin ordered in one pass
 constexpr int kPairs = 4096;          // pairs that bands bring together, held in LDS
-constexpr int kHits = 4096;           // and those that suppress
+// and those that suppress; or words of suppressor rows, a row of up to 23 words each for a
+// frame of 704 detections, of up to 15 each for frames of up to 448 that fill kLocal
+constexpr int kHits = 16384;
 constexpr int kTileThreads = 1024;
 constexpr int kTileDets = 256;        // detections per tile, about
 constexpr int kTilesMax = 256;        // tiles per frame
@@ -84,7 +87,7 @@ constexpr int kGridCap = 256;
 constexpr int kResolveThreads = 1024;
 constexpr int32_t kUndecided = 0, kKept = 1, kSuppressed = 2;
 
-// A frame of more than kLocal detections, or of more than kHits suppressing pairs:
+// A frame of more than kLocal detections, or one too crowded to be decided in LDS:
 // positions [lo, lo + n) of the frame order, cut
 // into g x g tiles numbered from `start` among all listed frames' tiles; tile (cx, cy) owns
 // the detections whose top-left corner has those cells. open: how many of its detections
@@ -399,12 +402,18 @@ struct LocalLds {
   uint16_t first[kLocal], end[kLocal];  // the positions of the detection's frame
   BandTable table;
   uint32_t pair[kPairs];  // position << 16 | a later position
-  uint32_t hit[kHits];    // suppressed << 16 | suppressor
+  uint32_t hit[kHits];    // suppressed << 16 | suppressor; or suppressor rows (decide_rows)
+  uint32_t kept[kLocalWords], open[kLocalWords];  // decide_rows: positions in that state
   uint8_t state[kLocal];
   uint8_t sees_kept[kLocal], sees_open[kLocal];  // this round, among its suppressors
   float ext[4][kLocal / 64];
-  int n_pairs, n_hits;
+  int n_pairs, n_hits, words;
 };
+
+// The words of 32 positions that hold o's frame.
+__device__ __forceinline__ int frame_words(const LocalLds &S, int o) {
+  return ((S.end[o] - 1) >> 5) - (S.first[o] >> 5) + 1;
+}
 
 // One pair of positions tested: listed as a hit when one suppresses the other.
 __device__ __forceinline__ void test_pair(const MergeParams &P, LocalLds &S, int i, int j) {
@@ -418,90 +427,96 @@ __device__ __forceinline__ void test_pair(const MergeParams &P, LocalLds &S, int
   }
 }
 
-// Decides n <= kLocal detections, each frame's at consecutive positions of S, by a workgroup
-// of kLocal threads, and writes their keep flags; false, with nothing written, when the
-// suppressing pairs do not fit. Called after a barrier; ends without one.
-// Testing only the pairs that bands bring together is what makes whole frames affordable
-// here (a frame of 400 boxes of cam20_4k has 80,000 pairs, of which about 2,000 share bands),
-// and listing them spreads the tests evenly: lanes that each step through their own
-// candidates wait for the one in the most crowded place (9 us of 24, frames of 400; the whole
-// pass takes 12 now). Code that runs once costs its instruction fetches, so loops stay loops.
-__device__ bool decide(const MergeParams &P, LocalLds &S, int n) {
-  const int i = threadIdx.x;
-  const bool mine = i < n, each = !(P.thr >= 0.0f);
-  if (i == 0) S.n_pairs = S.n_hits = 0;
-  S.state[i] = kKept;
-  S.sees_kept[i] = S.sees_open[i] = 0;
-  BandAxis ax, ay;
-  build_table(S.table, S.box[i], n, each, ax, ay);
-  // Each detection's pairs with later ones of its frame, in the words from its own on: `width`
-  // threads take a detection each, `parts` of them share its words.
+// The bits of positions lo .. hi in the word of positions 32 w .. 32 w + 31.
+__device__ __forceinline__ uint32_t range_bits(int w, int lo, int hi) {
+  lo = max(lo - 32 * w, 0);
+  hi = min(hi - 32 * w, 31);
+  return lo <= hi ? (0xFFFFFFFFu << lo) & (0xFFFFFFFFu >> (31 - hi)) : 0u;
+}
+
+// Decides the detections at positions [a, b) of S, whole frames, whatever their suppressing
+// pairs: each has a row of `stride` words (odd: rows in distinct banks) in which its
+// suppressors' bits are set, from the word of its frame's first position on; the rounds test
+// the rows against the kept and the undecided. Each pair is tested once: a detection takes
+// those of the half of its frame that follows it, cyclically, so that the lanes of a wave have
+// equally many (all later ones: 95 us instead of 84 below). The table of all boxes is built.
+// Called after a barrier; ends without one.
+// Pairs listed one by one overrun any list where boxes crowd, and frames sent to the tile pass
+// instead wait there for few workgroups: 1,920 frames of 100 detections, a frame's all in one
+// spot (4,700 pairs each), took 681 us so and take 84, around eight objects a frame 368 and 58;
+// 256 frames of 250 in one spot 379 and 64.
+__device__ void decide_rows(const MergeParams &P, LocalLds &S, int a, int b, int stride, bool each,
+                            BandAxis ax, BandAxis ay) {
+  const int i = threadIdx.x, lane = i & 63, wave = i >> 6, m = b - a;
+  for (int k = i; k < m * stride; k += kLocal) S.hit[k] = 0;
+  __syncthreads();
   int width = 64;
-  while (width < n) width *= 2;
-  const int o = i & (width - 1), part = i / width, parts = kLocal / width;
-  BandSpan v = {0, 0, 0, 0, false};
-  int w0 = 0, w1 = -1;
-  if (o < n) v = span_of(S.box[o], each, ax, ay);
-  if (v.named) {
-    w0 = o >> 5;
-    w1 = (S.end[o] - 1) >> 5;
-  }
-  const uint32_t tail = 0xFFFFFFFFu >> (31 - ((w1 >= 0 ? S.end[o] - 1 : 0) & 31));
-  auto word_of = [&](int w) {
-    uint32_t m = table_word(S.table, v, w);
-    if (w == w0) m &= 0xFFFFFFFEu << (o & 31);
-    return w == w1 ? m & tail : m;
-  };
-  int count = 0;
-#pragma unroll 2
-  for (int w = w0 + part; w <= w1; w += parts) count += __popc(word_of(w));
-  int at = wave_places(&S.n_pairs, count);
-  for (int w = w0 + part; w <= w1; w += parts)
-    for (uint32_t m = word_of(w); m != 0 && at < kPairs; m &= m - 1)
-      S.pair[at++] = static_cast<uint32_t>(o) << 16 | static_cast<uint32_t>(32 * w + __builtin_ctz(m));
-  __syncthreads();
-  const int n_pairs = S.n_pairs;
-  if (n_pairs <= kPairs) {
-    for (int p = i; p < n_pairs; p += kLocal) test_pair(P, S, S.pair[p] >> 16, S.pair[p] & 0xFFFFu);
-  } else {  // crowded: each lane its own
-    for (int w = w0 + part; w <= w1; w += parts)
-      for (uint32_t m = word_of(w); m != 0; m &= m - 1) test_pair(P, S, o, 32 * w + __builtin_ctz(m));
-  }
-  __syncthreads();
-  const int n_hits = S.n_hits;
-  if (n_hits > kHits) return false;  // uniform
-  for (int h = i; h < n_hits; h += kLocal) S.state[S.hit[h] >> 16] = kUndecided;
-  bool overrun = false;
-  if (n_hits > 0) {
-    __syncthreads();
-    for (int round = 0;; ++round) {
-      for (int h = i; h < n_hits; h += kLocal) {
-        const uint32_t v = S.hit[h];
-        const int s = S.state[v & 0xFFFFu];
-        if (s == kKept) S.sees_kept[v >> 16] = 1;
-        if (s == kUndecided) S.sees_open[v >> 16] = 1;
+  while (width < m) width *= 2;
+  const int o = a + (i & (width - 1)), part = i / width, parts = kLocal / width;
+  if (o < b) {
+    const float4 box = S.box[o];
+    const Aux aux = S.aux[o];
+    const float area = box_area(box);
+    const BandSpan v = span_of(box, each, ax, ay);
+    const int first = S.first[o], n = S.end[o] - first, w0 = first >> 5;
+    const int last = o + (n % 2 == 0 && o - first < n / 2 ? n / 2 : (n - 1) / 2);
+    for (int w = v.named ? w0 + part : kLocalWords; w < w0 + frame_words(S, o); w += parts) {
+      uint32_t bits = table_word(S.table, v, w) & (range_bits(w, o + 1, min(last, first + n - 1)) |
+                                                   range_bits(w, first, last - n));
+      uint32_t own = 0;
+      while (bits != 0) {  // two candidates' loads together
+        const int k0 = __builtin_ctz(bits);
+        bits &= bits - 1;
+        const int k1 = bits ? __builtin_ctz(bits) : k0;
+        bits &= bits - 1;
+        const int j0 = 32 * w + k0, j1 = 32 * w + k1;
+        const float4 q0 = S.box[j0], q1 = S.box[j1];
+        const Aux y0 = S.aux[j0], y1 = S.aux[j1];
+        auto test = [&](int k, float4 q, const Aux &y) {
+          if (!overlap_above(box, q, area, box_area(q), P.thr) || y.key == aux.key ||
+              (P.cross_only && y.roi == aux.roi))
+            return;
+          if (y.key < aux.key)
+            own |= 1u << k;
+          else
+            atomicOr(&S.hit[(32 * w + k - a) * stride + (o >> 5) - w0], 1u << (o & 31));
+        };
+        test(k0, q0, y0);
+        test(k1, q1, y1);  // the same one again changes nothing
       }
-      __syncthreads();
-      bool open = false;
-      if (mine && S.state[i] == kUndecided) {
-        if (S.sees_kept[i])
-          S.state[i] = kSuppressed;
-        else if (!S.sees_open[i])
-          S.state[i] = kKept;
-        else
-          open = true;
-        S.sees_open[i] = 0;
-      }
-      if (!__syncthreads_or(open)) break;
-      if (round > n) {  // each round decides a frame's best-ranked undecided detection
-        overrun = true;
-        break;
-      }
+      if (own != 0) atomicOr(&S.hit[(o - a) * stride + w - w0], own);
     }
   }
-  if (mine) P.keep[S.aux[i].idx] = S.state[i] == kKept ? 1 : 0;
-  if (overrun && i == 0) *P.status = 1;
-  return true;
+  __syncthreads();
+  const bool mine = i >= a && i < b;
+  int st = mine ? kUndecided : kSuppressed;
+  const int w0 = mine ? S.first[i] >> 5 : 0, words = mine ? frame_words(S, i) : 0;
+  const uint32_t *row = S.hit + (mine ? (i - a) * stride : 0);
+  for (int round = 0;; ++round) {
+    const uint64_t kept = __ballot(st == kKept), open = __ballot(st == kUndecided);
+    if (lane == 0) {
+      S.kept[2 * wave] = static_cast<uint32_t>(kept);
+      S.kept[2 * wave + 1] = static_cast<uint32_t>(kept >> 32);
+      S.open[2 * wave] = static_cast<uint32_t>(open);
+      S.open[2 * wave + 1] = static_cast<uint32_t>(open >> 32);
+    }
+    if (!__syncthreads_or(st == kUndecided)) break;
+    if (round > m) {  // each round decides a frame's best-ranked undecided detection
+      if (i == 0) *P.status = 1;
+      break;
+    }
+    if (st == kUndecided) {
+      uint32_t any_kept = 0, any_open = 0;
+      for (int w = 0; w < words; ++w) {
+        const uint32_t r = row[w];
+        any_kept |= r & S.kept[w0 + w];
+        any_open |= r & S.open[w0 + w];
+      }
+      st = any_kept ? kSuppressed : (any_open ? kUndecided : kKept);
+    }
+    __syncthreads();  // every row has been tested before the masks are rewritten
+  }
+  if (mine) P.keep[S.aux[i].idx] = st == kKept ? 1 : 0;
 }
 
 // Lists a frame for the tile and resolve passes. Called by the whole workgroup, after its
@@ -551,23 +566,118 @@ __device__ void add_large(const MergeParams &P, LocalLds &S, int lo, int n) {
   __syncthreads();
 }
 
-// The n detections of S (frame order, positions from lo on) written to the workspace and
-// their frames listed for the tile and resolve passes.
-__device__ void list_frames(const MergeParams &P, LocalLds &S, int lo, int n) {
+// The detections at positions [a, b) of S, one frame, written to the workspace (at lo + a on)
+// and listed.
+__device__ void list_frame(const MergeParams &P, LocalLds &S, int lo, int a, int b) {
   const int tid = threadIdx.x;
-  if (tid < n) {
-    P.rec[lo + tid] = Rec{S.box[tid], S.aux[tid]};
-  }
+  if (tid >= a && tid < b) P.rec[lo + tid] = Rec{S.box[tid], S.aux[tid]};
   __threadfence_block();
   __syncthreads();
-  for (int s = 0; s < n;) {  // uniform
-    const int e = S.end[s];
-    if (e - s > 1)
-      add_large(P, S, lo + s, e - s);
-    else if (tid == 0)
-      P.keep[S.aux[s].idx] = 1;  // alone in its frame
-    s = e;
+  add_large(P, S, lo + a, b - a);
+}
+
+// Decides n <= kLocal detections, each frame's at consecutive positions of S, by a workgroup
+// of kLocal threads, and writes their keep flags; a frame that alone is too crowded for the
+// rows of decide_rows is listed for the tile and resolve passes (its positions in the
+// workspace start at lo). Called after a barrier; ends without one.
+// Testing only the pairs that bands bring together is what makes whole frames affordable
+// here (a frame of 400 boxes of cam20_4k has 80,000 pairs, of which about 2,000 share bands),
+// and listing them spreads the tests evenly: lanes that each step through their own
+// candidates wait for the one in the most crowded place (9 us of 24, frames of 400; the whole
+// pass takes 12 now). Code that runs once costs its instruction fetches, so loops stay loops.
+__device__ void decide(const MergeParams &P, LocalLds &S, int lo, int n) {
+  const int i = threadIdx.x;
+  const bool mine = i < n, each = !(P.thr >= 0.0f);
+  if (i == 0) S.n_pairs = S.n_hits = S.words = 0;
+  S.state[i] = kKept;
+  S.sees_kept[i] = S.sees_open[i] = 0;
+  BandAxis ax, ay;
+  build_table(S.table, S.box[i], n, each, ax, ay);
+  // Each detection's pairs with later ones of its frame, in the words from its own on: `width`
+  // threads take a detection each, `parts` of them share its words.
+  int width = 64;
+  while (width < n) width *= 2;
+  const int o = i & (width - 1), part = i / width, parts = kLocal / width;
+  BandSpan v = {0, 0, 0, 0, false};
+  int w0 = 0, w1 = -1;
+  if (o < n) v = span_of(S.box[o], each, ax, ay);
+  if (v.named) {
+    w0 = o >> 5;
+    w1 = (S.end[o] - 1) >> 5;
   }
+  const uint32_t tail = 0xFFFFFFFFu >> (31 - ((w1 >= 0 ? S.end[o] - 1 : 0) & 31));
+  auto word_of = [&](int w) {
+    uint32_t m = table_word(S.table, v, w);
+    if (w == w0) m &= 0xFFFFFFFEu << (o & 31);
+    return w == w1 ? m & tail : m;
+  };
+  int count = 0;
+#pragma unroll 2
+  for (int w = w0 + part; w <= w1; w += parts) count += __popc(word_of(w));
+  int at = wave_places(&S.n_pairs, count);
+  for (int w = w0 + part; w <= w1; w += parts)
+    for (uint32_t m = word_of(w); m != 0 && at < kPairs; m &= m - 1)
+      S.pair[at++] = static_cast<uint32_t>(o) << 16 | static_cast<uint32_t>(32 * w + __builtin_ctz(m));
+  __syncthreads();
+  const int n_pairs = S.n_pairs;
+  if (n_pairs <= kPairs) {
+    for (int p = i; p < n_pairs; p += kLocal) test_pair(P, S, S.pair[p] >> 16, S.pair[p] & 0xFFFFu);
+  } else {  // crowded
+    if (mine) atomicMax(&S.words, frame_words(S, i));
+    __syncthreads();
+    const int stride = S.words | 1;
+    if (n * stride <= kHits) {
+      decide_rows(P, S, 0, n, stride, each, ax, ay);
+      return;
+    }
+    for (int w = w0 + part; w <= w1; w += parts)
+      for (uint32_t m = word_of(w); m != 0; m &= m - 1) test_pair(P, S, o, 32 * w + __builtin_ctz(m));
+  }
+  __syncthreads();
+  const int n_hits = S.n_hits;
+  if (n_hits > kHits) {  // frame by frame
+    for (int a = 0; a < n;) {  // uniform
+      const int b = S.end[a], stride = frame_words(S, a) | 1;
+      if ((b - a) * stride <= kHits)
+        decide_rows(P, S, a, b, stride, each, ax, ay);
+      else
+        list_frame(P, S, lo, a, b);
+      __syncthreads();
+      a = b;
+    }
+    return;
+  }
+  for (int h = i; h < n_hits; h += kLocal) S.state[S.hit[h] >> 16] = kUndecided;
+  bool overrun = false;
+  if (n_hits > 0) {
+    __syncthreads();
+    for (int round = 0;; ++round) {
+      for (int h = i; h < n_hits; h += kLocal) {
+        const uint32_t v = S.hit[h];
+        const int s = S.state[v & 0xFFFFu];
+        if (s == kKept) S.sees_kept[v >> 16] = 1;
+        if (s == kUndecided) S.sees_open[v >> 16] = 1;
+      }
+      __syncthreads();
+      bool open = false;
+      if (mine && S.state[i] == kUndecided) {
+        if (S.sees_kept[i])
+          S.state[i] = kSuppressed;
+        else if (!S.sees_open[i])
+          S.state[i] = kKept;
+        else
+          open = true;
+        S.sees_open[i] = 0;
+      }
+      if (!__syncthreads_or(open)) break;
+      if (round > n) {  // each round decides a frame's best-ranked undecided detection
+        overrun = true;
+        break;
+      }
+    }
+  }
+  if (mine) P.keep[S.aux[i].idx] = S.state[i] == kKept ? 1 : 0;
+  if (overrun && i == 0) *P.status = 1;
 }
 
 // In-place exclusive scan of hist[0 .. nf) with hist[nf] = the sum, by the workgroup.
@@ -607,7 +717,7 @@ __global__ __launch_bounds__(kLocal) void local_kernel(const MergeParams P) {
       S.end[tid] = static_cast<uint16_t>(n);
     }
     __syncthreads();
-    if (!decide(P, S, n)) add_large(P, S, lo, n);
+    decide(P, S, lo, n);
     return;
   }
   const int f0 = static_cast<int>(blockIdx.x) * P.per_bin;  // < n_frames
@@ -639,7 +749,7 @@ __global__ __launch_bounds__(kLocal) void local_kernel(const MergeParams P) {
       S.end[at] = static_cast<uint16_t>(hist[f + 1]);
     }
     __syncthreads();
-    if (!decide(P, S, n)) list_frames(P, S, lo, n);
+    decide(P, S, lo, n);
     return;
   }
   // A bin that does not fit: ordered by frame in the workspace, kFrameHist frames at a time,
@@ -688,7 +798,7 @@ __global__ __launch_bounds__(kLocal) void local_kernel(const MergeParams P) {
           S.end[tid] = static_cast<uint16_t>(hist[fr] - s);
         }
         __syncthreads();
-        if (!decide(P, S, m)) list_frames(P, S, base + s, m);
+        decide(P, S, base + s, m);
         __syncthreads();
       }
       s = hist[e - 1];

@@ -288,3 +288,63 @@ def test_compaction_limits(torch, n_max):
         if n <= n_max:
             dets, scores = random_dets(rng, max(n, 1), 9, 8)
             check(torch, dets[:n], scores, 9, 0.5, False, n_max=n_max)
+
+
+def crowded(rng, sizes):
+    """Frames of the given sizes, each frame's boxes jittered round one spot, in any order."""
+    n = sum(sizes)
+    dets, scores = random_dets(rng, n, len(sizes), 40)
+    x, y = (rng.uniform(100, 108, n).astype(np.float32) for _ in range(2))
+    w, h = (rng.uniform(56, 64, n).astype(np.float32) for _ in range(2))
+    dets["x1"], dets["y1"], dets["x2"], dets["y2"] = x, y, x + w, y + h
+    dets["frame"] = rng.permutation(np.repeat(np.arange(len(sizes), dtype=np.int32), sizes))
+    return dets, scores
+
+
+@pytest.mark.parametrize("n_frames,sizes", [
+    (3, [100, 92, 180]),             # a bin per frame; 92 boxes are the fewest pairs past the list
+    (600, [100] * 30),               # bins of three frames: one set of rows for the bin
+    (300, [448, 576, 512, 512, 500, 500]),  # rows that fit frame by frame, not together
+    (2, [704, 705]),                 # the largest frame whose rows fit, and one too large
+    (400, [1, 1023, 720, 304, 1, 1]),  # a listed frame beside others of its bin
+])
+def test_crowded_frames(torch, n_frames, sizes):
+    """Frames whose suppressing pairs overrun the list of the LDS path."""
+    rng = np.random.default_rng(sum(sizes))
+    dets, scores = crowded(rng, sizes)
+    for thr, cross in [(0.5, False), (0.5, True), (0.85, True)]:
+        check(torch, dets, scores, n_frames, thr, cross)
+
+
+def best_ms(torch, call, n=7):
+    """Fastest of n timed calls, each alone on the GPU."""
+    best = float("inf")
+    for _ in range(n + 2):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda.synchronize()
+        e0.record()
+        call()
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1))
+    return best
+
+
+def merge_ms(torch, dets, scores, n_frames):
+    d = torch.from_numpy(dets.view(np.int32).reshape(len(dets), tg.DET_WORDS).copy()).cuda()
+    count = torch.tensor([len(dets)], dtype=torch.int32, device="cuda")
+    s = torch.from_numpy(scores).cuda()
+    bufs = tg.MergeBuffers(len(dets), n_frames)
+    return best_ms(torch, lambda: tg.merge(d, count, s, n_frames, 0.5, False, bufs))
+
+
+def test_crowded_frames_cost(torch):
+    """1,920 frames of 100 detections: all of a frame's in one spot cost less than four times
+    as much as spread out (1.6 times; 12 times when crowded frames left the LDS path)."""
+    rng = np.random.default_rng(31)
+    dets, scores = crowded(rng, [100] * 1920)
+    near = merge_ms(torch, dets, scores, 1920)
+    spread, scores = random_dets(rng, len(dets), 1920, 40, span=2000.0)
+    far = merge_ms(torch, spread, scores, 1920)
+    say("crowded", near, "spread", far)
+    assert near < 4 * far
