@@ -74,8 +74,8 @@ constexpr int kLocal = 1024;          // detections decided in LDS by one workgr
 constexpr int kLocalWords = kLocal / 32;
 constexpr int kFrameHist = 4096;      // frames of a bin ordered in one pass
 constexpr int kPairs = 4096;          // pairs that bands bring together, held in LDS
-// and those that suppress; or words of suppressor rows, a row of up to 23 words each for a
-// frame of 704 detections, of up to 15 each for frames of up to 448 that fill kLocal
+// and those that suppress; or words of suppressor rows, rows of 23 words for a frame of 712
+// detections, of 15 for frames of up to 448 that fill kLocal
 constexpr int kHits = 16384;
 constexpr int kTileThreads = 1024;
 constexpr int kTileDets = 256;        // detections per tile, about

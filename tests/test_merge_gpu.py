@@ -305,7 +305,7 @@ def crowded(rng, sizes):
     (3, [100, 92, 180]),             # a bin per frame; 92 boxes are the fewest pairs past the list
     (600, [100] * 30),               # bins of three frames: one set of rows for the bin
     (300, [448, 576, 512, 512, 500, 500]),  # rows that fit frame by frame, not together
-    (2, [704, 705]),                 # the largest frame whose rows fit, and one too large
+    (2, [712, 713]),                 # the largest frame whose rows fit, and one too large
     (400, [1, 1023, 720, 304, 1, 1]),  # a listed frame beside others of its bin
 ])
 def test_crowded_frames(torch, n_frames, sizes):
