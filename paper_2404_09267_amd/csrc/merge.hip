@@ -827,6 +827,7 @@ struct TileLds {
   BandTable table;
   uint32_t pair[kPairs];       // searched << 16 | candidate
   float ext[4][kTileThreads / 64];
+  unsigned long long need[kTileThreads / 64], need_base;
   int n_own, n_cand, n_pairs, open_base;
 };
 
@@ -974,7 +975,7 @@ __device__ void search_owned(const MergeParams &P, TileLds &S, const LargeFrame 
 // there are none, else onto the frame's open list.
 __device__ void search_part(const MergeParams &P, TileLds &S, const LargeFrame &L, int k,
                             const int32_t *own, int m) {
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int np = 0;
   for (int fill = 0;; ++fill) {
     search_owned(P, S, L, own, m, fill != 0);
@@ -983,17 +984,29 @@ __device__ void search_part(const MergeParams &P, TileLds &S, const LargeFrame &
     __syncthreads();
     if (tid < m) S.at[tid] = -1;
     if (!__syncthreads_or(np > kPredSlots)) break;
-    if (tid == 0) {  // room for the longer lists, one atomic for all
-      unsigned long long need = 0;
-      for (int j = 0; j < m; ++j)
-        if (S.count[j] > kPredSlots) need += S.count[j];
-      int64_t at = static_cast<int64_t>(atomicAdd(P.ovf_used, need));
-      for (int j = 0; j < m; ++j) {
-        if (S.count[j] <= kPredSlots) continue;
-        if (at + S.count[j] <= P.ovf_cap) S.at[j] = static_cast<int>(at);
-        at += S.count[j];
-      }
+    // room for the longer lists, one atomic for all: this thread's place by a scan (64 bits,
+    // as the lists of a very large frame may overrun the area by far)
+    const unsigned long long need = np > kPredSlots ? np : 0;
+    unsigned long long incl = need;
+    for (int d = 1; d < 64; d <<= 1) {
+      const unsigned long long t = __shfl_up(incl, d);
+      if (lane >= d) incl += t;
     }
+    if (lane == 63) S.need[wave] = incl;
+    __syncthreads();
+    if (tid == 0) {
+      unsigned long long sum = 0;
+      for (int w = 0; w < kTileThreads / 64; ++w) {
+        const unsigned long long v = S.need[w];
+        S.need[w] = sum;
+        sum += v;
+      }
+      S.need_base = atomicAdd(P.ovf_used, sum);
+    }
+    __syncthreads();
+    const unsigned long long at = S.need_base + S.need[wave] + incl - need;
+    if (need > 0 && at + need <= static_cast<unsigned long long>(P.ovf_cap))
+      S.at[tid] = static_cast<int>(at);
     __syncthreads();
   }
   if (tid == 0) S.n_cand = 0;

@@ -316,6 +316,16 @@ def test_crowded_frames(torch, n_frames, sizes):
         check(torch, dets, scores, n_frames, thr, cross)
 
 
+@pytest.mark.parametrize("n", [713, 1024, 1025, 2600])
+def test_crowded_listed_frames(torch, n):
+    """Frames for the tile pass whose detections all have longer lists than are kept in place:
+    lists that fit the overflow area, and (2,600) lists far past its end."""
+    rng = np.random.default_rng(n)
+    dets, scores = crowded(rng, [n, 3, n // 2])
+    for thr, cross in [(0.5, False), (0.8, True), (0.97, False)]:
+        check(torch, dets, scores, 3, thr, cross)
+
+
 def best_ms(torch, call, n=7):
     """Fastest of n timed calls, each alone on the GPU."""
     best = float("inf")
