@@ -348,6 +348,67 @@ def merge_ms(torch, dets, scores, n_frames):
     return best_ms(torch, lambda: tg.merge(d, count, s, n_frames, 0.5, False, bufs))
 
 
+def place(rng, dets, kind):
+    """Puts the boxes of `dets` unevenly over the frame."""
+    n = len(dets)
+    x, y = rng.uniform(0, 3840, n), rng.uniform(0, 2160, n)
+    if kind == "outlier":
+        x[0] = y[0] = 1e6
+    elif kind == "half in one place":
+        hot = rng.random(n) < 0.5
+        x, y = np.where(hot, 500 + 0.08 * x, x), np.where(hot, 500 + 0.14 * y, y)
+    elif kind == "diagonal":
+        y = 0.56 * x + rng.normal(0, 20, n)
+    elif kind == "edges":  # many share a coordinate exactly
+        x, y = np.where(rng.random(n) < 0.3, 0, x), np.where(rng.random(n) < 0.3, -0.0, y)
+    elif kind == "one corner":
+        x[:], y[:] = 700, 300
+    w, h = rng.uniform(20, 60, n), rng.uniform(20, 60, n)
+    for c, v in zip(("x1", "y1", "x2", "y2"), (x, y, x + w, y + h)):
+        dets[c] = v
+    if kind == "odd corners":
+        k = rng.permutation(n)
+        for i, v in enumerate((np.nan, np.inf, -np.inf)):
+            dets["x1"][k[100 * i:100 * i + 60]] = v
+            dets["y1"][k[100 * i + 40:100 * i + 100]] = v
+        dets["x1"][k[300:320]] = dets["y1"][k[300:320]] = 3e38
+        dets["x1"][k[320:340]] = dets["y1"][k[320:340]] = -3e38
+
+
+@pytest.mark.parametrize("kind", ["outlier", "half in one place", "diagonal", "edges", "one corner",
+                                  "odd corners", "none finite"])
+def test_uneven_large_frames(torch, kind, monkeypatch):
+    """Large frames whose detections an even grid would leave to few tiles."""
+    from oracle import merge
+
+    # min and max ignore a NaN operand (tg.h); Python's, which the oracle takes, only the second
+    monkeypatch.setattr(merge, "_pmin", np.fmin)
+    monkeypatch.setattr(merge, "_pmax", np.fmax)
+    rng = np.random.default_rng(len(kind))
+    sizes = [1025, 4000, 1300, 200]
+    dets, scores = random_dets(rng, sum(sizes), len(sizes), 20)
+    place(rng, dets, kind)
+    if kind == "none finite":
+        dets["x1"], dets["y1"] = -np.inf, np.nan
+    dets["frame"] = rng.permutation(np.repeat(np.arange(len(sizes), dtype=np.int32), sizes))
+    for thr, cross in [(0.4, True), (0.6, False)]:
+        check(torch, dets, scores, len(sizes), thr, cross)
+
+
+@pytest.mark.parametrize("kind", ["outlier", "diagonal"])
+def test_uneven_large_frames_cost(torch, kind):
+    """20,000 detections in one frame: with one box far outside 1.3 times the time of a frame
+    spread out (68 times over an even grid), on a diagonal 6 times (19)."""
+    rng = np.random.default_rng(33)
+    dets, scores = random_dets(rng, 20000, 1, 40)
+    place(rng, dets, "plain")
+    plain = merge_ms(torch, dets, scores, 1)
+    place(rng, dets, kind)
+    uneven = merge_ms(torch, dets, scores, 1)
+    say("plain", plain, kind, uneven)
+    assert uneven < {"outlier": 4, "diagonal": 11}[kind] * plain
+
+
 def test_crowded_frames_cost(torch):
     """1,920 frames of 100 detections: all of a frame's in one spot cost less than four times
     as much as spread out (1.6 times; 12 times when crowded frames left the LDS path)."""
