@@ -608,10 +608,20 @@ __device__ void add_large(const MergeParams &P, LocalLds &S, int lo, int n) {
   const int cell = cell_of(sample.y, y0, g * __builtin_amdgcn_rcpf(dy), g) * g +
                    cell_of(sample.x, x0, g * __builtin_amdgcn_rcpf(dx), g);
   const int before = atomicAdd(&S.hit[cell], 1);
-  const bool even = !__syncthreads_or(before >= 2 * kLocal / (g * g) + 12) &&
+  const bool even = !__syncthreads_or(before * g * g >= 2 * kLocal + 12 * g * g) &&
                     __builtin_isfinite(dx) && __builtin_isfinite(dy);
-  const int cx = tid % g, cy = tid / g;  // this thread's tile
-  auto first_of = [&](int c) { return (c * kLocal + g - 1) / g; };  // of column c's samples
+  // (divisions by g, integer ones too, expand to fused multiply-adds: 1 / g in 16 bits)
+  const float share = __builtin_amdgcn_rcpf(g);
+  const int inv = static_cast<int>(65536.0f * share);
+  auto first_of = [&](int c) { return c < g ? c * inv * kLocal >> 16 : kLocal; };  // column c's
+  int cx = tid, cy = 0, column = 0;  // this thread's tile, and its sample's column
+  for (int c = 1; c < g; ++c) {
+    if (cx >= g) {
+      cx -= g;
+      ++cy;
+    }
+    if (tid >= first_of(c)) ++column;
+  }
   if (!even) {
     // (samples of one x in scrambled order, so that a column that takes part of them takes
     // a fair part)
@@ -622,18 +632,17 @@ __device__ void add_large(const MergeParams &P, LocalLds &S, int lo, int n) {
     __syncthreads();
     sort_keys(S.key);
     const uint64_t k = S.key[tid];
-    const int column = tid * g / kLocal;
     if (tid == first_of(column)) S.cut[column] = value_of(static_cast<uint32_t>(k >> 32));
     __syncthreads();
     S.key[tid] = static_cast<uint64_t>(column) << 32 | y_order[static_cast<uint32_t>(k) * kInverse];
     __syncthreads();
     sort_keys(S.key);
   }
-  auto cut_x = [&](int c) { return even ? x0 + c * (dx / g) : S.cut[c]; };
+  auto cut_x = [&](int c) { return even ? x0 + c * (dx * share) : S.cut[c]; };
   auto cut_y = [&](int r) {
-    if (even) return y0 + r * (dy / g);
+    if (even) return y0 + r * (dy * share);
     const int a = first_of(cx), b = first_of(cx + 1);
-    return value_of(static_cast<uint32_t>(S.key[a + (b - a) * r / g]));
+    return value_of(static_cast<uint32_t>(S.key[a + ((b - a) * r * inv >> 16)]));
   };
   if (tid < g * g) {
     TileRect R = {-inf, -inf, __builtin_nanf(""), __builtin_nanf("")};
