@@ -409,6 +409,23 @@ def test_uneven_large_frames_cost(torch, kind):
     assert uneven < {"outlier": 4, "diagonal": 11}[kind] * plain
 
 
+def test_tile_sizes(torch):
+    """450,000 detections in frames of 1,500 and 6,000 take tiles of 439 instead of 256. The
+    oracle checks three frames on their own, as the others do not affect them."""
+    from oracle import merge
+
+    rng = np.random.default_rng(35)
+    sizes = [1500] * 60 + [6000] * 60
+    dets, scores = random_dets(rng, sum(sizes), len(sizes), 20, span=1500.0)
+    dets["frame"] = rng.permutation(np.repeat(np.arange(len(sizes), dtype=np.int32), sizes))
+    keep, kept, n_kept = run_gpu(torch, dets, scores, len(sizes), 0.5, True)
+    sub = np.nonzero(np.isin(dets["frame"], [5, 61, 119]))[0]
+    want, _ = merge.merge(dets[sub], scores, len(sizes), 0.5, True)
+    np.testing.assert_array_equal(keep[sub], want.astype(np.int32))
+    assert n_kept == int(keep.sum())
+    np.testing.assert_array_equal(kept.view(np.int32), dets[keep == 1].view(np.int32))
+
+
 def test_crowded_frames_cost(torch):
     """1,920 frames of 100 detections: all of a frame's in one spot cost less than four times
     as much as spread out (1.6 times; 12 times when crowded frames left the LDS path)."""
