@@ -100,15 +100,19 @@ __device__ __forceinline__ void segment_of(const UnstitchParams &P, int c, int &
 // The placed rectangle of the RoI at plan position k for a box of canvas c, and order[k]; a
 // position that holds no RoI of that canvas gets a rectangle no box meets.
 __device__ __forceinline__ float4 patch_at(const UnstitchParams &P, int k, int c, int &id) {
+  const float inf = __builtin_inff();
+  float4 r = make_float4(inf, inf, -inf, -inf);
   id = P.order[k];
   if (id >= 0 && id < P.n_rois) {
     const tg_place pl = P.place[id];
     const tg_roi ro = P.rois[id];
-    if (pl.canvas == c)
-      return make_float4(float(pl.x), float(pl.y), float(pl.x + ro.w), float(pl.y + ro.h));
+    const bool here = pl.canvas == c;  // (a branch would load the RoI only after the placement)
+    r.x = here ? float(pl.x) : inf;
+    r.y = here ? float(pl.y) : inf;
+    r.z = here ? float(pl.x + ro.w) : -inf;
+    r.w = here ? float(pl.y + ro.h) : -inf;
   }
-  const float inf = __builtin_inff();
-  return make_float4(inf, inf, -inf, -inf);
+  return r;
 }
 
 __device__ __forceinline__ bool holds(float4 r, float cx, float cy) {
