@@ -7,12 +7,14 @@
 // patch's frame offset minus its canvas offset.
 //
 // Every size is bound by latency (launches and chains of dependent loads), not by bytes:
-// 24 bytes in and up to 32 out per box. Launches on the caller's stream, by size:
-//  - up to kSmallBoxes boxes and kSmallRois RoIs: one workgroup, one launch (small_kernel;
-//    cam1_1080p, 200 boxes: 6.2 us in two launches, 4.4 in one).
-//  - up to kCountBoxes boxes that test few patches in all: assign (LPB lanes per box test
+// 24 bytes in and up to 32 out per box. Launches on the caller's stream, by size
+// (the rules and where their lines lie: unstitch_route.h):
+//  - few boxes on a small plan: one workgroup, one launch (small_kernel; cam1_1080p, 200
+//    boxes: 6.2 us in two launches, 4.4 in one).
+//  - boxes that test few patches in all, or no room for a layout: assign (LPB lanes per box test
 //    the box canvas's patches, gathered from the plan) and emit, whose workgroups count the
-//    kept boxes before their own by reading roi_of_box.
+//    kept boxes before their own by reading roi_of_box; many boxes are counted by a pass in
+//    between.
 //  - more: prep, assign, emit. prep lays out each canvas's patches: one rectangle per plan
 //    position and, for canvases of at least kBandPatches patches, a bit per patch and band
 //    -- the canvas's extent cut into kBands columns and kBands rows, band i's bits naming
@@ -29,6 +31,7 @@
 
 #include "bands.h"
 #include "tg.h"
+#include "unstitch_route.h"
 
 // Built with -ffp-contract=off: every binary32 operation here is rounded on its own (no
 // multiply-add fusion), so decisions taken in floating point match any plain IEEE
@@ -39,24 +42,19 @@ namespace {
 using tg_detail::band_axis;
 using tg_detail::band_of;
 using tg_detail::BandAxis;
+using tg_detail::kCountBlock;
+using tg_detail::kSmallBoxes;
 using tg_detail::transpose32;
+using tg_detail::unstitch_route;
+using tg_detail::UnstitchRoute;
 using tg_detail::wave_min;
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr int kCountBlock = 128;  // boxes per count (a byte of workspace each)
-// Calls whose boxes test at least this many patches in all read the plan through prep's
-// rectangles and bands (one launch more); smaller ones gather it directly.
-// (cam20_4k, 10,000 boxes on canvases of 31 patches: gathered 8.8 us, laid out 13; 50,000
-// boxes on canvases of 302, overlap rule: 74.8 us gathered by 64 lanes per box from 24-byte
-// records before, 26.5 laid out; 200,000 boxes on canvases of 29: 39.0 before, 29.4.)
-constexpr int64_t kRecordsMinTests = int64_t(1) << 21;
-constexpr int kCountBoxes = 65536;  // up to this many, emit may count the boxes before its own
 constexpr int kBandThreads = 1024;  // assign over prep's layout
-constexpr int kSmallBoxes = 256;    // one workgroup
-constexpr int kSmallLanes = 4;      // lanes per box there
+constexpr int kSmallLanes = 4;      // lanes per box in small_kernel
 constexpr int kSmallThreads = kSmallBoxes * kSmallLanes;
-constexpr int kSmallRois = 128;     // largest plan it takes (a canvas may hold all of it)
+constexpr int kCheckGroups = 1;     // workgroups of prep that check canvas_begin
 constexpr int kBands = 15;          // per axis: 30 bits of a patch's mask
 constexpr int kBandWords = 4;       // a canvas's header: band origin and scale per axis
 // Fewest patches whose bands fit their canvas's 8 bytes per patch:
@@ -75,7 +73,7 @@ struct UnstitchParams {
   int32_t *roi_of_box;
   tg_det *dets;
   int32_t *n_out;
-  int32_t *gather;  // set by prep when the assign has to gather the plan (see prep_kernel)
+  uint8_t *gather;  // set by prep when the assign has to gather the plan
   uint8_t *counts;  // 4-byte aligned: kept boxes of each kCountBlock boxes
   float4 *rect;    // per plan position k: the placed rectangle of RoI order[k] (prep) ...
   int32_t *bands;  // ... and the canvas's header and band words, from word 2 k_lo on
@@ -190,31 +188,32 @@ __global__ __launch_bounds__(kThreads) void assign_kernel(const UnstitchParams P
 
 // Lays out every canvas's patches (kWavesPer waves a canvas): its rectangles (positions
 // that hold no RoI of the canvas: one that no box meets) and, from kBandPatches patches on,
-// its header and band words. Workgroup 0 checks that canvas_begin cuts the plan into consecutive segments; where it does not, two
-// canvases may share positions, whose rectangles are then not those of one canvas, and the
-// assign gathers from the plan instead (as it does without room for the layout).
+// its header and band words. Workgroup 0 checks that canvas_begin cuts the
+// plan into consecutive segments; where it does not, two canvases may share positions, whose
+// rectangles are then not those of one canvas, and the assign gathers from the plan instead.
 template <int kWavesPer>
 __global__ __launch_bounds__(kThreads) void prep_kernel(const UnstitchParams P) {
   __shared__ float s_ext[4][kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (blockIdx.x == 0) {
-    int bad = P.rect == nullptr;
-    if (P.rect) {
-      constexpr int kPer = 8;  // canvases per thread and step, their words loaded together
-      for (int c0 = kPer * tid; c0 < P.n_canvases; c0 += kPer * kThreads) {
-        int v[kPer + 1];
+  if (blockIdx.x < kCheckGroups) {
+    int bad = 0;
+    constexpr int kPer = 8;  // canvases per thread and step, their words loaded together
+    for (int64_t c0 = kPer * (int64_t(blockIdx.x) * kThreads + tid); c0 < P.n_canvases;
+         c0 += kPer * kThreads * kCheckGroups) {
+      int v[kPer + 1];
 #pragma unroll
-        for (int j = 0; j <= kPer; ++j) v[j] = P.canvas_begin[min(c0 + j, P.n_canvases)];
+      for (int j = 0; j <= kPer; ++j)
+        v[j] = P.canvas_begin[min(c0 + j, static_cast<int64_t>(P.n_canvases))];
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) bad |= v[j] < 0 || v[j + 1] < v[j] || v[j + 1] > P.n_rois;
-      }
+      for (int j = 0; j < kPer; ++j) bad |= v[j] < 0 || v[j + 1] < v[j] || v[j + 1] > P.n_rois;
     }
     bad = __syncthreads_or(bad);
-    if (tid == 0) *P.gather = bad;
+    if (tid == 0) P.gather[blockIdx.x] = static_cast<uint8_t>(bad != 0);
     return;
   }
-  const int c = (static_cast<int>(blockIdx.x) - 1) * (kWaves / kWavesPer) + wave / kWavesPer;
-  if (kWavesPer == 1 && c >= P.n_canvases) return;
+  const int64_t c64 = (int64_t(blockIdx.x) - kCheckGroups) * (kWaves / kWavesPer) + wave / kWavesPer;
+  if (kWavesPer == 1 && c64 >= P.n_canvases) return;
+  const int c = static_cast<int>(c64);
   const int wv = wave % kWavesPer;
   int k_lo, k_hi;
   segment_of(P, c, k_lo, k_hi);
@@ -275,17 +274,64 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const UnstitchParams P) 
   }
 }
 
-// The assign over prep's layout: L lanes per box, each taking every L-th word of 32 patches
-// (every L-th patch of canvases without bands). The pass is a chain of dependent loads
-// (canvas, segment, header, bands, rectangles), each of which meets a line per box, so
-// neighbouring words share a load and a patch's RoI id is read only when it decides. The
-// workgroup's kept boxes are counted by kCountBlock boxes and stored, with no atomic: adding
-// them to shared words queued at 9 ns an add (50,000 boxes in 3,125 workgroups: 28 us).
+// Counts the kept boxes of a workgroup of kBandThreads threads, L lanes per box, by kCountBlock
+// boxes and stores the counts, with no atomic: adding them to shared words queued at 9 ns an
+// add (50,000 boxes in 3,125 workgroups: 28 us). `kept`: a kept box's first lane.
 template <int L>
-__global__ __launch_bounds__(kBandThreads) void assign_bands_kernel(const UnstitchParams P) {
+__device__ __forceinline__ void store_counts(const UnstitchParams &P, bool kept) {
   constexpr int kBlocks = kBandThreads / L / kCountBlock;  // counted blocks per workgroup
   static_assert(kBlocks >= 1, "a workgroup holds whole counted blocks");
   __shared__ int s_kept[kBandThreads / 64];
+  const int tid = threadIdx.x;
+  const uint64_t m = __ballot(kept);
+  if ((tid & 63) == 0) s_kept[tid >> 6] = __popcll(m);
+  __syncthreads();
+  if (tid < kBlocks) {
+    int sum = 0;
+#pragma unroll
+    for (int w = 0; w < 2 * L; ++w) sum += s_kept[2 * L * tid + w];  // kCountBlock boxes' waves
+    const uint32_t blk = blockIdx.x * kBlocks + tid;
+    if (blk * kCountBlock < static_cast<uint32_t>(P.n_boxes))
+      P.counts[blk] = static_cast<uint8_t>(sum);
+  }
+}
+
+// assign_kernel with few lanes per box and the counts (many boxes). A plan's canvases may hold
+// many more patches than they do on average (the last ones of a plan packed by height): a box
+// whose canvas would take more than kLongRounds rounds is left to the whole wave.
+template <int L>
+__global__ __launch_bounds__(kBandThreads) void assign_count_kernel(const UnstitchParams P) {
+  constexpr int kLongRounds = 32;
+  const int lane = threadIdx.x & 63, sl = threadIdx.x % L;
+  const uint32_t b = blockIdx.x * (kBandThreads / L) + threadIdx.x / L;
+  const bool in = b < static_cast<uint32_t>(P.n_boxes);  // whole segments
+  tg_box box = {};
+  int c = -1, k_lo = 0, k_hi = 0, roi = -1;
+  if (in) {
+    box = P.boxes[b];
+    c = P.box_canvas[b];
+    segment_of(P, c, k_lo, k_hi);
+  }
+  const bool is_long = k_hi - k_lo > kLongRounds * L;
+  if (!is_long) roi = find_direct<L>(P, box, c, k_lo, k_hi, sl);
+  for (uint64_t m = __ballot(is_long && sl == 0); m != 0; m &= m - 1) {
+    const int from = __builtin_ctzll(m);
+    const tg_box long_box = {__shfl(box.x1, from), __shfl(box.y1, from), __shfl(box.x2, from),
+                             __shfl(box.y2, from)};
+    const int r = find_direct<64>(P, long_box, __shfl(c, from), __shfl(k_lo, from),
+                                  __shfl(k_hi, from), lane);
+    if (lane / L == from / L) roi = r;
+  }
+  if (in && sl == 0) P.roi_of_box[b] = roi;
+  store_counts<L>(P, in && sl == 0 && roi >= 0);
+}
+
+// The assign over prep's layout: L lanes per box, each taking every L-th word of 32 patches
+// (every L-th patch of canvases without bands). The pass is a chain of dependent loads
+// (canvas, segment, header, bands, rectangles), each of which meets a line per box, so
+// neighbouring words share a load and a patch's RoI id is read only when it decides.
+template <int L>
+__global__ __launch_bounds__(kBandThreads) void assign_bands_kernel(const UnstitchParams P) {
   const int tid = threadIdx.x, sl = tid % L;
   const uint32_t b = blockIdx.x * (kBandThreads / L) + tid / L;
   const bool gather = *P.gather != 0;  // uniform
@@ -387,16 +433,7 @@ __global__ __launch_bounds__(kBandThreads) void assign_bands_kernel(const Unstit
     }
     if (sl == 0) P.roi_of_box[b] = roi;
   }
-  const uint64_t kept = __ballot(sl == 0 && roi >= 0);
-  if ((tid & 63) == 0) s_kept[tid >> 6] = __popcll(kept);
-  __syncthreads();
-  if (tid < kBlocks) {
-    int sum = 0;
-#pragma unroll
-    for (int w = 0; w < 2 * L; ++w) sum += s_kept[2 * L * tid + w];  // kCountBlock boxes' waves
-    const uint32_t blk = blockIdx.x * kBlocks + tid;
-    if (blk * kCountBlock < static_cast<uint32_t>(P.n_boxes)) P.counts[blk] = static_cast<uint8_t>(sum);
-  }
+  store_counts<L>(P, sl == 0 && roi >= 0);
 }
 
 // The detection of kept box b (patch roi).
@@ -426,18 +463,31 @@ __device__ __forceinline__ tg_det make_det(const UnstitchParams &P, int32_t b, i
   return d;
 }
 
+// The kept boxes of each kCountBlock boxes, for an assign that gathers and does not count: a
+// wave per kCountBlock boxes.
+__global__ __launch_bounds__(kThreads) void count_kernel(const UnstitchParams P) {
+  static_assert(kCountBlock == 128, "two boxes per lane");
+  const uint32_t blk = blockIdx.x * kWaves + (threadIdx.x >> 6), n = P.n_boxes;
+  const uint32_t b = blk * kCountBlock + (threadIdx.x & 63);
+  const uint64_t m0 = __ballot(b < n && P.roi_of_box[b] >= 0);
+  const uint64_t m1 = __ballot(b + 64 < n && P.roi_of_box[b + 64] >= 0);
+  if ((threadIdx.x & 63) == 0 && blk * kCountBlock < n)
+    P.counts[blk] = static_cast<uint8_t>(__popcll(m0) + __popcll(m1));
+}
+
 // Writes the kept boxes of 256 consecutive boxes, one per thread, in increasing box order: a
-// stable compaction. The workgroup's first position is the kept boxes before its own: with
-// kCounts the assign's counts, else (few boxes) all earlier box ids -- read again by every workgroup, which costs less
-// than a ticket and a look-back over the earlier workgroups (10,000 boxes: 6.6 -> 4 us).
-template <bool kCounts>
+// stable compaction. The workgroup's first position is the kept boxes before its own:
+// kOwnCounts all earlier box ids, read again by every workgroup; kSumCounts the sum of the
+// earlier counts.
+enum EmitCounts { kOwnCounts, kSumCounts };
+template <EmitCounts kMode>
 __global__ __launch_bounds__(kThreads) void emit_kernel(const UnstitchParams P) {
   __shared__ int s_before[kWaves], s_wave[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint32_t b0 = blockIdx.x * kThreads, b = b0 + tid;
   const int roi = b < static_cast<uint32_t>(P.n_boxes) ? P.roi_of_box[b] : -1;
   int before = 0;
-  if (kCounts) {  // the counts before b0 (an even number of them), four at a time
+  if (kMode == kSumCounts) {  // the counts before b0 (an even number), four at a time
     const uint32_t n = b0 / kCountBlock;
 #pragma unroll 4
     for (uint32_t i = 4 * tid; i < n; i += 4 * kThreads) {
@@ -630,53 +680,52 @@ int launch(const tg_unstitch_args *a, void *words, void *records, hipStream_t s)
   P.roi_of_box = a->roi_of_box;
   P.dets = a->dets;
   P.n_out = a->n_out;
-  P.gather = static_cast<int32_t *>(words);
+  P.gather = static_cast<uint8_t *>(words);
   P.counts = static_cast<uint8_t *>(words) + 8;
-  const int64_t per_canvas = a->n_canvases > 0 ? (int64_t(a->n_rois) + a->n_canvases - 1) /
-                                                     a->n_canvases
-                                               : 1;
-  if (a->n_boxes <= kSmallBoxes && a->n_rois <= kSmallRois) {
+  const UnstitchRoute R =
+      unstitch_route(a->n_boxes, a->n_rois, a->n_canvases, records != nullptr);
+  const auto groups = [](int64_t work, int64_t per) {
+    return dim3(static_cast<uint32_t>((work + per - 1) / per));
+  };
+  if (R.small) {
     hipLaunchKernelGGL(small_kernel, dim3(1), dim3(kSmallThreads), 0, s, P);
     return hipGetLastError() == hipSuccess ? TG_OK : TG_E_HIP;
   }
-  const bool laid_out = int64_t(a->n_boxes) * per_canvas >= kRecordsMinTests ||
-                        a->n_boxes > kCountBoxes;
-  const bool room = records && a->n_rois > 0 && a->n_canvases > 0;
-  P.rect = laid_out && room ? static_cast<float4 *>(records) : nullptr;
-  P.bands = P.rect ? reinterpret_cast<int32_t *>(P.rect + a->n_rois) : nullptr;
-  if (laid_out) {
-    // workgroup 0 checks canvas_begin, the others lay out the canvases
-    const uint32_t canvases = P.rect ? static_cast<uint32_t>(a->n_canvases) : 0;
+  if (R.laid_out) {
+    P.rect = static_cast<float4 *>(records);
+    P.bands = reinterpret_cast<int32_t *>(P.rect + a->n_rois);
+    const int64_t per_canvas = (int64_t(a->n_rois) + a->n_canvases - 1) / a->n_canvases;
     if (per_canvas > 64)
-      hipLaunchKernelGGL(prep_kernel<kWaves>, dim3(1 + canvases), dim3(kThreads), 0, s, P);
+      hipLaunchKernelGGL(prep_kernel<kWaves>, groups(int64_t(a->n_canvases) + kCheckGroups, 1),
+                         dim3(kThreads), 0, s, P);
     else
-      hipLaunchKernelGGL(prep_kernel<1>, dim3(1 + (canvases + kWaves - 1) / kWaves),
+      hipLaunchKernelGGL(prep_kernel<1>, groups(int64_t(a->n_canvases) + kCheckGroups * kWaves, kWaves),
                          dim3(kThreads), 0, s, P);
     if (hipGetLastError() != hipSuccess) return TG_E_HIP;
-    // (of 1, 2 and 4 lanes per box on canvases of about 30 patches 2 are fastest, of 4 and 8
-    // on canvases of hundreds 8)
-    const int64_t words32 = (per_canvas + 31) / 32;
-    if (P.rect && words32 <= 2)
+    if (R.lanes == 2)
       launch_bands<2>(a->n_boxes, s, P);
     else
       launch_bands<8>(a->n_boxes, s, P);
+  } else if (R.lanes == 8) {
+    hipLaunchKernelGGL(assign_count_kernel<8>, groups(a->n_boxes, kBandThreads / 8),
+                       dim3(kBandThreads), 0, s, P);
   } else {
-    // Lanes per box: a round is two dependent gathers, so 64 lanes, for one round to settle
-    // a box, unless canvases hold at most 16 patches (cam20_4k, 32 patches per canvas, with
-    // the emit of then: 11.6 us with 64 lanes, 12.0 with 32, 14.9 with 16).
-    const int64_t per_block = per_canvas <= 16 ? kThreads / 16 : kThreads / 64;
-    const dim3 grid(static_cast<uint32_t>((int64_t(a->n_boxes) + per_block - 1) / per_block));
-    if (per_canvas <= 16)
+    const dim3 grid = groups(a->n_boxes, kThreads / R.lanes);
+    if (R.lanes == 16)
       hipLaunchKernelGGL(assign_kernel<16>, grid, dim3(kThreads), 0, s, P);
     else
       hipLaunchKernelGGL(assign_kernel<64>, grid, dim3(kThreads), 0, s, P);
+    if (hipGetLastError() != hipSuccess) return TG_E_HIP;
+    if (R.counted)
+      hipLaunchKernelGGL(count_kernel, groups(a->n_boxes, kCountBlock * kWaves), dim3(kThreads), 0,
+                         s, P);
   }
   if (hipGetLastError() != hipSuccess) return TG_E_HIP;
-  const dim3 grid(static_cast<uint32_t>((int64_t(a->n_boxes) + kThreads - 1) / kThreads));
-  if (laid_out)
-    hipLaunchKernelGGL(emit_kernel<true>, grid, dim3(kThreads), 0, s, P);
+  const dim3 grid = groups(a->n_boxes, kThreads);
+  if (R.counted)
+    hipLaunchKernelGGL(emit_kernel<kSumCounts>, grid, dim3(kThreads), 0, s, P);
   else
-    hipLaunchKernelGGL(emit_kernel<false>, grid, dim3(kThreads), 0, s, P);
+    hipLaunchKernelGGL(emit_kernel<kOwnCounts>, grid, dim3(kThreads), 0, s, P);
   return hipGetLastError() == hipSuccess ? TG_OK : TG_E_HIP;
 }
 

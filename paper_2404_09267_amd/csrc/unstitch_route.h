@@ -1,0 +1,63 @@
+// How one tg_unstitch call runs, by its sizes (host code without HIP, so that the rules can be
+// tested on their own).
+#ifndef TG_UNSTITCH_ROUTE_H
+#define TG_UNSTITCH_ROUTE_H
+
+#include <cstdint>
+
+namespace tg_detail {
+
+// One workgroup, one launch: up to this many boxes, on a plan of up to this many RoIs (a canvas
+// may hold them all).
+constexpr int32_t kSmallBoxes = 256, kSmallRois = 128;
+
+// Calls whose boxes test at least this many patches in all read the plan through a layout
+// (10,000 boxes on canvases of 31 patches: gathered 10.6 us, laid out 13.2; 50,000 boxes on
+// canvases of 302, overlap rule: 74.8 us gathered by 64 lanes per box from 24-byte records
+// before, 26.5 laid out), as do calls of more than kOwnCountBoxes boxes.
+constexpr int64_t kLaidOutTests = int64_t(1) << 21;
+
+// An emit workgroup counts the kept boxes before its own by itself up to here when the plan was
+// gathered, ...
+constexpr int32_t kOwnCountBoxes = 65536;
+// ... and sums the counts of kCountBlock boxes each past it.
+constexpr int32_t kCountBlock = 128;  // boxes per count (a byte of workspace each)
+
+struct UnstitchRoute {
+  bool small;     // small_kernel alone
+  bool laid_out;  // prep, and the assign over its layout; else the assign gathers the plan
+  int lanes;      // per box in the assign
+  bool counted;   // an emit workgroup finds the kept boxes before its own in the counts, else
+                  // in roi_of_box
+};
+
+// `room`: there is scratch for the layout.
+inline UnstitchRoute unstitch_route(int32_t n_boxes, int32_t n_rois, int32_t n_canvases,
+                                    bool room) {
+  UnstitchRoute r = {};
+  const int64_t per_canvas =
+      n_canvases > 0 ? (int64_t(n_rois) + n_canvases - 1) / n_canvases : 1;
+  r.small = n_boxes <= kSmallBoxes && n_rois <= kSmallRois;
+  if (r.small) return r;
+  r.laid_out = room && n_rois > 0 && n_canvases > 0 &&
+               (n_boxes * per_canvas >= kLaidOutTests || n_boxes > kOwnCountBoxes);
+  r.counted = r.laid_out || n_boxes > kOwnCountBoxes;
+  // Laid out: a 32-patch word per lane (of 1, 2 and 4 lanes per box on canvases of about 30
+  // patches 2 are fastest, of 4 and 8 on canvases of hundreds 8). Gathered: a round is two
+  // dependent gathers, so 64 lanes, for one round to settle a box, unless canvases hold at most
+  // 16 patches (10,000 boxes on canvases of 32: 11.6 us with 64 lanes, 12.0 with 32, 14.9 with
+  // 16); many boxes fill the chip with 8, which can count them too (400,000 boxes on canvases of
+  // 30: 113 us with 8 lanes, 161 with 64 and a pass that counts; of 300, 100,000 boxes: 227 and
+  // 211).
+  if (r.laid_out)
+    r.lanes = per_canvas <= 64 ? 2 : 8;
+  else if (r.counted && per_canvas <= 64)
+    r.lanes = 8;
+  else
+    r.lanes = per_canvas <= 16 ? 16 : 64;
+  return r;
+}
+
+}  // namespace tg_detail
+
+#endif  // TG_UNSTITCH_ROUTE_H

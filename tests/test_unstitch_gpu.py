@@ -290,3 +290,21 @@ def test_few_boxes(torch, n):
         for rule in (0, 1):
             say("few", n, n_rois, rule)
             check(torch, boxes, canv, rois, plan, 1, rule=rule)
+
+
+@pytest.mark.parametrize("n", [16384, 16385, 40000, 120000])
+@pytest.mark.parametrize("rule", [0, 1])
+def test_uneven_canvases(torch, n, rule):
+    """Canvases of 257, 700 and 2,000 patches among thousands of one to four: the boxes of long
+    ones are assigned by whole waves where the others take few lanes, and every path agrees."""
+    sizes = [3, 2000, 1, 257, 256, 0, 700] + [1, 4, 2] * 1000
+    rois, plan = _grid_plan(sizes, 6, 300)
+    rng = np.random.default_rng(n + rule)
+    c, s = rng.uniform(-5, 305, (n, 2)), rng.uniform(0, 12, (n, 2))
+    boxes = np.concatenate([c - s / 2, c + s / 2], 1).astype(np.float32)
+    canv = rng.integers(-1, len(sizes) + 1, n).astype(np.int32)
+    canv[:n // 4] = rng.integers(0, 8, n // 4)
+    boxes[:50, 0] = np.nan
+    perm = rng.permutation(n)
+    say("uneven canvases", n, rule)
+    check(torch, boxes[perm], canv[perm], rois, plan, 1, rule=rule)

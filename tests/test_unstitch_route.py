@@ -1,0 +1,44 @@
+"""Which passes tg_unstitch takes by the sizes of a call (csrc/unstitch_route.h), on the CPU."""
+import os
+import shutil
+import subprocess
+from collections import namedtuple
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2404_09267_amd", "csrc")
+Route = namedtuple("Route", "small laid_out lanes counted")
+I32 = 2 ** 31 - 1
+OWN = 65536  # most boxes that emit workgroups count by themselves
+
+
+@pytest.fixture(scope="module")
+def route(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not found")
+    exe = str(tmp_path_factory.mktemp("route") / "route")
+    subprocess.run([gxx, "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined",
+                    "-fno-sanitize-recover=undefined", "-I", CSRC,
+                    os.path.join(HERE, "route_harness.cpp"), "-o", exe], check=True)
+
+    def run(boxes, rois, canvases, room=True):
+        out = subprocess.run([exe], input=f"{boxes} {rois} {canvases} {int(room)}\n",
+                             capture_output=True, text=True, check=True).stdout
+        return Route(*map(int, out.split()))
+
+    return run
+
+
+def test_no_layout_without_room(route):
+    """Without scratch for the layout (or without a plan) the plan is gathered as in calls that
+    never lay it out: where canvases hold hundreds of patches by 64 lanes per box."""
+    for boxes in (10000, 100000, 1 << 24, I32):
+        counted = boxes > OWN
+        for rois, canvases, lanes in [(150000, 5000, 8 if counted else 64), (150000, 500, 64),
+                                      (150000, 150000, 8 if counted else 16)]:
+            r = route(boxes, rois, canvases, room=False)
+            assert (r.laid_out, r.lanes, r.counted) == (0, lanes, counted)
+    assert not route(I32, 0, 5).laid_out
+    assert not route(I32, 0, 0).laid_out

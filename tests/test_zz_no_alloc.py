@@ -91,6 +91,28 @@ def test_noalloc_plan_beyond_record_area(torch):
         assert got[1].tobytes() == want[1].tobytes()
 
 
+@pytest.mark.parametrize("rule", [0, 1])
+def test_noalloc_many_boxes_beyond_record_area(torch, rule):
+    """Such plans with as many boxes as are counted by the emit itself, by a pass of their
+    own, and one more than are summed."""
+    rng = np.random.default_rng(15 + rule)
+    n_rois = tg.UNSTITCH_NOALLOC_MAX_ROIS + 9000
+    rois = W.random_rois(rng, n_rois, 8, 3840, 2160, 4, 12, 12)
+    plan = tg.plan_pack(rois, 160, 160, 3840, 2160, 8, tg.SHELF_FFDH)
+    dplan = tg.DevicePlan(rois, plan)
+    n = (1 << 21) + 1
+    c = rng.uniform(0, 170, (n, 2))
+    boxes_d = torch.from_numpy(np.concatenate([c - 3, c + 3], 1).astype(np.float32)).cuda()
+    canv_d = torch.from_numpy(rng.integers(-1, plan.n_canvases + 1, n).astype(np.int32)).cuda()
+    for m in (n, 100_000, 65_537, 65_536, 16_385, 16_384, 300):
+        say("noalloc, many boxes, large plan", m, plan.n_canvases, rule)
+        want = _run(torch, dplan, boxes_d[:m], canv_d[:m], rule, noalloc=False)
+        got = _run(torch, dplan, boxes_d[:m], canv_d[:m], rule, noalloc=True)
+        np.testing.assert_array_equal(got[0], want[0])
+        assert got[2] == want[2] and got[2] > 0
+        assert got[1].tobytes() == want[1].tobytes()
+
+
 def test_noalloc_limits(torch):
     dplan, boxes_d, canv_d = _case(torch, 13, 10, 0)
     bufs = tg.UnstitchBuffers(10, dplan.n_rois)
