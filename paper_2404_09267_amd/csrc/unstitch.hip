@@ -54,7 +54,7 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kBandThreads = 1024;  // assign over prep's layout
 constexpr int kSmallLanes = 4;      // lanes per box in small_kernel
 constexpr int kSmallThreads = kSmallBoxes * kSmallLanes;
-constexpr int kCheckGroups = 1;     // workgroups of prep that check canvas_begin
+constexpr int kCheckGroups = 8;     // workgroups of prep that check canvas_begin, a byte each
 constexpr int kBands = 15;          // per axis: 30 bits of a patch's mask
 constexpr int kBandWords = 4;       // a canvas's header: band origin and scale per axis
 // Fewest patches whose bands fit their canvas's 8 bytes per patch:
@@ -73,7 +73,7 @@ struct UnstitchParams {
   int32_t *roi_of_box;
   tg_det *dets;
   int32_t *n_out;
-  uint8_t *gather;  // set by prep when the assign has to gather the plan
+  uint8_t *gather;  // kCheckGroups verdicts of prep: any set, and the assign gathers the plan
   uint8_t *counts;  // 4-byte aligned: kept boxes of each kCountBlock boxes
   float4 *rect;    // per plan position k: the placed rectangle of RoI order[k] (prep) ...
   int32_t *bands;  // ... and the canvas's header and band words, from word 2 k_lo on
@@ -188,9 +188,10 @@ __global__ __launch_bounds__(kThreads) void assign_kernel(const UnstitchParams P
 
 // Lays out every canvas's patches (kWavesPer waves a canvas): its rectangles (positions
 // that hold no RoI of the canvas: one that no box meets) and, from kBandPatches patches on,
-// its header and band words. Workgroup 0 checks that canvas_begin cuts the
+// its header and band words. The first kCheckGroups workgroups check that canvas_begin cuts the
 // plan into consecutive segments; where it does not, two canvases may share positions, whose
 // rectangles are then not those of one canvas, and the assign gathers from the plan instead.
+// (One workgroup alone for the check took 1,000 us for 2,000,000 canvases.)
 template <int kWavesPer>
 __global__ __launch_bounds__(kThreads) void prep_kernel(const UnstitchParams P) {
   __shared__ float s_ext[4][kWaves];
@@ -334,7 +335,7 @@ template <int L>
 __global__ __launch_bounds__(kBandThreads) void assign_bands_kernel(const UnstitchParams P) {
   const int tid = threadIdx.x, sl = tid % L;
   const uint32_t b = blockIdx.x * (kBandThreads / L) + tid / L;
-  const bool gather = *P.gather != 0;  // uniform
+  const bool gather = *reinterpret_cast<const uint64_t *>(P.gather) != 0;  // uniform
   int roi = -1;
   if (b < static_cast<uint32_t>(P.n_boxes)) {  // whole segments
     const tg_box box = P.boxes[b];

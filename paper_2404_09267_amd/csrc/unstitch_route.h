@@ -14,8 +14,10 @@ constexpr int32_t kSmallBoxes = 256, kSmallRois = 128;
 // Calls whose boxes test at least this many patches in all read the plan through a layout
 // (10,000 boxes on canvases of 31 patches: gathered 10.6 us, laid out 13.2; 50,000 boxes on
 // canvases of 302, overlap rule: 74.8 us gathered by 64 lanes per box from 24-byte records
-// before, 26.5 laid out), as do calls of more than kOwnCountBoxes boxes.
-constexpr int64_t kLaidOutTests = int64_t(1) << 21;
+// before, 26.5 laid out), and more for each canvas, which takes time to lay out whether boxes
+// meet it or not (100,000 canvases of 4, 200,000 boxes: gathered 38 us, laid out 46; 400,000 68
+// and 58; 500,000 canvases of 2, 300,000 boxes: 45 and 140).
+constexpr int64_t kLaidOutTests = int64_t(1) << 21, kLaidOutPerCanvas = 24;
 
 // An emit workgroup counts the kept boxes before its own by itself up to here when the plan was
 // gathered, ...
@@ -40,7 +42,8 @@ inline UnstitchRoute unstitch_route(int32_t n_boxes, int32_t n_rois, int32_t n_c
   r.small = n_boxes <= kSmallBoxes && n_rois <= kSmallRois;
   if (r.small) return r;
   r.laid_out = room && n_rois > 0 && n_canvases > 0 &&
-               (n_boxes * per_canvas >= kLaidOutTests || n_boxes > kOwnCountBoxes);
+               n_boxes * per_canvas >=
+                   kLaidOutTests + kLaidOutPerCanvas * n_canvases;
   r.counted = r.laid_out || n_boxes > kOwnCountBoxes;
   // Laid out: a 32-patch word per lane (of 1, 2 and 4 lanes per box on canvases of about 30
   // patches 2 are fastest, of 4 and 8 on canvases of hundreds 8). Gathered: a round is two

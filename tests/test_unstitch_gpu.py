@@ -308,3 +308,27 @@ def test_uneven_canvases(torch, n, rule):
     perm = rng.permutation(n)
     say("uneven canvases", n, rule)
     check(torch, boxes[perm], canv[perm], rois, plan, 1, rule=rule)
+
+
+@pytest.mark.parametrize("at", [1, 2047, 2048, 9000, 16383, 16384, 19999, 20000])
+def test_broken_begin_among_many_canvases(torch, at):
+    """One entry of canvas_begin out of order among 20,001: found wherever it is, so that calls
+    that lay the plan out give what calls that gather it give."""
+    C = 20000
+    rois, plan = _grid_plan([20] * C, 9, 60)
+    begin = plan.canvas_begin.copy()
+    begin[at] += 30 if at < C else -len(rois)
+    dplan = tg.DevicePlan(rois, tg.Plan(plan.place, plan.order, begin, C))
+    rng = np.random.default_rng(at)
+    n = 150000
+    c = rng.uniform(-5, 65, (n, 2))
+    boxes = np.concatenate([c - 6, c + 6], 1).astype(np.float32)
+    canv = rng.integers(0, C, n).astype(np.int32)
+    canv[:2000] = rng.integers(at - 3, at + 3, 2000)  # canvases beside the broken entry
+    for rule in (0, 1):
+        say("broken begin", at, rule)
+        whole = run_unstitch(torch, boxes, canv, rois, plan, 1, dplan, rule)
+        parts = [run_unstitch(torch, boxes[k:k + 10000], canv[k:k + 10000], rois, plan, 1, dplan,
+                              rule)[0] for k in range(0, n, 10000)]
+        assert (whole[0] >= 0).any()
+        np.testing.assert_array_equal(whole[0], np.concatenate(parts))

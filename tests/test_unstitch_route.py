@@ -42,3 +42,12 @@ def test_no_layout_without_room(route):
             assert (r.laid_out, r.lanes, r.counted) == (0, lanes, counted)
     assert not route(I32, 0, 5).laid_out
     assert not route(I32, 0, 0).laid_out
+
+
+def test_layout_pays_for_its_canvases(route):
+    """Laying the plan out takes time per canvas, whether boxes meet it or not."""
+    assert not route(300000, 1000000, 500000).laid_out
+    assert not route(300000, 2000000, 2000000).laid_out
+    assert not route(1 << 24, I32, I32).laid_out
+    assert route(2000000, 400000, 100000).laid_out
+    assert route(200000, 120000, 4000).laid_out
