@@ -21,7 +21,7 @@
 //    the patches that touch it. A box's candidates are the AND of its columns' and its
 //    rows' bits, a few patches instead of the canvas's hundreds. assign (L lanes per box, a
 //    32-patch word each) tests those and counts the kept boxes of each kCountBlock boxes;
-//    emit sums the counts before its own.
+//    emit sums the counts before its own, or reads them scanned.
 // No pass takes tickets or waits for another workgroup.
 #include <hip/hip_runtime.h>
 
@@ -52,6 +52,7 @@ using tg_detail::wave_min;
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kBandThreads = 1024;  // assign over prep's layout
+constexpr int kScanThreads = 1024;
 constexpr int kSmallLanes = 4;      // lanes per box in small_kernel
 constexpr int kSmallThreads = kSmallBoxes * kSmallLanes;
 constexpr int kCheckGroups = 8;     // workgroups of prep that check canvas_begin, a byte each
@@ -476,11 +477,62 @@ __global__ __launch_bounds__(kThreads) void count_kernel(const UnstitchParams P)
     P.counts[blk] = static_cast<uint8_t>(__popcll(m0) + __popcll(m1));
 }
 
+// The counts scanned in place by one workgroup, so that an emit workgroup reads one word
+// instead of summing all counts before its own: each 8 counts (1,024 boxes) become the kept
+// boxes before them, and in the upper word those of their first 2, 4 and 6 counts in 10 bits
+// each.
+__global__ __launch_bounds__(kScanThreads) void scan_counts_kernel(const UnstitchParams P) {
+  __shared__ int s_wave[kScanThreads / 64];
+  constexpr int kPer = 4;  // words per thread and step
+  uint64_t *words = reinterpret_cast<uint64_t *>(P.counts);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_counts = static_cast<int>((uint32_t(P.n_boxes) + kCountBlock - 1) / kCountBlock);
+  const int n_words = (n_counts + 7) / 8;
+  int carry = 0;
+  for (int w0 = 0; w0 < n_words; w0 += kPer * kScanThreads) {
+    const int first = w0 + kPer * tid;
+    int pair[kPer][4], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int w = first + k, left = n_counts - 8 * w;  // counts of this word and later ones
+      uint64_t v = left > 0 ? words[w] : 0;
+      if (left > 0 && left < 8) v &= (uint64_t(1) << (8 * left)) - 1;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        pair[k][j] = static_cast<int>((v >> (16 * j) & 0xFFu) + (v >> (16 * j + 8) & 0xFFu));
+        sum += pair[k][j];
+      }
+    }
+    int incl = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int at = carry + incl - sum;
+#pragma unroll
+    for (int w = 0; w < kScanThreads / 64; ++w) {
+      if (w < wave) at += s_wave[w];
+      carry += s_wave[w];
+    }
+    __syncthreads();  // s_wave is written again by the next step
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      if (first + k >= n_words) break;
+      const int p1 = pair[k][0], p2 = p1 + pair[k][1], p3 = p2 + pair[k][2];
+      words[first + k] = static_cast<uint32_t>(at) |
+                         static_cast<uint64_t>(p1 | p2 << 10 | p3 << 20) << 32;
+      at += p3 + pair[k][3];
+    }
+  }
+}
+
 // Writes the kept boxes of 256 consecutive boxes, one per thread, in increasing box order: a
 // stable compaction. The workgroup's first position is the kept boxes before its own:
 // kOwnCounts all earlier box ids, read again by every workgroup; kSumCounts the sum of the
-// earlier counts.
-enum EmitCounts { kOwnCounts, kSumCounts };
+// earlier counts; kScanned its own word of the scanned counts.
+enum EmitCounts { kOwnCounts, kSumCounts, kScanned };
 template <EmitCounts kMode>
 __global__ __launch_bounds__(kThreads) void emit_kernel(const UnstitchParams P) {
   __shared__ int s_before[kWaves], s_wave[kWaves];
@@ -488,7 +540,14 @@ __global__ __launch_bounds__(kThreads) void emit_kernel(const UnstitchParams P) 
   const uint32_t b0 = blockIdx.x * kThreads, b = b0 + tid;
   const int roi = b < static_cast<uint32_t>(P.n_boxes) ? P.roi_of_box[b] : -1;
   int before = 0;
-  if (kMode == kSumCounts) {  // the counts before b0 (an even number), four at a time
+  if (kMode == kScanned) {
+    if (tid == 0) {
+      const uint64_t v = reinterpret_cast<const uint64_t *>(P.counts)[b0 / (8 * kCountBlock)];
+      const uint32_t part = b0 / kThreads % 4;
+      before = static_cast<int>(static_cast<uint32_t>(v));
+      if (part > 0) before += static_cast<int>(v >> (32 + 10 * (part - 1)) & 1023u);
+    }
+  } else if (kMode == kSumCounts) {  // the counts before b0 (an even number), four at a time
     const uint32_t n = b0 / kCountBlock;
 #pragma unroll 4
     for (uint32_t i = 4 * tid; i < n; i += 4 * kThreads) {
@@ -722,8 +781,12 @@ int launch(const tg_unstitch_args *a, void *words, void *records, hipStream_t s)
                          s, P);
   }
   if (hipGetLastError() != hipSuccess) return TG_E_HIP;
+  if (R.scanned) hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(kScanThreads), 0, s, P);
+  if (hipGetLastError() != hipSuccess) return TG_E_HIP;
   const dim3 grid = groups(a->n_boxes, kThreads);
-  if (R.counted)
+  if (R.scanned)
+    hipLaunchKernelGGL(emit_kernel<kScanned>, grid, dim3(kThreads), 0, s, P);
+  else if (R.counted)
     hipLaunchKernelGGL(emit_kernel<kSumCounts>, grid, dim3(kThreads), 0, s, P);
   else
     hipLaunchKernelGGL(emit_kernel<kOwnCounts>, grid, dim3(kThreads), 0, s, P);

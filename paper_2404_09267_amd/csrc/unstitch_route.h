@@ -22,15 +22,20 @@ constexpr int64_t kLaidOutTests = int64_t(1) << 21, kLaidOutPerCanvas = 24;
 // An emit workgroup counts the kept boxes before its own by itself up to here when the plan was
 // gathered, ...
 constexpr int32_t kOwnCountBoxes = 65536;
-// ... and sums the counts of kCountBlock boxes each past it.
+// ... sums the counts of kCountBlock boxes each up to here, and past it finds its sum in the
+// scanned counts: what all workgroups sum together grows with the square of the boxes
+// (us: 2^20 boxes 52.5, scanned 54.4; 2^21 91.3 and 92.0; 2^22 170 and 164; 2^24 933 and 763;
+// 2^25 2,267 and 1,521).
+constexpr int32_t kSumBoxes = 1 << 21;
 constexpr int32_t kCountBlock = 128;  // boxes per count (a byte of workspace each)
 
 struct UnstitchRoute {
   bool small;     // small_kernel alone
   bool laid_out;  // prep, and the assign over its layout; else the assign gathers the plan
   int lanes;      // per box in the assign
-  bool counted;   // an emit workgroup finds the kept boxes before its own in the counts, else
-                  // in roi_of_box
+  // Where an emit workgroup finds the kept boxes before its own: in roi_of_box (neither), in
+  // the counts (counted), or in the scanned counts (scanned as well).
+  bool counted, scanned;
 };
 
 // `room`: there is scratch for the layout.
@@ -45,6 +50,7 @@ inline UnstitchRoute unstitch_route(int32_t n_boxes, int32_t n_rois, int32_t n_c
                n_boxes * per_canvas >=
                    kLaidOutTests + kLaidOutPerCanvas * n_canvases;
   r.counted = r.laid_out || n_boxes > kOwnCountBoxes;
+  r.scanned = r.counted && n_boxes > kSumBoxes;
   // Laid out: a 32-patch word per lane (of 1, 2 and 4 lanes per box on canvases of about 30
   // patches 2 are fastest, of 4 and 8 on canvases of hundreds 8). Gathered: a round is two
   // dependent gathers, so 64 lanes, for one round to settle a box, unless canvases hold at most

@@ -332,3 +332,20 @@ def test_broken_begin_among_many_canvases(torch, at):
                               rule)[0] for k in range(0, n, 10000)]
         assert (whole[0] >= 0).any()
         np.testing.assert_array_equal(whole[0], np.concatenate(parts))
+
+
+@pytest.mark.parametrize("n", [1 << 21, (1 << 21) + 1, (1 << 21) + 1279, (1 << 22) + 4096 * 1024 + 77])
+def test_scanned_counts(torch, n):
+    """Calls on both sides of the scan of the counts, with a last word that is not full and
+    more words than one step of the scan takes."""
+    rois, plan = _grid_plan([25, 30, 0, 31], 9, 60)
+    rng = np.random.default_rng(n)
+    c = rng.uniform(-5, 65, (n, 2)).astype(np.float32)
+    boxes = np.concatenate([c - 6, c + 6], 1)
+    canv = rng.integers(-1, 5, n).astype(np.int32)
+    canv[5000:9000] = -1  # whole counts of nothing, and of everything
+    c[9000:13000] = 15
+    boxes[9000:13000] = [10, 10, 20, 20]
+    canv[9000:13000] = 1
+    say("scanned counts", n)
+    check(torch, boxes, canv, rois, plan, 1)

@@ -8,7 +8,7 @@ import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2404_09267_amd", "csrc")
-Route = namedtuple("Route", "small laid_out lanes counted")
+Route = namedtuple("Route", "small laid_out lanes counted scanned")
 I32 = 2 ** 31 - 1
 OWN = 65536  # most boxes that emit workgroups count by themselves
 
@@ -51,3 +51,18 @@ def test_layout_pays_for_its_canvases(route):
     assert not route(1 << 24, I32, I32).laid_out
     assert route(2000000, 400000, 100000).laid_out
     assert route(200000, 120000, 4000).laid_out
+
+
+def test_counts_read_again_stay_linear(route):
+    """What the emit workgroups (256 boxes each) read to find the kept boxes before their own
+    -- 4 bytes per box, or a byte per 128 boxes -- is at most 16 KB each, half of it on average:
+    it does not grow with the square of the boxes."""
+    boxes = 1
+    while boxes <= I32:
+        for rois, canvases, room in [(120000, 4000, 1), (150000, 500, 0), (40, 2, 1)]:
+            r = route(boxes, rois, canvases, room)
+            if r.small or r.scanned:
+                continue
+            assert (boxes // 128 if r.counted else 4 * boxes) <= 1 << (14 if r.counted else 18)
+        boxes = 2 * boxes + 1
+    assert route(1 << 24, 120000, 4000).scanned
