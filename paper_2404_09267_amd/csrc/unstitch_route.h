@@ -3,6 +3,7 @@
 #ifndef TG_UNSTITCH_ROUTE_H
 #define TG_UNSTITCH_ROUTE_H
 
+#include <algorithm>
 #include <cstdint>
 
 namespace tg_detail {
@@ -11,17 +12,20 @@ namespace tg_detail {
 // may hold them all).
 constexpr int32_t kSmallBoxes = 256, kSmallRois = 128;
 
-// Calls whose boxes test at least this many patches in all read the plan through a layout
-// (10,000 boxes on canvases of 31 patches: gathered 10.6 us, laid out 13.2; 50,000 boxes on
-// canvases of 302, overlap rule: 74.8 us gathered by 64 lanes per box from 24-byte records
-// before, 26.5 laid out), and more for each canvas, which takes time to lay out whether boxes
-// meet it or not (100,000 canvases of 4, 200,000 boxes: gathered 38 us, laid out 46; 400,000 68
-// and 58; 500,000 canvases of 2, 300,000 boxes: 45 and 140).
-constexpr int64_t kLaidOutTests = int64_t(1) << 21, kLaidOutPerCanvas = 24;
+// Gathering the plan costs a box about as much as its canvas has patches, but never less than
+// eight; laying the plan out costs a launch and some time per canvas, after which patches hardly
+// count. Gathered and laid out (us, whole calls): canvases of 31 patches, 10,000 boxes 8.9 and
+// 11.3, 40,000 14.4 and 13.7, 65,000 17.8 and 13.5; of 300, 5,000 boxes 13.7 and 15.1, 10,000
+// 22.5 and 15.3; of 4, 100,000 boxes 11.1 and 12.8, 200,000 16.9 and 16.4; 100,000 canvases of
+// 4, 200,000 boxes 39 and 46, 400,000 69 and 57; 500,000 canvases of 2, 400,000 boxes 52 and
+// 143, 2,000,000 230 and 225.
+constexpr int64_t kLaidOutTests = 3 << 18, kLaidOutPerCanvas = 24;
+constexpr int64_t kLeastTests = 8;
 
 // An emit workgroup counts the kept boxes before its own by itself up to here when the plan was
-// gathered, ...
-constexpr int32_t kOwnCountBoxes = 65536;
+// gathered (us, canvases of 29 patches: 16,384 boxes 13.0, with counts from the assign 13.0;
+// 32,768 20.6 and 13.7; 65,536 34.4 and 20.0), ...
+constexpr int32_t kOwnCountBoxes = 16384;
 // ... sums the counts of kCountBlock boxes each up to here, and past it finds its sum in the
 // scanned counts: what all workgroups sum together grows with the square of the boxes
 // (us: 2^20 boxes 52.5, scanned 54.4; 2^21 91.3 and 92.0; 2^22 170 and 164; 2^24 933 and 763;
@@ -47,7 +51,7 @@ inline UnstitchRoute unstitch_route(int32_t n_boxes, int32_t n_rois, int32_t n_c
   r.small = n_boxes <= kSmallBoxes && n_rois <= kSmallRois;
   if (r.small) return r;
   r.laid_out = room && n_rois > 0 && n_canvases > 0 &&
-               n_boxes * per_canvas >=
+               n_boxes * std::max(per_canvas, kLeastTests) >=
                    kLaidOutTests + kLaidOutPerCanvas * n_canvases;
   r.counted = r.laid_out || n_boxes > kOwnCountBoxes;
   r.scanned = r.counted && n_boxes > kSumBoxes;

@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2404_09267_amd", "csrc")
 Route = namedtuple("Route", "small laid_out lanes counted scanned")
 I32 = 2 ** 31 - 1
-OWN = 65536  # most boxes that emit workgroups count by themselves
+OWN = 16384  # most boxes that emit workgroups count by themselves
 
 
 @pytest.fixture(scope="module")
@@ -66,3 +66,26 @@ def test_counts_read_again_stay_linear(route):
             assert (boxes // 128 if r.counted else 4 * boxes) <= 1 << (14 if r.counted else 18)
         boxes = 2 * boxes + 1
     assert route(1 << 24, 120000, 4000).scanned
+
+
+@pytest.mark.parametrize("boxes,rois,canvases,room,want", [
+    (256, 128, 3, 1, Route(1, 0, 0, 0, 0)),
+    (257, 128, 3, 1, Route(0, 0, 64, 0, 0)),
+    (256, 129, 9, 1, Route(0, 0, 16, 0, 0)),
+    (10000, 2000, 63, 1, Route(0, 0, 64, 0, 0)),      # canvases of 31 patches
+    (20000, 15500, 500, 1, Route(0, 0, 8, 1, 0)),
+    (30000, 15500, 500, 1, Route(0, 1, 2, 1, 0)),
+    (10000, 30000, 100, 1, Route(0, 1, 8, 1, 0)),     # of 300
+    (16384, 8000, 2000, 1, Route(0, 0, 16, 0, 0)),    # of 4
+    (16385, 8000, 2000, 1, Route(0, 0, 8, 1, 0)),
+    (100000, 8000, 2000, 1, Route(0, 0, 8, 1, 0)),
+    (200000, 8000, 2000, 1, Route(0, 1, 2, 1, 0)),
+    (300000, 1000000, 500000, 1, Route(0, 0, 8, 1, 0)),
+    (2000000, 1000000, 500000, 1, Route(0, 1, 2, 1, 0)),
+    (1 << 21, 120000, 4000, 1, Route(0, 1, 2, 1, 0)),
+    ((1 << 21) + 1, 120000, 4000, 1, Route(0, 1, 2, 1, 1)),
+    ((1 << 21) + 1, 150000, 500, 0, Route(0, 0, 64, 1, 1)),
+])
+def test_measured_lines(route, boxes, rois, canvases, room, want):
+    """The sides on which the measured sizes lie."""
+    assert route(boxes, rois, canvases, room) == want
