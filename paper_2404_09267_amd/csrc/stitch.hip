@@ -484,21 +484,21 @@ __global__ __launch_bounds__(kThreads) void stitch_kernel(const StitchParams P) 
     return;
   }
   // Any other plane size or output alignment: each plane's run starts at its own offset
-  // from a 128-byte line (`past` elements), so the run is written as the 16-byte chunks of
-  // memory it meets, a wave's 64 chunks on eight whole lines: chunk m of a plane holds run
-  // pixels [8 m - past, 8 m - past + 8). Those start at any staged dword; a lane reads the
-  // three aligned 16-byte words holding them and shifts by 0-3 dwords (the same for the
-  // whole workgroup, so the selects are on scalars). Only the chunks at the ends of a run
-  // are written element by element. (Two-byte stores throughout, as before, kept the store
-  // path busy with eight times the instructions: six 2047x1151 frames onto 19 canvases of
-  // 999x667, 102 MB: 59.6 us; as built 26.9 us, and 24.9 us, 4.1 TB/s, in runs of 4096.
-  // Chunks on 16-byte boundaries only, joined from neighbouring lanes: 27.6 us.)
+  // (`past` elements) from a 16-byte boundary, so the run is written as the 16-byte chunks of
+  // memory it meets: chunk m of a plane holds run pixels [8 m - past, 8 m - past + 8). Those
+  // start at any staged dword; a lane reads the three aligned 16-byte words holding them and
+  // shifts by 0-3 dwords (the same for the whole workgroup, so the selects are on scalars).
+  // Only the chunks at the ends of a run are written element by element. (Two-byte stores
+  // throughout, as before, kept the store path busy with eight times the instructions: 19
+  // canvases of 999x667 from six 2047x1151 frames 59.6 us; as built 26.9 us, and 24.2 us in runs
+  // of 4096. With a wave's 64 chunks on whole 128-byte lines: 24.2 us, 12 canvases 18.4 instead
+  // of 18.9, four 11.0 instead of 10.7. Chunks joined from neighbouring lanes: 27.6 us.)
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     uint16_t *base = P.out + (static_cast<int64_t>(c_local) * 3 + k) * P.plane + R.p0;
-    const int past = static_cast<int>((reinterpret_cast<uintptr_t>(base) >> 1) & 63u);
-    const int shift = (8 - (past & 7)) & 3;  // u0 mod 4
-    for (int m = (past >> 3) + tid; 8 * m - past < R.np; m += kThreads) {
+    const int past = static_cast<int>((reinterpret_cast<uintptr_t>(base) >> 1) & 7u);
+    const int shift = (8 - past) & 3;  // u0 mod 4
+    for (int m = tid; 8 * m - past < R.np; m += kThreads) {
       const int u0 = 8 * m - past;  // > -8
       const int q = (u0 - shift) >> 2;  // 16-byte word of the first pixel, >= -2
       uint32_t d[12];
