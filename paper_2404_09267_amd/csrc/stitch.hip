@@ -53,12 +53,16 @@ using tg_detail::StitchGeometry;
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 // Pixels per unit: kRun, the size the unit numbers of a unit_order refer to. Launches without
-// one use smaller runs where those are faster: up to kSmallPixels canvas pixels runs of
-// kRunSmall, since 6144-pixel units would leave CUs idle (2.5 M pixels are 407 of them; one
-// 1024x1024 canvas 6.6 -> 5.4 us, two 7.5 -> 6.2; three cost 7.6 against 8.2 but ten 18.9
-// against 18.7, 32 of them 20 % more), and runs of kRunAny where a plane does not take whole
-// 16-byte groups (19 canvases of 999x667 26.5 -> 24.5 us, one 9.0 -> 7.5: its conversion
-// reads LDS three times, and more, smaller workgroups per CU hide that).
+// one use smaller runs where those are faster.
+//  - Up to kSmallPixels canvas pixels runs of kRunSmall, since 6144-pixel units would leave CUs
+//    idle (2.5 M pixels are 407 of them). Short and long runs (us): crops of 32-512 pixels, one
+//    1024x1024 canvas 5.6 and 6.7, two 6.0 and 7.5, three (3.1 M pixels) 7.6 and 8.2, four 10.4
+//    and 9.4, eight 15.6 and 14.8, 16 27.0 and 24.7; crops of 8-64, one 9.1 and 11.0, three 15.7
+//    and 14.7, ten 42.0 and 35.2, 640x640 six (2.5 M) 9.9 and 11.4, eight (3.3 M) 13.0 and 12.3.
+//    Between 2.5 M and 3.3 M pixels it depends on the crops, by 7 % either way.
+//  - Runs of kRunAny where a plane does not take whole 16-byte groups (19 canvases of 999x667
+//    26.5 -> 24.5 us, one 9.0 -> 7.5: its conversion reads LDS three times, and more, smaller
+//    workgroups per CU hide that).
 constexpr int kRun = tg_detail::kStitchRun;
 constexpr int kRunSmall = 2048;
 constexpr int kRunAny = 4096;
