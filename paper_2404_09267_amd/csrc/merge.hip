@@ -217,7 +217,8 @@ __device__ __forceinline__ int block_exclusive(int v, int *s, int *total) {
 }
 
 __device__ __forceinline__ int bin_of(const MergeParams &P, int f) {
-  return P.per_bin == 1 ? f : static_cast<int>(static_cast<uint32_t>(f) / static_cast<uint32_t>(P.per_bin));
+  const uint32_t per = P.per_bin;
+  return per == 1 ? f : static_cast<int>(static_cast<uint32_t>(f) / per);
 }
 
 // Detections of this workgroup's chunk per bin. (Counting into global counters instead
@@ -607,7 +608,8 @@ __device__ void add_large(const MergeParams &P, LocalLds &S, int lo, int n) {
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < 4; ++k) e[k] = wave_min(S.ext[k][lane & (kLocal / 64 - 1)]);
-  const float x0 = __builtin_isfinite(e[0]) ? e[0] : 0.0f, y0 = __builtin_isfinite(e[1]) ? e[1] : 0.0f;
+  const float x0 = __builtin_isfinite(e[0]) ? e[0] : 0.0f;
+  const float y0 = __builtin_isfinite(e[1]) ? e[1] : 0.0f;
   const float dx = -e[2] - e[0], dy = -e[3] - e[1];  // (not finite: no even grid below)
   const int cell = cell_of(sample.y, y0, g * __builtin_amdgcn_rcpf(dy), g) * g +
                    cell_of(sample.x, x0, g * __builtin_amdgcn_rcpf(dx), g);
@@ -989,10 +991,11 @@ __device__ void test_candidates(const MergeParams &P, TileLds &S, const int32_t 
 }
 
 // The suppressors ranked above each of m <= kTileThreads detections (positions own[]) of
-// frame L, among the frame's boxes that can meet the rectangle around the m boxes. The point that two overlapping boxes share (see above) lies in
-// the one and so in the rectangle, hence the comparisons; they let NaN corners through, and
-// a NaN corner among the m, or a negative threshold, lets every box through. (Every
-// detection against every candidate: 10-28 us a tile of 250 by 270.)
+// frame L, among the frame's boxes that can meet the rectangle around the m boxes. The point
+// that two overlapping boxes share (see above) lies in the one and so in the rectangle, hence
+// the comparisons; they let NaN corners through, and a NaN corner among the m, or a negative
+// threshold, lets every box through. (Every detection against every candidate: 10-28 us a tile
+// of 250 by 270.)
 __device__ void search_owned(const MergeParams &P, TileLds &S, const LargeFrame &L,
                              const int32_t *own, int m, bool fill) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1304,10 +1307,10 @@ __global__ __launch_bounds__(kTiny) void tiny_kernel(const MergeParams P) {
   for (int w = 0; w < kTinyWords; ++w) s_sup[i][w] = 0;
   __syncthreads();
 
-  // the suppressor rows, each pair tested once (as in the LDS path of small frames: thread
-  // i takes the detections 1 .. n/2 places after it, cyclically, four records per step,
-  // and the bit goes into the row of whichever of the two is ranked below); a pair with a
-  // detection outside the frames sets no bit, so such a thread skips its share
+  // the suppressor rows, each pair tested once (as in decide_rows: thread i takes the
+  // detections 1 .. n/2 places after it, cyclically, four records per step, and the bit goes
+  // into the row of whichever of the two is ranked below); a pair with a detection outside the
+  // frames sets no bit, so such a thread skips its share
   if (f >= 0) {
     const int last = (n % 2 == 0 && i < n / 2) ? n / 2 : (n - 1) / 2;
     for (int d0 = 1; d0 <= last; d0 += 4) {
@@ -1476,9 +1479,9 @@ int compact_blocks(int32_t n_max) { return (n_max + kCompactBlock - 1) / kCompac
 size_t round16(size_t v) { return (v + 15) / 16 * 16; }
 
 // Bytes of the workspace: the look-back words and three more, per frame 516 bytes (12 past
-// 16,384 frames) for the table of bins, and per detection 344, of which the passes' arrays
-// take 130 (166 with several frames per bin) and the rest holds suppressor lists of more than
-// kPredSlots.
+// 16,384 frames) and per detection 344. The table of bins takes at most 128 KB of that, the
+// passes' arrays 113 bytes per detection (149 with several frames per bin); the rest holds
+// suppressor lists of more than kPredSlots.
 size_t workspace_bytes(int32_t n_max, int32_t n_frames) {
   const size_t n = static_cast<size_t>(n_max), f = static_cast<size_t>(n_frames);
   const size_t head = sizeof(uint64_t) * (3 + static_cast<size_t>(compact_blocks(n_max))) +
@@ -1492,8 +1495,7 @@ int32_t chunk_of(int32_t n_max) {
   return static_cast<int32_t>((per + kBinThreads - 1) / kBinThreads * kBinThreads);
 }
 
-// Lays the arrays out from `ws` (null: only sizes them); returns the bytes before ovf, which
-// takes the rest.
+// Lays the arrays out from `ws`; returns the bytes before ovf, which takes the rest.
 size_t lay_out(uint8_t *ws, int32_t n_max, MergeParams &P) {
   const size_t n = static_cast<size_t>(n_max);
   size_t at = 0;

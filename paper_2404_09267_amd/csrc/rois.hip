@@ -1260,7 +1260,8 @@ extern "C" int tg_mask_rois(const tg_mask_rois_args *a, void *stream) {
                      T, L.tile_bits, L.rec_fg, L.words, L.n_words);
   const int64_t n_bit_words = n_bands * T.wpb, n_chunks = list_chunks(n_bit_words);
   hipLaunchKernelGGL(n_bit_words <= kListCount ? list_kernel<true> : list_kernel<false>,
-                     dim3(static_cast<uint32_t>(n_chunks)), dim3(kListThreads), 0, s, L.tile_bits, n_bit_words, T, L.tile_list, L.words, L.list_state,
+                     dim3(static_cast<uint32_t>(n_chunks)), dim3(kListThreads), 0, s,
+                     L.tile_bits, n_bit_words, T, L.tile_list, L.words, L.list_state,
                      static_cast<int32_t>(n_chunks), n_list, status);
   hipLaunchKernelGGL(local_kernel, local_groups, dim3(kLocalThreads), 0, s, W, frame_px, T,
                      L.tile_list, n_list, L.rec_fg, L.rec_roots, L.rec_border, L.entries,

@@ -213,7 +213,8 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(const UnstitchParams P) 
     if (tid == 0) P.gather[blockIdx.x] = static_cast<uint8_t>(bad != 0);
     return;
   }
-  const int64_t c64 = (int64_t(blockIdx.x) - kCheckGroups) * (kWaves / kWavesPer) + wave / kWavesPer;
+  const int64_t c64 =
+      (int64_t(blockIdx.x) - kCheckGroups) * (kWaves / kWavesPer) + wave / kWavesPer;
   if (kWavesPer == 1 && c64 >= P.n_canvases) return;
   const int c = static_cast<int>(c64);
   const int wv = wave % kWavesPer;
@@ -759,7 +760,8 @@ int launch(const tg_unstitch_args *a, void *words, void *records, hipStream_t s)
       hipLaunchKernelGGL(prep_kernel<kWaves>, groups(int64_t(a->n_canvases) + kCheckGroups, 1),
                          dim3(kThreads), 0, s, P);
     else
-      hipLaunchKernelGGL(prep_kernel<1>, groups(int64_t(a->n_canvases) + kCheckGroups * kWaves, kWaves),
+      hipLaunchKernelGGL(prep_kernel<1>,
+                         groups(int64_t(a->n_canvases) + kCheckGroups * kWaves, kWaves),
                          dim3(kThreads), 0, s, P);
     if (hipGetLastError() != hipSuccess) return TG_E_HIP;
     if (R.lanes == 2)
