@@ -124,20 +124,22 @@ def test_random_forests_give_components(harness):
         assert all(low[arr[i]] == low[i] for i in range(n))  # links stay in their set
 
 
-def test_unites_between_the_accesses_of_others(harness):
-    """Unites that run between two accesses of another one, nested: the components are those
-    of the edges, each rooted at its smallest index, and every root that stops being one is
-    linked once (the components are counted by that)."""
+@pytest.mark.parametrize("op,trials", [("N", 400), ("A", 1500)])
+def test_unites_between_the_accesses_of_others(harness, op, trials):
+    """Unites that run between two accesses of another one, nested (N), and up to eight whose
+    accesses alternate in any order (A), each between the other's reads and writes: the
+    components are those of the edges, each rooted at its smallest index, and every root that
+    stops being one is linked once (the components are counted by that)."""
     rng = np.random.default_rng(13)
     lines, want = [], []
-    for trial in range(400):
+    for trial in range(trials):
         n = int(rng.integers(2, 60))
         m = int(rng.integers(1, 3 * n))
         near = trial % 2  # chains of neighbours, or any pairs
         a = rng.integers(0, n, m)
         b = np.clip(a + rng.integers(-3, 4, m), 0, n - 1) if near else rng.integers(0, n, m)
         edges = list(zip(a.tolist(), b.tolist()))
-        lines.append(f"N {n} {int(rng.integers(1, 2**31))} {m} " +
+        lines.append(f"{op} {n} {int(rng.integers(1, 2**31))} {m} " +
                      " ".join(f"{x} {y}" for x, y in edges))
         want.append((n, _components(n, edges)))
     for (n, low), g in zip(want, harness(lines)):
