@@ -166,15 +166,16 @@ def test_workload_boxes_overlap_rule(torch, name):
 
 
 def test_patch_records_switch(torch):
-    """The calls on either side of the switch to patch records (at 2^21 box-patch tests,
-    about n_boxes times the mean patches per canvas) agree with the oracle and with each
-    other on their common boxes: the direct gathers and the records give one result."""
+    """The calls on either side of the switch to a laid out plan (786,432 box-patch tests,
+    n_boxes times the mean patches per canvas, and 24 for each canvas), and one of 2^21 tests,
+    agree with the oracle and with each other on their common boxes: gathering and the layout
+    give one result."""
     rng = np.random.default_rng(91)
     rois = W.random_rois(rng, 9000, 4, 800, 600, 5, 11, 11)
     plan = tg.plan_pack(rois, 200, 200, 800, 600, 4, tg.SHELF_FFDH)
     per_canvas = -(-len(rois) // plan.n_canvases)
-    n_switch = -(-(1 << 21) // per_canvas)
-    n = n_switch + 100
+    n_switch = -(-((3 << 18) + 24 * plan.n_canvases) // per_canvas)
+    n = -(-(1 << 21) // per_canvas) + 100
     cx, cy = rng.uniform(-4, 204, n), rng.uniform(-4, 204, n)
     bw, bh = rng.uniform(0, 20, n), rng.uniform(0, 20, n)
     boxes = np.stack([cx - bw / 2, cy - bh / 2, cx + bw / 2, cy + bh / 2], 1).astype(np.float32)
@@ -182,16 +183,18 @@ def test_patch_records_switch(torch):
     canv = rng.integers(-1, plan.n_canvases + 1, n).astype(np.int32)
     dplan = tg.DevicePlan(rois, plan)
     for rule in (0, 1):
-        say("records switch", per_canvas, n_switch, "rule", rule)
+        say("layout switch", per_canvas, n_switch, "rule", rule)
         lo = check(torch, boxes[:n_switch - 1], canv[:n_switch - 1], rois, plan, 1, dplan, rule)
+        at = check(torch, boxes[:n_switch], canv[:n_switch], rois, plan, 1, dplan, rule)
         hi = check(torch, boxes, canv, rois, plan, 1, dplan, rule)
         np.testing.assert_array_equal(lo[0], hi[0][:n_switch - 1])
+        np.testing.assert_array_equal(at[0], hi[0][:n_switch])
 
 
 @pytest.mark.parametrize("rule", [0, 1])
 def test_patch_records_with_small_canvases(torch, rule):
-    """Patch records on canvases of about 24 patches (16 lanes per box, two rounds):
-    120,000 boxes, centres on edges, NaN and infinite corners, bad canvases."""
+    """The layout of canvases of about 24 patches (one word of band bits each): 120,000
+    boxes, centres on edges, NaN and infinite corners, bad canvases."""
     rng = np.random.default_rng(95 + rule)
     rois = W.random_rois(rng, 720, 4, 800, 600, 28, 48, 48)
     plan = tg.plan_pack(rois, 200, 200, 800, 600, 4, tg.SHELF_FFDH)
@@ -229,7 +232,8 @@ def _grid_plan(sizes, cell, cw):
 @pytest.mark.parametrize("rule", [0, 1])
 def test_band_layout_sizes(torch, sizes, rule):
     """Canvases around the smallest count with band words and around whole 32-patch words,
-    in calls of every lanes-per-box width and of the gathered path; boxes on patch edges,
+    in calls of both lanes-per-box widths over the layout and on either side of the most boxes
+    that a gathering call counts in its emit (16,384); boxes on patch edges,
     with NaN and infinite corners and inverted, whole-canvas boxes, bad canvases."""
     rois, plan = _grid_plan(sizes, 9, 300)
     rng = np.random.default_rng(len(rois))
@@ -269,8 +273,8 @@ def test_laid_out_path_with_corrupt_plans(torch):
         for rule in (0, 1):
             say("corrupt", what, rule)
             whole = run_unstitch(torch, boxes, canv, rois, plan, 1, dplan, rule)
-            parts = [run_unstitch(torch, boxes[k:k + 5000], canv[k:k + 5000], rois, plan, 1, dplan,
-                                  rule)[0] for k in range(0, n, 5000)]
+            parts = [run_unstitch(torch, boxes[k:k + 2500], canv[k:k + 2500], rois, plan, 1, dplan,
+                                  rule)[0] for k in range(0, n, 2500)]
             assert (whole[0] >= 0).any()
             np.testing.assert_array_equal(whole[0], np.concatenate(parts))
             assert whole[2] == (whole[0] >= 0).sum()
