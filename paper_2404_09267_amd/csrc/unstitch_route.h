@@ -13,13 +13,17 @@ namespace tg_detail {
 constexpr int32_t kSmallBoxes = 256, kSmallRois = 128;
 
 // Gathering the plan costs a box about as much as its canvas has patches, but never less than
-// eight; laying the plan out costs a launch and some time per canvas, after which patches hardly
-// count. Gathered and laid out (us, whole calls): canvases of 31 patches, 10,000 boxes 8.9 and
-// 11.3, 40,000 14.4 and 13.7, 65,000 17.8 and 13.5; of 300, 5,000 boxes 13.7 and 15.1, 10,000
-// 22.5 and 15.3; of 4, 100,000 boxes 11.1 and 12.8, 200,000 16.9 and 16.4; 100,000 canvases of
-// 4, 200,000 boxes 39 and 46, 400,000 69 and 57; 500,000 canvases of 2, 400,000 boxes 52 and
-// 143, 2,000,000 230 and 225.
-constexpr int64_t kLaidOutTests = 3 << 18, kLaidOutPerCanvas = 24;
+// eight, once the boxes fill the chip; fewer wait for the latency of the gathers alone. Laying
+// the plan out costs a launch and some time per canvas, after which patches hardly count. So the
+// line lies lower past kManyBoxes. Gathered and laid out (us, whole calls): canvases of 31
+// patches, 10,000 boxes 8.9 and 11.3, 40,000 14.4 and 13.7, 65,000 17.8 and 13.5; 60 of 300, 5,000
+// boxes 13.7 and 15.1, 8,000 19.0 and 15.0; eight of 533, 2,000 boxes 11.3 and 17.4, 4,000 13.9
+// and 17.0, 8,000 21.3 and 16.8; of 4, 100,000 boxes 11.1 and 12.8, 200,000 16.9 and 16.4;
+// 100,000 canvases of 4, 200,000 boxes 39 and 46, 400,000 69 and 57; 500,000 canvases of 2,
+// 400,000 boxes 52 and 143, 2,000,000 230 and 225.
+constexpr int32_t kManyBoxes = 32768;
+constexpr int64_t kLaidOutTests = 1 << 21, kLaidOutTestsMany = 3 << 18;
+constexpr int64_t kLaidOutPerCanvas = 24;
 constexpr int64_t kLeastTests = 8;
 
 // An emit workgroup counts the kept boxes before its own by itself up to here when the plan was
@@ -52,7 +56,8 @@ inline UnstitchRoute unstitch_route(int32_t n_boxes, int32_t n_rois, int32_t n_c
   if (r.small) return r;
   r.laid_out = room && n_rois > 0 && n_canvases > 0 &&
                n_boxes * std::max(per_canvas, kLeastTests) >=
-                   kLaidOutTests + kLaidOutPerCanvas * n_canvases;
+                   (n_boxes > kManyBoxes ? kLaidOutTestsMany : kLaidOutTests) +
+                       kLaidOutPerCanvas * n_canvases;
   r.counted = r.laid_out || n_boxes > kOwnCountBoxes;
   r.scanned = r.counted && n_boxes > kSumBoxes;
   // Laid out: a 32-patch word per lane (of 1, 2 and 4 lanes per box on canvases of about 30

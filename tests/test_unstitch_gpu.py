@@ -166,15 +166,16 @@ def test_workload_boxes_overlap_rule(torch, name):
 
 
 def test_patch_records_switch(torch):
-    """The calls on either side of the switch to a laid out plan (786,432 box-patch tests,
-    n_boxes times the mean patches per canvas, and 24 for each canvas), and one of 2^21 tests,
-    agree with the oracle and with each other on their common boxes: gathering and the layout
-    give one result."""
+    """The calls on either side of the switch to a laid out plan (more than 32,768 boxes:
+    786,432 box-patch tests, n_boxes times the mean patches per canvas, and 24 for each
+    canvas), and a larger one, agree with the oracle and with each other on their common boxes:
+    gathering and the layout give one result."""
     rng = np.random.default_rng(91)
-    rois = W.random_rois(rng, 9000, 4, 800, 600, 5, 11, 11)
+    rois = W.random_rois(rng, 900, 4, 800, 600, 24, 60, 60)
     plan = tg.plan_pack(rois, 200, 200, 800, 600, 4, tg.SHELF_FFDH)
     per_canvas = -(-len(rois) // plan.n_canvases)
     n_switch = -(-((3 << 18) + 24 * plan.n_canvases) // per_canvas)
+    assert n_switch > 32768
     n = -(-(1 << 21) // per_canvas) + 100
     cx, cy = rng.uniform(-4, 204, n), rng.uniform(-4, 204, n)
     bw, bh = rng.uniform(0, 20, n), rng.uniform(0, 20, n)
@@ -189,6 +190,24 @@ def test_patch_records_switch(torch):
         hi = check(torch, boxes, canv, rois, plan, 1, dplan, rule)
         np.testing.assert_array_equal(lo[0], hi[0][:n_switch - 1])
         np.testing.assert_array_equal(at[0], hi[0][:n_switch])
+
+
+@pytest.mark.parametrize("rule", [0, 1])
+def test_layout_switch_of_few_boxes(torch, rule):
+    """The same with at most 32,768 boxes, where the switch is at 2^21 tests."""
+    rng = np.random.default_rng(93)
+    rois = W.random_rois(rng, 9000, 4, 800, 600, 5, 11, 11)
+    plan = tg.plan_pack(rois, 200, 200, 800, 600, 4, tg.SHELF_FFDH)
+    n = -(-((1 << 21) + 24 * plan.n_canvases) // -(-len(rois) // plan.n_canvases))
+    assert n <= 32768
+    c, s = rng.uniform(-4, 204, (n, 2)), rng.uniform(0, 20, (n, 2))
+    boxes = np.concatenate([c - s / 2, c + s / 2], 1).astype(np.float32)
+    canv = rng.integers(-1, plan.n_canvases + 1, n).astype(np.int32)
+    dplan = tg.DevicePlan(rois, plan)
+    say("layout switch, few boxes", n, rule)
+    lo = check(torch, boxes[:n - 1], canv[:n - 1], rois, plan, 1, dplan, rule)
+    at = check(torch, boxes, canv, rois, plan, 1, dplan, rule)
+    np.testing.assert_array_equal(lo[0], at[0][:n - 1])
 
 
 @pytest.mark.parametrize("rule", [0, 1])

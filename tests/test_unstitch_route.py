@@ -74,8 +74,11 @@ def test_counts_read_again_stay_linear(route):
     (256, 129, 9, 1, Route(0, 0, 16, 0, 0)),
     (10000, 2000, 63, 1, Route(0, 0, 64, 0, 0)),      # canvases of 31 patches
     (20000, 15500, 500, 1, Route(0, 0, 8, 1, 0)),
-    (30000, 15500, 500, 1, Route(0, 1, 2, 1, 0)),
-    (10000, 30000, 100, 1, Route(0, 1, 8, 1, 0)),     # of 300
+    (40000, 15500, 500, 1, Route(0, 1, 2, 1, 0)),
+    (5000, 18000, 60, 1, Route(0, 0, 64, 0, 0)),      # of 300
+    (8000, 18000, 60, 1, Route(0, 1, 8, 1, 0)),
+    (3000, 4264, 8, 1, Route(0, 0, 64, 0, 0)),        # of 533
+    (8000, 4264, 8, 1, Route(0, 1, 8, 1, 0)),
     (16384, 8000, 2000, 1, Route(0, 0, 16, 0, 0)),    # of 4
     (16385, 8000, 2000, 1, Route(0, 0, 8, 1, 0)),
     (100000, 8000, 2000, 1, Route(0, 0, 8, 1, 0)),
