@@ -8,9 +8,11 @@
 
 namespace tg_detail {
 
-// One workgroup, one launch: up to this many boxes, on a plan of up to this many RoIs (a canvas
-// may hold them all).
-constexpr int32_t kSmallBoxes = 256, kSmallRois = 128;
+// One workgroup, one launch: up to this many boxes, on a plan of up to this many RoIs, which one
+// canvas may hold (us, 256 boxes on one canvas, overlap rule, in one launch and in two: 20
+// patches 5.1 and 7.8, 64 6.7 and 7.9, 100 9.0 and 8.0, 128 10.0 and 8.0; centre rule 4.4 and
+// 7.8, 5.3 and 7.8, 6.7 and 7.8, 7.2 and 8.0).
+constexpr int32_t kSmallBoxes = 256, kSmallRois = 96;
 
 // Gathering the plan costs a box about as much as its canvas has patches, but never less than
 // eight, once the boxes fill the chip; fewer wait for the latency of the gathers alone. Laying

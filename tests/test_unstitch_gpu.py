@@ -304,7 +304,7 @@ def test_laid_out_path_with_corrupt_plans(torch):
 def test_few_boxes(torch, n):
     """The one-workgroup path and the first size past it, by boxes and by RoIs."""
     rng = np.random.default_rng(n)
-    for n_rois in (1, 128, 129):
+    for n_rois in (1, 96, 97, 128, 129):
         rois = W.random_rois(rng, n_rois, 2, 400, 300, 4, 60, 60)
         plan = tg.plan_pack(rois, 160, 160, 400, 300, 2, 0)
         c, s = rng.uniform(0, 160, (n, 2)), rng.uniform(0, 40, (n, 2))
@@ -372,3 +372,64 @@ def test_scanned_counts(torch, n):
     canv[9000:13000] = 1
     say("scanned counts", n)
     check(torch, boxes, canv, rois, plan, 1)
+
+
+@pytest.mark.parametrize("n", [1, 64, 256])
+@pytest.mark.parametrize("rule", [0, 1])
+def test_few_boxes_corrupt_plans(torch, n, rule):
+    """The one-workgroup path on plans with positions that hold no RoI, RoIs placed on another
+    canvas and segments that overlap or leave the plan: as the passes that gather (the same
+    boxes among 300)."""
+    rois, plan = _grid_plan([30, 1, 40, 0, 20], 9, 90)
+    rng = np.random.default_rng(n)
+    c, s = rng.uniform(-5, 95, (300, 2)), rng.uniform(0, 25, (300, 2))
+    boxes = np.concatenate([c - s / 2, c + s / 2], 1).astype(np.float32)
+    boxes[::37, 1] = np.nan
+    canv = rng.integers(-1, 6, 300).astype(np.int32)
+    for what in ("ids", "begin"):
+        place, order, begin = plan.place.copy(), plan.order.copy(), plan.canvas_begin.copy()
+        if what == "ids":
+            order[::7], order[3::31] = 100000, -4
+            place[5::11, 0] = 2
+            place[6::13, 0] = -1
+        else:
+            begin[:] = [20, 95, 10, 70, 60, 88]
+        dplan = tg.DevicePlan(rois, tg.Plan(place, order, begin, 5))
+        say("few boxes, corrupt", what, n, rule)
+        few = run_unstitch(torch, boxes[:n], canv[:n], rois, plan, 1, dplan, rule)
+        all_ = run_unstitch(torch, boxes, canv, rois, plan, 1, dplan, rule)
+        np.testing.assert_array_equal(few[0], all_[0][:n])
+        assert few[2] == (few[0] >= 0).sum()
+        np.testing.assert_array_equal(few[1].view(np.int32), all_[1][:few[2]].view(np.int32))
+
+
+@pytest.mark.parametrize("rule", [0, 1])
+def test_few_boxes_cost(torch, rule):
+    """200 boxes on one canvas of 96 patches, one launch, cost no more than 1.3 times 300 boxes,
+    two launches (0.7 and 1.0 times by rule; 1.8 when the one launch gathered
+    the plan for every box)."""
+    rois, plan = _grid_plan([96], 9, 90)
+    dplan = tg.DevicePlan(rois, plan)
+    rng = np.random.default_rng(5)
+    c = rng.uniform(0, 90, (300, 2))
+    boxes = torch.from_numpy(np.concatenate([c - 9, c + 9], 1).astype(np.float32)).cuda()
+    canv = torch.zeros(300, dtype=torch.int32, device="cuda")
+
+    def us(n):
+        bufs = tg.UnstitchBuffers(n, dplan.n_rois)
+        args = tg.unstitch_args(boxes[:n], canv[:n], dplan, 1, bufs, rule)
+        best = float("inf")
+        for _ in range(20):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            e0.record()
+            for _ in range(50):
+                tg.unstitch_raw(args)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, 20 * e0.elapsed_time(e1))
+        return best
+
+    one, two = us(200), us(300)
+    say("few boxes", one, two)
+    assert one <= 1.3 * two

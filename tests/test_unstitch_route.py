@@ -69,9 +69,9 @@ def test_counts_read_again_stay_linear(route):
 
 
 @pytest.mark.parametrize("boxes,rois,canvases,room,want", [
-    (256, 128, 3, 1, Route(1, 0, 0, 0, 0)),
-    (257, 128, 3, 1, Route(0, 0, 64, 0, 0)),
-    (256, 129, 9, 1, Route(0, 0, 16, 0, 0)),
+    (256, 96, 3, 1, Route(1, 0, 0, 0, 0)),
+    (257, 96, 3, 1, Route(0, 0, 64, 0, 0)),
+    (256, 97, 9, 1, Route(0, 0, 16, 0, 0)),
     (10000, 2000, 63, 1, Route(0, 0, 64, 0, 0)),      # canvases of 31 patches
     (20000, 15500, 500, 1, Route(0, 0, 8, 1, 0)),
     (40000, 15500, 500, 1, Route(0, 1, 2, 1, 0)),
