@@ -1,4 +1,6 @@
 """tg_plan_pack (host, no GPU) against the oracle: bit-exact plans and error codes."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -124,3 +126,10 @@ def test_batch_split():
     ranges = [tg.batch_range(J, cap, k) for k in range(tg.batch_count(J, cap))]
     assert sum(c for _, c in ranges) == J
     assert all(f == k * cap for k, (f, _) in enumerate(ranges))
+
+
+def test_host_code_starts_on_cache_lines():
+    """The host entry points are aligned to 64 bytes, so that their speed does not depend on
+    where the kernels' code leaves room for them."""
+    for name in ("tg_plan_pack", "tg_slo_replay"):
+        assert ctypes.cast(getattr(tg.lib(), name), ctypes.c_void_p).value % 64 == 0, name
