@@ -93,12 +93,14 @@ constexpr int kResolveThreads = 1024;
 constexpr int32_t kUndecided = 0, kKept = 1, kSuppressed = 2;
 
 // A frame of more than kLocal detections, or one too crowded to be decided in LDS:
-// positions [lo, lo + n) of the frame order, cut into tiles numbered from `start` among all
-// listed frames' tiles. open: how many of its detections have suppressors (their positions
-// are listed in MergeParams::open from lo on).
+// positions [lo, lo + n) of the frame order, cut into g x g tiles numbered from `start` among
+// all listed frames' tiles: an even grid of dx x dy each from (x0, y0) on, or, g being
+// negative, by samples (uneven_rect). open: how many of its detections have suppressors (their
+// positions are listed in MergeParams::open from lo on).
 struct LargeFrame {
-  int32_t lo, n;
+  int32_t lo, n, g;
   uint32_t start;
+  float x0, y0, dx, dy;
   int32_t open;
 };
 
@@ -147,7 +149,6 @@ struct MergeParams {
   int32_t *table;           // [n_chunks][n_bins]
   int32_t *bin_begin;       // [n_bins + 1]
   LargeFrame *large;
-  TileRect *tile;           // by tile number
   // Per detection, at its position in bin order ...
   Rec *crec;
   // ... and in frame order (the same arrays with one frame per bin; else only the bins that
@@ -414,18 +415,13 @@ struct LocalLds {
   Aux aux[kLocal];
   uint16_t first[kLocal], end[kLocal];  // the positions of the detection's frame
   BandTable table;
-  union {
-    uint32_t pair[kPairs];  // position << 16 | a later position
-    uint64_t key[kLocal];   // add_large: samples in order
-  };
+  uint32_t pair[kPairs];  // position << 16 | a later position
   uint32_t hit[kHits];    // suppressed << 16 | suppressor; or suppressor rows (decide_rows)
   uint32_t kept[kLocalWords], open[kLocalWords];  // decide_rows: positions in that state
   uint8_t state[kLocal];
   uint8_t sees_kept[kLocal], sees_open[kLocal];  // this round, among its suppressors
   float ext[4][kLocal / 64];
-  float cut[kTilesPerAxis];  // add_large: where columns begin
   int n_pairs, n_hits, words;
-  uint32_t start;
 };
 
 // The words of 32 positions that hold o's frame.
@@ -537,61 +533,56 @@ __device__ void decide_rows(const MergeParams &P, LocalLds &S, int a, int b, int
   if (mine) P.keep[S.aux[i].idx] = st == kKept ? 1 : 0;
 }
 
-// Floats as integers in the same order, NaN as -infinity; and back.
-__device__ __forceinline__ uint32_t order_of(float v) {
-  const uint32_t b = __float_as_uint(fmaxf(v, -__builtin_inff()));
-  return b ^ ((b & 0x80000000u) ? 0xFFFFFFFFu : 0x80000000u);
-}
-__device__ __forceinline__ float value_of(uint32_t o) {
-  return __uint_as_float(o ^ ((o & 0x80000000u) ? 0x80000000u : 0xFFFFFFFFu));
-}
-
-// Sorts key[0 .. kLocal) upwards (bitonic), one element per thread. Called after a barrier,
-// ends with one.
-__device__ void sort_keys(uint64_t *key) {
-  const int i = threadIdx.x;
-  for (int size = 2; size <= kLocal; size *= 2)
-    for (int d = size / 2; d > 0; d /= 2) {
-      const uint64_t a = key[i], b = key[i ^ d];
-      const bool low = ((i & d) == 0) == ((i & size) == 0);  // this place takes the smaller
-      __syncthreads();
-      key[i] = (a < b) == low ? a : b;
-      __syncthreads();
-    }
-}
-
 __device__ __forceinline__ int cell_of(float v, float origin, float scale, int g) {
   return static_cast<int>(
       fminf(fmaxf(__fmul_rn(__fsub_rn(v, origin), scale), 0.0f), static_cast<float>(g - 1)));
 }
 
-// Lists a frame for the tile and resolve passes and cuts it into g x g tiles. Called by the
+// The position that thread i of kLocal samples of a frame of n > kLocal / 2: spread over the
+// frame, and one that thread i reads in any case when the threads step through it (samples
+// n / kLocal apart, loaded besides: 2 us).
+__device__ __forceinline__ int sample_at(int n, int i) {
+  if (n < kLocal) return i < n ? i : i - n;
+  const uint32_t step = static_cast<uint32_t>(i) * (static_cast<uint32_t>(n) / kLocal) / kLocal;
+  return i + kLocal * static_cast<int>(step);
+}
+
+// Lists a frame for the tile and resolve passes, to be cut into g x g tiles. Called by the
 // whole workgroup, after its boxes are in the workspace.
 // A tile is one workgroup's work, so its share of the detections decides the pass's time. An
 // even grid over the frame serves detections that are spread out (its tiles are then as
 // alike as they come); where kLocal samples show a cell with more than twice its share, the
-// cuts go where the samples say: g columns of equally many, each cut into g rows of equally
-// many. (20,000 detections, half of them in 300 x 300 of 3840 x 2160 pixels: 13.8 ms over the
-// even grid, 0.85 so; with one box a million pixels away 7.8 ms and 0.15; spread out 0.115
-// either way.)
+// cuts go where the samples say (uneven_rect). (20,000 detections, half of them in 300 x 300 of
+// 3840 x 2160 pixels: 13.8 ms over the even grid, 0.86 so; with one box a million pixels away
+// 7.8 ms and 0.14; spread out 0.114 either way. The check is 1 us of 8 frames of 6,000.)
 __device__ void add_large(const MergeParams &P, LocalLds &S, int lo, int n) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float inf = __builtin_inff();
-  const float4 sample = P.rec[lo + static_cast<int>((static_cast<int64_t>(tid) * n) / kLocal)].box;
+  // every tile reads the whole frame, so there are at most about kTilesMax of them
+  const int per_tile = min(max(count_of(P) / (4 * kGridCap), kTileDets), kTileDetsMax);
+  const float tiles = fminf(n * __builtin_amdgcn_rcpf(per_tile), static_cast<float>(kTilesMax));
+  const int g = min(max(1, static_cast<int>(ceilf(__builtin_amdgcn_sqrtf(tiles)))), kTilesPerAxis);
+  unsigned long long old = 0;  // (asked for here, waited for when the boxes are in)
+  if (tid == 0)
+    old = atomicAdd(P.large_used, (1ull << 32) | static_cast<unsigned long long>(g) * g);
+  const int at = sample_at(n, tid);
+  float2 sample = make_float2(0.0f, 0.0f);  // its top-left corner
   float e[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) e[k] = inf;
-#pragma unroll 4
+#pragma unroll 2  // (4: 0.4 us more of instruction fetches for frames of 6,000)
   for (int p = tid; p < n; p += kLocal) {
     const float4 b = P.rec[lo + p].box;
+    if (p == at) sample = make_float2(b.x, b.y);
     if (__builtin_isfinite(b.x)) e[0] = fminf(e[0], b.x);
     if (__builtin_isfinite(b.y)) e[1] = fminf(e[1], b.y);
     if (__builtin_isfinite(b.x)) e[2] = fminf(e[2], -b.x);
     if (__builtin_isfinite(b.y)) e[3] = fminf(e[3], -b.y);
   }
-  const int per_tile = min(max(count_of(P) / (4 * kGridCap), kTileDets), kTileDetsMax);
-  const float tiles = fminf(n * __builtin_amdgcn_rcpf(per_tile), static_cast<float>(kTilesMax));
-  const int g = min(max(1, static_cast<int>(ceilf(__builtin_amdgcn_sqrtf(tiles)))), kTilesPerAxis);
+  if (tid >= n) {
+    const float4 b = P.rec[lo + at].box;
+    sample = make_float2(b.x, b.y);
+  }
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -599,65 +590,19 @@ __device__ void add_large(const MergeParams &P, LocalLds &S, int lo, int n) {
     if (lane == 0) S.ext[k][wave] = e[k];
   }
   if (tid < g * g) S.hit[tid] = 0;
-  if (tid == 0) {
-    const unsigned long long old =
-        atomicAdd(P.large_used, (1ull << 32) | static_cast<unsigned long long>(g) * g);
-    P.large[old >> 32] = LargeFrame{lo, n, static_cast<uint32_t>(old), 0};
-    S.start = static_cast<uint32_t>(old);
-  }
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < 4; ++k) e[k] = wave_min(S.ext[k][lane & (kLocal / 64 - 1)]);
-  const float x0 = __builtin_isfinite(e[0]) ? e[0] : 0.0f;
-  const float y0 = __builtin_isfinite(e[1]) ? e[1] : 0.0f;
-  const float dx = -e[2] - e[0], dy = -e[3] - e[1];  // (not finite: no even grid below)
-  const int cell = cell_of(sample.y, y0, g * __builtin_amdgcn_rcpf(dy), g) * g +
-                   cell_of(sample.x, x0, g * __builtin_amdgcn_rcpf(dx), g);
+  const float share = __builtin_amdgcn_rcpf(g);
+  const float dx = (-e[2] - e[0]) * share, dy = (-e[3] - e[1]) * share;
+  const int cell = cell_of(sample.y, e[1], __builtin_amdgcn_rcpf(dy), g) * g +
+                   cell_of(sample.x, e[0], __builtin_amdgcn_rcpf(dx), g);
   const int before = atomicAdd(&S.hit[cell], 1);
   const bool even = !__syncthreads_or(before * g * g >= 2 * kLocal + 12 * g * g) &&
                     __builtin_isfinite(dx) && __builtin_isfinite(dy);
-  // (divisions by g, integer ones too, expand to fused multiply-adds: 1 / g in 16 bits)
-  const float share = __builtin_amdgcn_rcpf(g);
-  const int inv = static_cast<int>(65536.0f * share);
-  auto first_of = [&](int c) { return c < g ? c * inv * kLocal >> 16 : kLocal; };  // column c's
-  int cx = tid, cy = 0, column = 0;  // this thread's tile, and its sample's column
-  for (int c = 1; c < g; ++c) {
-    if (cx >= g) {
-      cx -= g;
-      ++cy;
-    }
-    if (tid >= first_of(c)) ++column;
-  }
-  if (!even) {
-    // (samples of one x in scrambled order, so that a column that takes part of them takes
-    // a fair part)
-    constexpr uint32_t kScramble = 0x9E3779B1u, kInverse = 0x0E8B2F51u;  // product 1 mod 2^32
-    uint32_t *y_order = S.hit + kTilesPerAxis * kTilesPerAxis;
-    y_order[tid] = order_of(sample.y);
-    S.key[tid] = static_cast<uint64_t>(order_of(sample.x)) << 32 | tid * kScramble;
-    __syncthreads();
-    sort_keys(S.key);
-    const uint64_t k = S.key[tid];
-    if (tid == first_of(column)) S.cut[column] = value_of(static_cast<uint32_t>(k >> 32));
-    __syncthreads();
-    S.key[tid] = static_cast<uint64_t>(column) << 32 | y_order[static_cast<uint32_t>(k) * kInverse];
-    __syncthreads();
-    sort_keys(S.key);
-  }
-  auto cut_x = [&](int c) { return even ? x0 + c * (dx * share) : S.cut[c]; };
-  auto cut_y = [&](int r) {
-    if (even) return y0 + r * (dy * share);
-    const int a = first_of(cx), b = first_of(cx + 1);
-    return value_of(static_cast<uint32_t>(S.key[a + ((b - a) * r * inv >> 16)]));
-  };
-  if (tid < g * g) {
-    TileRect R = {-inf, -inf, __builtin_nanf(""), __builtin_nanf("")};
-    if (cx > 0) R.x0 = cut_x(cx);
-    if (cy > 0) R.y0 = cut_y(cy);
-    if (cx < g - 1) R.x1 = cut_x(cx + 1);
-    if (cy < g - 1) R.y1 = cut_y(cy + 1);
-    P.tile[S.start + tid] = R;
-  }
+  if (tid == 0)
+    P.large[old >> 32] =
+        LargeFrame{lo, n, even ? g : -g, static_cast<uint32_t>(old), e[0], e[1], dx, dy, 0};
   __syncthreads();
 }
 
@@ -1125,6 +1070,69 @@ __device__ void search_part(const MergeParams &P, TileLds &S, const LargeFrame &
   __syncthreads();
 }
 
+// Floats as integers in the same order, NaN as -infinity; and back.
+__device__ __forceinline__ uint32_t order_of(float v) {
+  const uint32_t b = __float_as_uint(fmaxf(v, -__builtin_inff()));
+  return b ^ ((b & 0x80000000u) ? 0xFFFFFFFFu : 0x80000000u);
+}
+__device__ __forceinline__ float value_of(uint32_t o) {
+  return __uint_as_float(o ^ ((o & 0x80000000u) ? 0x80000000u : 0xFFFFFFFFu));
+}
+
+// Sorts key[0 .. kLocal) upwards (bitonic), one element per thread. Called after a barrier,
+// ends with one.
+__device__ __forceinline__ void sort_keys(uint64_t *key) {
+  const int i = threadIdx.x;
+  for (int size = 2; size <= kLocal; size *= 2)
+    for (int d = size / 2; d > 0; d /= 2) {
+      const uint64_t a = key[i], b = key[i ^ d];
+      const bool low = ((i & d) == 0) == ((i & size) == 0);  // this place takes the smaller
+      __syncthreads();
+      key[i] = (a < b) == low ? a : b;
+      __syncthreads();
+    }
+}
+
+// The rectangle of tile (tx, ty) of a frame whose tiles go by its samples: g columns of equally
+// many samples, each cut into g rows of equally many. Called by the whole workgroup, ends with a
+// barrier. (A tile computes its own rectangle, with the same cuts as its neighbours. With this
+// in the pass that lists the frames, that pass was up to 1.5 us slower for all frames: its code
+// no longer fitted its registers.)
+__device__ TileRect uneven_rect(const MergeParams &P, TileLds &S, const LargeFrame &L, int tx,
+                                int ty) {
+  static_assert(kTileThreads == kLocal && sizeof(S.own) >= 12 * kLocal, "samples in own");
+  const int tid = threadIdx.x, g = -L.g;
+  uint64_t *key = reinterpret_cast<uint64_t *>(S.own);
+  uint32_t *y_order = reinterpret_cast<uint32_t *>(key + kLocal);
+  // the first of column c's samples (divisions by g, integer ones too, may expand to fused
+  // multiply-adds: 1 / g in 16 bits)
+  const int inv = static_cast<int>(65536.0f * __builtin_amdgcn_rcpf(g));
+  auto first_of = [&](int c) { return c < g ? c * inv * kLocal >> 16 : kLocal; };
+  const int a = first_of(tx), b = first_of(tx + 1);
+  // (samples of one x in scrambled order, so that a column that takes part of them takes a fair
+  // part)
+  constexpr uint32_t kScramble = 0x9E3779B1u, kInverse = 0x0E8B2F51u;  // product 1 mod 2^32
+  const float4 sample = P.rec[L.lo + sample_at(L.n, tid)].box;
+  TileRect R = {-__builtin_inff(), -__builtin_inff(), __builtin_nanf(""), __builtin_nanf("")};
+  y_order[tid] = order_of(sample.y);
+  key[tid] = static_cast<uint64_t>(order_of(sample.x)) << 32 | tid * kScramble;
+  __syncthreads();
+  for (int axis = 0;; ++axis) {
+    sort_keys(key);
+    if (axis == 1) break;
+    if (tx > 0) R.x0 = value_of(static_cast<uint32_t>(key[a] >> 32));
+    if (tx < g - 1) R.x1 = value_of(static_cast<uint32_t>(key[b] >> 32));
+    const uint32_t y = y_order[static_cast<uint32_t>(key[tid]) * kInverse];
+    __syncthreads();
+    key[tid] = tid >= a && tid < b ? y : ~uint64_t(0);  // the column's first
+    __syncthreads();
+  }
+  if (ty > 0) R.y0 = value_of(static_cast<uint32_t>(key[(b - a) * ty * inv >> 16]));
+  if (ty < g - 1) R.y1 = value_of(static_cast<uint32_t>(key[(b - a) * (ty + 1) * inv >> 16]));
+  __syncthreads();
+  return R;
+}
+
 __global__ __launch_bounds__(kTileThreads) void tile_kernel(const MergeParams P) {
   __shared__ TileLds S;
   const unsigned long long used = *P.large_used;
@@ -1140,7 +1148,16 @@ __global__ __launch_bounds__(kTileThreads) void tile_kernel(const MergeParams P)
       if (hits < 64) break;
     }
     const LargeFrame L = P.large[k];
-    const TileRect R = P.tile[v];
+    const int g = abs(L.g), t = static_cast<int>(v - L.start), ty = t / g, tx = t - ty * g;
+    TileRect R = {-inf, -inf, __builtin_nanf(""), __builtin_nanf("")};
+    if (L.g < 0) {
+      R = uneven_rect(P, S, L, tx, ty);
+    } else {
+      if (tx > 0) R.x0 = L.x0 + tx * L.dx;
+      if (ty > 0) R.y0 = L.y0 + ty * L.dy;
+      if (tx < g - 1) R.x1 = L.x0 + (tx + 1) * L.dx;
+      if (ty < g - 1) R.y1 = L.y0 + (ty + 1) * L.dy;
+    }
     int n_own = 0, p0 = 0;  // collected until the next ones do not fit, then searched
     while (p0 < L.n || n_own > 0) {
       bool full = p0 >= L.n;
@@ -1480,7 +1497,7 @@ size_t round16(size_t v) { return (v + 15) / 16 * 16; }
 
 // Bytes of the workspace: the look-back words and three more, per frame 516 bytes (12 past
 // 16,384 frames) and per detection 344. The table of bins takes at most 128 KB of that, the
-// passes' arrays 113 bytes per detection (149 with several frames per bin); the rest holds
+// passes' arrays 112 bytes per detection (148 with several frames per bin); the rest holds
 // suppressor lists of more than kPredSlots.
 size_t workspace_bytes(int32_t n_max, int32_t n_frames) {
   const size_t n = static_cast<size_t>(n_max), f = static_cast<size_t>(n_frames);
@@ -1513,10 +1530,8 @@ size_t lay_out(uint8_t *ws, int32_t n_max, MergeParams &P) {
   P.state = words + 3;
   take(P.table, static_cast<size_t>(P.n_chunks) * P.n_bins);
   take(P.bin_begin, static_cast<size_t>(P.n_bins) + 1);
-  // Listed frames have more than 496 detections (fewer fit decide_rows wherever they start),
-  // and a frame of n at most (sqrt(n / kTileDets) + 1)^2 tiles, 9 of 1,025 at the most.
+  // Listed frames have more than 496 detections: fewer fit decide_rows wherever they start.
   take(P.large, n / 496 + 1);
-  take(P.tile, n / 32 + 1);
   at = (at + sizeof(Rec) - 1) / sizeof(Rec) * sizeof(Rec);  // (if the workspace is so aligned)
   take(P.rec, n);
   P.crec = P.rec;
