@@ -24,8 +24,8 @@
  *    never lets a C++ exception cross the ABI. A device call that returns an error
  *    has enqueued nothing.
  *  - Device buffers need only their natural alignment (4 bytes for int32/float, 2 for
- *    fp16); tg_stitch takes a faster path when `out` is 16-byte aligned and canvas_w
- *    is a multiple of 8.
+ *    fp16); tg_stitch takes a faster path when `out` is 16-byte aligned and
+ *    canvas_w * canvas_h is a multiple of 8.
  */
 #ifndef TG_H
 #define TG_H

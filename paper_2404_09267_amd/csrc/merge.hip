@@ -36,8 +36,8 @@
 //  6. compact: the kept detections in input order.
 // Measured (unstitched detections, IoU 0.5 across patches), with the eight launches of a
 // grid index per frame before: 8,249 in 20 frames 45.6 -> 27 us; 47,939 in 8 frames
-// 111 -> 47; 164,685 in 1,920 frames 62.7 -> 45.5; 20,000 in one frame 367 -> 141, crowded
-// into 300 x 300 pixels 619 ms (its pairs overran the lists) -> 4.1 ms.
+// 111 -> 48; 164,685 in 1,920 frames 62.7 -> 45.4; 20,000 in one frame 317 -> 113, crowded
+// into 300 x 300 pixels 619 ms (its pairs overran the lists) -> 1.7 ms.
 // Tile and resolve return at once when no frame is listed. Inputs of at most kTiny
 // detections (by capacity) take one launch instead (tiny_kernel).
 #include <hip/hip_runtime.h>

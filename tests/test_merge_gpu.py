@@ -104,11 +104,11 @@ def test_large_frames(torch):
 
 
 def test_large_frames_special_boxes(torch):
-    """A 3000-detection frame with the cases the cell index treats apart: boxes with
+    """A 3000-detection frame with the cases the bands and tiles treat apart: boxes with
     infinite corners, inverted boxes, boxes wider than the frame, duplicates of one box
     (up to 239 suppressors each: their whole lists go to the overflow area), and a
     negative threshold (every pair suppresses: the lists need about 4.5 M entries, far
-    past the overflow area's 48,000, so most detections search their lists again in
+    past the overflow area's 170,000, so most detections search their lists again in
     the rounds)."""
     rng = np.random.default_rng(19)
     dets, scores = random_dets(rng, 3000, 1, 12, span=800.0)
@@ -126,8 +126,7 @@ def test_large_frames_special_boxes(torch):
 
 
 def test_frames_around_the_matrix_limit(torch):
-    """Frames of 437, 439, 448, 512 and 513 detections side by side (through the spatial
-    index: frames of up to 256 detections are decided in one workgroup's LDS)."""
+    """Frames of 437, 439, 448, 512 and 513 detections side by side, a workgroup each."""
     rng = np.random.default_rng(12)
     sizes = [437, 439, 448, 512, 513]
     dets, scores = random_dets(rng, sum(sizes), len(sizes), 8, span=400.0)
@@ -137,8 +136,7 @@ def test_frames_around_the_matrix_limit(torch):
 
 
 def test_frames_around_the_small_workgroup_limit(torch):
-    """Frames averaging at most 256 detections take 256-thread workgroups: frames of 256
-    are decided in LDS, of 257 through the spatial index, side by side."""
+    """Frames of 256 and 257 detections beside small ones, none and one."""
     rng = np.random.default_rng(14)
     sizes = [256, 257, 40, 1, 0, 120]
     dets, scores = random_dets(rng, sum(sizes), len(sizes), 6, span=250.0)
@@ -169,16 +167,15 @@ def test_small_frames_special_boxes(torch):
 
 
 def test_many_frames(torch):
-    """More frames than the LDS histograms hold (4096): direct global counters."""
+    """5,000 frames of four detections: bins of twenty frames, ordered in LDS."""
     rng = np.random.default_rng(13)
     dets, scores = random_dets(rng, 20000, 5000, 6, span=100.0)
     check(torch, dets, scores, 5000, 0.5, True)
 
 
 def test_many_frames_with_large_ones(torch):
-    """3,000 frames of 25 detections with four of 257-600 among them, the large ones on
-    both sides of frame 2048 (the rounds step through frames 2048 apart) and more than
-    65,536 detections (the search steps through them 65,536 apart). Frames are merged
+    """3,000 frames of 25 detections with four of 257-600 among them, in bins of twelve frames,
+    and more than 65,536 detections (the compaction by look-back). Frames are merged
     independently, so the oracle checks the large frames and 200 others on their own; the
     compacted output is the kept detections in input order."""
     from oracle import merge
