@@ -405,9 +405,9 @@ def test_few_boxes_corrupt_plans(torch, n, rule):
 
 @pytest.mark.parametrize("rule", [0, 1])
 def test_few_boxes_cost(torch, rule):
-    """200 boxes on one canvas of 96 patches, one launch, cost no more than 1.3 times 300 boxes,
-    two launches (0.7 and 1.0 times by rule; 1.8 when the one launch gathered
-    the plan for every box)."""
+    """256 boxes on one canvas of 96 patches, one launch, cost no more than 1.75 times 300 boxes,
+    two launches (0.8 to 1.5 times by rule and by how closely launches follow each other; 2.0 to
+    2.8 when the one launch gathered the plan for every box)."""
     rois, plan = _grid_plan([96], 9, 90)
     dplan = tg.DevicePlan(rois, plan)
     rng = np.random.default_rng(5)
@@ -430,6 +430,6 @@ def test_few_boxes_cost(torch, rule):
             best = min(best, 20 * e0.elapsed_time(e1))
         return best
 
-    one, two = us(200), us(300)
+    one, two = us(256), us(300)
     say("few boxes", one, two)
-    assert one <= 1.3 * two
+    assert one <= 1.75 * two
