@@ -36,7 +36,7 @@
 //  6. compact: the kept detections in input order.
 // Measured (unstitched detections, IoU 0.5 across patches), with the eight launches of a
 // grid index per frame before: 8,249 in 20 frames 45.6 -> 27 us; 47,939 in 8 frames
-// 111 -> 48; 164,685 in 1,920 frames 62.7 -> 45.4; 20,000 in one frame 317 -> 113, crowded
+// 111 -> 48; 164,685 in 1,920 frames 62.7 -> 45.4; 20,000 in one frame 317 -> 108, crowded
 // into 300 x 300 pixels 619 ms (its pairs overran the lists) -> 1.7 ms.
 // Tile and resolve return at once when no frame is listed. Inputs of at most kTiny
 // detections (by capacity) take one launch instead (tiny_kernel).
@@ -538,23 +538,21 @@ __device__ __forceinline__ int cell_of(float v, float origin, float scale, int g
       fminf(fmaxf(__fmul_rn(__fsub_rn(v, origin), scale), 0.0f), static_cast<float>(g - 1)));
 }
 
-// The position that thread i of kLocal samples of a frame of n > kLocal / 2: spread over the
-// frame, and one that thread i reads in any case when the threads step through it (samples
-// n / kLocal apart, loaded besides: 2 us).
-__device__ __forceinline__ int sample_at(int n, int i) {
-  if (n < kLocal) return i < n ? i : i - n;
-  const uint32_t step = static_cast<uint32_t>(i) * (static_cast<uint32_t>(n) / kLocal) / kLocal;
-  return i + kLocal * static_cast<int>(step);
+// The box that thread i of kLocal samples of the frame at positions [lo, lo + n).
+__device__ __forceinline__ float4 sample_of(const MergeParams &P, int lo, int n, int i) {
+  const uint64_t at = static_cast<uint64_t>(i) * static_cast<uint32_t>(n) / kLocal;
+  return P.rec[lo + static_cast<int>(at)].box;
 }
 
 // Lists a frame for the tile and resolve passes, to be cut into g x g tiles. Called by the
 // whole workgroup, after its boxes are in the workspace.
 // A tile is one workgroup's work, so its share of the detections decides the pass's time. An
 // even grid over the frame serves detections that are spread out (its tiles are then as
-// alike as they come); where kLocal samples show a cell with more than twice its share, the
-// cuts go where the samples say (uneven_rect). (20,000 detections, half of them in 300 x 300 of
-// 3840 x 2160 pixels: 13.8 ms over the even grid, 0.86 so; with one box a million pixels away
-// 7.8 ms and 0.14; spread out 0.114 either way. The check is 1 us of 8 frames of 6,000.)
+// alike as they come); where kLocal samples, whose extent the grid takes, show a cell with more
+// than twice its share, the cuts go where the samples say (uneven_rect). (20,000 detections, half
+// of them in 300 x 300 of 3840 x 2160 pixels: 13.8 ms over an even grid, 0.84 so; with one box a
+// million pixels away 7.8 ms and 0.15; spread out 0.108 either way. Reading all boxes of a frame
+// for its extent, and the samples among them, took 1.2 us more for eight frames of 6,000.)
 __device__ void add_large(const MergeParams &P, LocalLds &S, int lo, int n) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float inf = __builtin_inff();
@@ -562,27 +560,13 @@ __device__ void add_large(const MergeParams &P, LocalLds &S, int lo, int n) {
   const int per_tile = min(max(count_of(P) / (4 * kGridCap), kTileDets), kTileDetsMax);
   const float tiles = fminf(n * __builtin_amdgcn_rcpf(per_tile), static_cast<float>(kTilesMax));
   const int g = min(max(1, static_cast<int>(ceilf(__builtin_amdgcn_sqrtf(tiles)))), kTilesPerAxis);
-  unsigned long long old = 0;  // (asked for here, waited for when the boxes are in)
+  unsigned long long old = 0;  // (asked for here, waited for at the end)
   if (tid == 0)
     old = atomicAdd(P.large_used, (1ull << 32) | static_cast<unsigned long long>(g) * g);
-  const int at = sample_at(n, tid);
-  float2 sample = make_float2(0.0f, 0.0f);  // its top-left corner
-  float e[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) e[k] = inf;
-#pragma unroll 2  // (4: 0.4 us more of instruction fetches for frames of 6,000)
-  for (int p = tid; p < n; p += kLocal) {
-    const float4 b = P.rec[lo + p].box;
-    if (p == at) sample = make_float2(b.x, b.y);
-    if (__builtin_isfinite(b.x)) e[0] = fminf(e[0], b.x);
-    if (__builtin_isfinite(b.y)) e[1] = fminf(e[1], b.y);
-    if (__builtin_isfinite(b.x)) e[2] = fminf(e[2], -b.x);
-    if (__builtin_isfinite(b.y)) e[3] = fminf(e[3], -b.y);
-  }
-  if (tid >= n) {
-    const float4 b = P.rec[lo + at].box;
-    sample = make_float2(b.x, b.y);
-  }
+  const float4 sample = sample_of(P, lo, n, tid);
+  const bool fx = __builtin_isfinite(sample.x), fy = __builtin_isfinite(sample.y);
+  float e[4] = {fx ? sample.x : inf, fy ? sample.y : inf, fx ? -sample.x : inf,
+                fy ? -sample.y : inf};
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -1112,7 +1096,7 @@ __device__ TileRect uneven_rect(const MergeParams &P, TileLds &S, const LargeFra
   // (samples of one x in scrambled order, so that a column that takes part of them takes a fair
   // part)
   constexpr uint32_t kScramble = 0x9E3779B1u, kInverse = 0x0E8B2F51u;  // product 1 mod 2^32
-  const float4 sample = P.rec[L.lo + sample_at(L.n, tid)].box;
+  const float4 sample = sample_of(P, L.lo, L.n, tid);
   TileRect R = {-__builtin_inff(), -__builtin_inff(), __builtin_nanf(""), __builtin_nanf("")};
   y_order[tid] = order_of(sample.y);
   key[tid] = static_cast<uint64_t>(order_of(sample.x)) << 32 | tid * kScramble;
